@@ -4,11 +4,20 @@
 //   h1 = relu(X W1^T + b1), h2 = relu(h1 W2^T + b2), y = softplus(h2 . w3 + b3)
 // and a penalty head lr = mean_b(h2) . wr + br.  Loss
 //   L = mean_b (y_b - t_b)^2 + lam (lr - lr_t)^2.
-// Flat parameter order W1, b1, W2, b2, w3, b3, wr, br (float32).  Every sum
-// over rows is a fixed-order loop in one thread, so gradients are
-// deterministic.  The sizes are small (H = 128): these kernels are latency
-// bound and use plain fp32 FMA; inference can keep the hidden activations in
-// bf16.
+// Flat parameter order W1, b1, W2, b2, w3, b3, wr, br (float32).
+//
+// A training step is five launches: k_mlp_forward (both layers, the intensity
+// head and the block's share of mean(h2) and of the loss), k_mlp_scalars
+// (penalty head, loss, dL/dlr), k_mlp_backward (dz3, dz2 and, through W2, dz1),
+// k_mlp_wgrad (every weight and bias gradient, row ranges apart) and
+// k_mlp_grads (their sums).  The layer products run on the fp32 16x16x4 MFMA,
+// the sums over rows (weight gradients, mean, loss) in fp64 in a fixed order,
+// so gradients are deterministic.  The sizes are small (B about 3 000, H =
+// 128: 0.3 GFLOP a step), so launches and dependent loads bound a step, not
+// arithmetic: with one thread walking all B rows of every weight gradient,
+// mean and loss sum, a step took 3.2 ms at B = 2 981, H = 128 (2.9 ms in those
+// sums); now 0.147 ms with its copies and the Adam step: forward 18 us, scalars
+// 6, backward 11, weight gradients 15, their sums 5.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -17,14 +26,20 @@
 #include <exception>
 #include <new>
 #include <string>
-#include <type_traits>
 #include <vector>
 
 #include "../../include/admmbb.h"
+#include "scalars.h"
 
 namespace {
 
-constexpr int kRows = 16;  // rows per block of the dense kernels
+using admmbb::group_allsum;
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+constexpr int kRows = 16;  // rows per block of the layer kernels: one MFMA tile
+constexpr int kNt = 256;   // threads of every kernel but k_mlp_scalars
 
 struct HipErr {
   hipError_t e;
@@ -39,233 +54,369 @@ __device__ __forceinline__ float bf16_round(float x) {
   return __uint_as_float(u & 0xffff0000u);
 }
 
-// out[b][k] = sum_i act(in[b][i]) W[k][i] + bias[k]; act = relu when relu_in,
-// inputs rounded to bf16 when bf16_in.  Block: H threads (one output column
-// each), kRows rows staged in LDS.
-__global__ void k_dense(const float* __restrict__ in, int nin, const float* __restrict__ W,
-                        const float* __restrict__ bias, float* __restrict__ out, int B, int H, int relu_in,
-                        int bf16_in) {
-  extern __shared__ float xs[];  // kRows x nin
-  const int b0 = blockIdx.x * kRows;
-  for (int idx = threadIdx.x; idx < kRows * nin; idx += blockDim.x) {
-    const int r = idx / nin, i = idx % nin;
-    float v = (b0 + r < B) ? in[static_cast<int64_t>(b0 + r) * nin + i] : 0.0f;
-    if (relu_in) v = fmaxf(v, 0.0f);
-    if (bf16_in) v = bf16_round(v);
-    xs[idx] = v;
+// LDS row stride (floats) of an activation tile with n columns: whole
+// four-column steps (zero beyond n) and four more, so that for n a multiple of
+// 64 the 16 rows that one load instruction reads start in different banks.
+__host__ __device__ __forceinline__ int lds_stride(int n) { return ((n + 3) & ~3) + 4; }
+
+// Everything the kernels address, by value.
+struct MlpArgs {
+  const float* X;  // B x F
+  const float* t;  // B, or nullptr (no loss)
+  float *z1, *z2;  // B x H pre-activations kept for the backward pass (nullptr: inference)
+  float *z3, *y, *dz3, *dz2, *dz1, *pooled;
+  const float* th;   // parameters
+  double* blk;       // per forward block: H sums of h2 over its rows, then its sum of (y - t)^2
+  double* sc;        // lr, L, dL/dlr
+  double* part;      // per row range: np gradient sums
+  float* g;          // gradient
+  int64_t oW1, ob1, oW2, ob2, ow3, ob3, owr, obr, np;
+  int B, F, H, nblk, splits, rows_per_split;
+  float lr_t, lam;
+};
+
+// One layer of a block: dst[r][k] = bias[k] + sum_i src[r][i] W[k][i] for its 16
+// rows, columns k in 16-wide groups dealt to the four waves.  Each MFMA step
+// takes four consecutive i in ascending order (lane l: row or column l % 16,
+// i = l / 16 of the four), which gives the sums of a plain ascending fma chain.
+// src is zero beyond nin.  fin(r, k, v) receives every entry.
+template <class Fin>
+__device__ __forceinline__ void layer_rows(const float* src, int ss, int nin, const float* __restrict__ W,
+                                           const float* __restrict__ bias, int H, Fin fin) {
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, m = l & 15, kk = l >> 4;
+  for (int k0 = 16 * w; k0 < H; k0 += 64) {
+    const int k = k0 + m;
+    const float* wk = W + static_cast<int64_t>(k < H ? k : H - 1) * nin + kk;
+    const float* sm = src + m * ss + kk;
+    v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    int i0 = 0;
+    for (; i0 + 64 <= nin; i0 += 64) {
+      float b[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) b[q] = wk[i0 + 4 * q];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sm[i0 + 4 * q], b[q], acc, 0, 0, 0);
+    }
+    for (; i0 < nin; i0 += 4)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sm[i0], i0 + kk < nin ? wk[i0] : 0.0f, acc, 0, 0, 0);
+    // item r of the lane: row 4 (l / 16) + r, column k0 + l % 16
+    if (k < H) {
+      const float bk = bias[k];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) fin(4 * kk + r, k, acc[r] + bk);
+    }
   }
-  __syncthreads();
-  const int k = threadIdx.x;
-  if (k >= H) return;
-  float acc[kRows];
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) acc[r] = 0.0f;
-  const float* wk = W + static_cast<int64_t>(k) * nin;
-  for (int i = 0; i < nin; ++i) {
-    const float w = wk[i];
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) acc[r] = fmaf(xs[r * nin + i], w, acc[r]);
-  }
-  const float bk = bias[k];
-#pragma unroll
-  for (int r = 0; r < kRows; ++r)
-    if (b0 + r < B) out[static_cast<int64_t>(b0 + r) * H + k] = acc[r] + bk;
 }
 
-// bf16 inference with the hidden activations stored as bf16:
-// out[b][k] = bf16(relu(sum_i in[b][i] W[k][i] + bias[k])), in given as fp32
-// (the network input) or as bf16 bits (a stored hidden layer).
-__device__ __forceinline__ float bf16_value(uint16_t h) { return __uint_as_float(static_cast<uint32_t>(h) << 16); }
-__device__ __forceinline__ uint16_t bf16_bits(float x) { return static_cast<uint16_t>(__float_as_uint(bf16_round(x)) >> 16); }
+// Both layers and the intensity head of 16 rows.  BF16 (inference): the hidden
+// activations rounded to bf16 as they are stored in LDS, weights and sums fp32.
+// LDS: the input tile, later h2 (the input is dead by then), and h1.
+template <bool BF16>
+__global__ __launch_bounds__(kNt) void k_mlp_forward(MlpArgs a) {
+  extern __shared__ __align__(16) float smem[];
+  __shared__ float ysh[kRows];
+  const int H = a.H, F = a.F, B = a.B;
+  const int sF = lds_stride(F), sH = lds_stride(H);
+  float* h1 = smem;               // kRows x sH
+  float* xs = smem + kRows * sH;  // kRows x max(sF, sH)
+  const int b0 = static_cast<int>(blockIdx.x) * kRows;
+  const int nr = B - b0 < kRows ? B - b0 : kRows;
+  const int tid = threadIdx.x;
+  for (int e = tid; e < kRows * sF; e += kNt) {
+    const int r = e / sF, i = e - r * sF;
+    xs[e] = (r < nr && i < F) ? a.X[static_cast<int64_t>(b0 + r) * F + i] : 0.0f;
+  }
+  // zero columns H .. of the hidden tiles: the next product reads whole groups
+  for (int e = tid; e < kRows * (sH - H); e += kNt) h1[(e / (sH - H)) * sH + H + e % (sH - H)] = 0.0f;
+  __syncthreads();
+  auto act = [](float v) {
+    v = fmaxf(v, 0.0f);
+    return BF16 ? bf16_round(v) : v;
+  };
+  layer_rows(xs, sF, F, a.th + a.oW1, a.th + a.ob1, H, [&](int r, int k, float v) {
+    h1[r * sH + k] = act(v);
+    if (!BF16 && a.z1 != nullptr && r < nr) a.z1[static_cast<int64_t>(b0 + r) * H + k] = v;
+  });
+  __syncthreads();
+  float* h2 = xs;
+  layer_rows(h1, sH, H, a.th + a.oW2, a.th + a.ob2, H, [&](int r, int k, float v) {
+    h2[r * sH + k] = act(v);
+    if (!BF16 && a.z2 != nullptr && r < nr) a.z2[static_cast<int64_t>(b0 + r) * H + k] = v;
+  });
+  __syncthreads();
+  {
+    // 16 lanes a row
+    const int r = tid >> 4, c = tid & 15;
+    const float* w3 = a.th + a.ow3;
+    float s = 0.0f;
+    for (int k = c; k < H; k += 16) s = fmaf(h2[r * sH + k], w3[k], s);
+    s = group_allsum<16>(s);
+    if (c == 0) {
+      const float z = s + a.th[a.ob3];
+      const float y = fmaxf(z, 0.0f) + log1pf(expf(-fabsf(z)));
+      ysh[r] = y;
+      if (r < nr) {
+        if (a.z3 != nullptr) a.z3[b0 + r] = z;
+        a.y[b0 + r] = y;
+      }
+    }
+  }
+  double* bp = a.blk + static_cast<int64_t>(blockIdx.x) * (H + 1);
+  for (int k = tid; k < H; k += kNt) {
+    double s = 0.0;
+    for (int r = 0; r < nr; ++r) s += static_cast<double>(h2[r * sH + k]);
+    bp[k] = s;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    double se = 0.0;
+    if (a.t != nullptr)
+      for (int r = 0; r < nr; ++r) {
+        const double d = static_cast<double>(ysh[r]) - static_cast<double>(a.t[b0 + r]);
+        se += d * d;
+      }
+    bp[H] = se;
+  }
+}
 
-template <class TIN>
-__global__ void k_dense_bf16(const TIN* __restrict__ in, int nin, const float* __restrict__ W,
-                             const float* __restrict__ bias, uint16_t* __restrict__ out, int B, int H) {
-  extern __shared__ float xs[];  // kRows x nin
-  const int b0 = blockIdx.x * kRows;
-  for (int idx = threadIdx.x; idx < kRows * nin; idx += blockDim.x) {
-    const int r = idx / nin, i = idx % nin;
+// pooled = mean_b(h2), lr, the loss and dL/dlr from the forward blocks' sums:
+// one workgroup; column k's blocks are dealt to nsl threads (as many as 1024
+// threads give every column), their sums added in order, so nothing depends on
+// timing.
+__global__ __launch_bounds__(1024) void k_mlp_scalars(MlpArgs a) {
+  __shared__ double sh[1024];
+  __shared__ double wsum[16];
+  __shared__ double se;  // sum of squared errors (the last column)
+  const int tid = threadIdx.x, H = a.H, C = H + 1;
+  const int w = C < 1024 ? C : 1024;
+  const int nsl = 1024 / w;
+  double lr = 0.0;
+  for (int c0 = 0; c0 < C; c0 += w) {
+    const int c = c0 + tid % w, sl = tid / w;
+    double s = 0.0;
+    if (sl < nsl && c < C) {
+      int b = sl;
+      for (; b + 7 * nsl < a.nblk; b += 8 * nsl) {
+        double q[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) q[u] = a.blk[static_cast<int64_t>(b + u * nsl) * C + c];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += q[u];
+      }
+      for (; b < a.nblk; b += nsl) s += a.blk[static_cast<int64_t>(b) * C + c];
+    }
+    sh[tid] = s;
+    __syncthreads();
+    if (sl == 0 && c < C) {
+      for (int u = 1; u < nsl; ++u) s += sh[u * w + tid];
+      if (c < H) {
+        const float p = static_cast<float>(s / a.B);
+        a.pooled[c] = p;
+        lr += static_cast<double>(p) * static_cast<double>(a.th[a.owr + c]);
+      } else {
+        se = s;
+      }
+    }
+    __syncthreads();
+  }
+  lr = group_allsum<64>(lr);
+  if ((tid & 63) == 0) wsum[tid >> 6] = lr;
+  __syncthreads();
+  if (tid == 0) {
+    double s = static_cast<double>(a.th[a.obr]);
+    for (int q = 0; q < 16; ++q) s += wsum[q];
+    const double d = s - static_cast<double>(a.lr_t), lam = static_cast<double>(a.lam);
+    a.sc[0] = s;
+    a.sc[1] = se / a.B + lam * d * d;
+    a.sc[2] = 2.0 * lam * d;
+  }
+}
+
+// Of 16 rows: dz3 = 2 (y - t) / B sigmoid(z3), dz2 = (dz3 w3 + dL/dlr wr / B)
+// [z2 > 0] and dz1 = (dz2 W2) [z1 > 0] by the MFMA, operands as in layer_rows
+// with W2 read down its columns (64 contiguous bytes per row and load).
+__global__ __launch_bounds__(kNt) void k_mlp_backward(MlpArgs a) {
+  extern __shared__ __align__(16) float smem[];
+  __shared__ float d3[kRows];
+  const int H = a.H, B = a.B, sH = lds_stride(H);
+  const int b0 = static_cast<int>(blockIdx.x) * kRows;
+  const int nr = B - b0 < kRows ? B - b0 : kRows;
+  const int tid = threadIdx.x;
+  if (tid < kRows) {
+    float d = 0.0f;
+    if (tid < nr) {
+      const float s = 1.0f / (1.0f + expf(-a.z3[b0 + tid]));
+      d = 2.0f * (a.y[b0 + tid] - a.t[b0 + tid]) / B * s;
+      a.dz3[b0 + tid] = d;
+    }
+    d3[tid] = d;
+  }
+  __syncthreads();
+  const float dlr = static_cast<float>(a.sc[2]);
+  for (int e = tid; e < kRows * sH; e += kNt) {
+    const int r = e / sH, k = e - r * sH;
     float v = 0.0f;
-    if (b0 + r < B) {
-      if constexpr (std::is_same<TIN, uint16_t>::value)
-        v = bf16_value(in[static_cast<int64_t>(b0 + r) * nin + i]);
+    if (r < nr && k < H) {
+      const int64_t o = static_cast<int64_t>(b0 + r) * H + k;
+      const float g = d3[r] * a.th[a.ow3 + k] + dlr * a.th[a.owr + k] / B;
+      v = a.z2[o] > 0.0f ? g : 0.0f;
+      a.dz2[o] = v;
+    }
+    smem[e] = v;
+  }
+  __syncthreads();
+  const int w = tid >> 6, l = tid & 63, m = l & 15, kk = l >> 4;
+  const float* W2 = a.th + a.oW2;
+  for (int i0 = 16 * w; i0 < H; i0 += 64) {
+    const int i = i0 + m, ic = i < H ? i : H - 1;
+    v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    const float* sm = smem + m * sH + kk;
+    const float* wp = W2 + static_cast<int64_t>(kk) * H + ic;
+    int k0 = 0;
+    for (; k0 + 64 <= H; k0 += 64) {
+      float b[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) b[q] = wp[static_cast<int64_t>(k0 + 4 * q) * H];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sm[k0 + 4 * q], b[q], acc, 0, 0, 0);
+    }
+    for (; k0 < H; k0 += 4)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sm[k0], k0 + kk < H ? wp[static_cast<int64_t>(k0) * H] : 0.0f, acc, 0,
+                                                 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 4 * kk + r;
+      if (i < H && row < nr) {
+        const int64_t o = static_cast<int64_t>(b0 + row) * H + i;
+        a.dz1[o] = a.z1[o] > 0.0f ? acc[r] : 0.0f;
+      }
+    }
+  }
+}
+
+// Weight and bias gradients of one layer as one product over rows:
+// gW[k][i] = sum_b dz[b][k] act(in[b][i]), gb[k] with a column of ones at
+// i = nin.  Three layers: (dz1, X), (dz2, relu z1) and (dz3, relu z2; one k).
+struct Layer {
+  const float *dz, *in;
+  int K, nin, relu;
+  int64_t oW, ob;
+};
+__device__ __forceinline__ Layer layer_of(const MlpArgs& a, int which) {
+  if (which == 0) return Layer{a.dz2, a.z1, a.H, a.H, 1, a.oW2, a.ob2};
+  if (which == 1) return Layer{a.dz1, a.X, a.H, a.F, 0, a.oW1, a.ob1};
+  return Layer{a.dz3, a.z2, 1, a.H, 1, a.ow3, a.ob3};
+}
+__host__ __device__ __forceinline__ int wgrad_tiles(int K, int nin) { return ((K + 63) / 64) * ((nin + 64) / 64); }
+
+// One 64 x 64 tile of one layer's gradient over one range of rows: wave w takes
+// 16 k and up to four 16-column groups on the fp64 16x16x4 MFMA, four rows a
+// step, operands straight from memory (64 contiguous bytes per row; the
+// activations are L2-resident).  Row ranges make enough blocks to fill the
+// chip (see admm_mlp::plan); their sums go to part, one slice per range.
+__global__ __launch_bounds__(kNt) void k_mlp_wgrad(MlpArgs a) {
+  int tile = static_cast<int>(blockIdx.x), which = 0;
+  for (; which < 2; ++which) {
+    const Layer q = layer_of(a, which);
+    const int n = wgrad_tiles(q.K, q.nin);
+    if (tile < n) break;
+    tile -= n;
+  }
+  const Layer L = layer_of(a, which);
+  const int ni = (L.nin + 64) / 64;
+  const int k0 = (tile / ni) * 64 + 16 * static_cast<int>(threadIdx.x >> 6), i0 = (tile % ni) * 64;
+  if (k0 >= L.K) return;
+  const int l = threadIdx.x & 63, m = l & 15, kk = l >> 4;
+  const int k = k0 + m;
+  int ng = (L.nin + 1 - i0 + 15) / 16;  // column groups of the tile, the ones column included
+  if (ng > 4) ng = 4;
+  const int s = static_cast<int>(blockIdx.y);
+  const int r0 = s * a.rows_per_split;
+  const int r1 = r0 + a.rows_per_split < a.B ? r0 + a.rows_per_split : a.B;
+  v4d acc[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) acc[g] = v4d{0.0, 0.0, 0.0, 0.0};
+  // addresses: a wave-uniform base per step and the lane's offset within four
+  // rows, fixed over the loop; columns clamped into the arrays
+  bool one[4];
+  int off[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int i = i0 + 16 * g + m;
+    one[g] = i >= L.nin;  // the ones column (and, beyond it, columns not written)
+    off[g] = kk * L.nin + (one[g] ? L.nin - 1 : i);
+  }
+  const int offz = kk * L.K + (k < L.K ? k : L.K - 1);
+  auto step = [&](float av, const float* bv) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      if (g < ng) {
+        const float v = one[g] ? 1.0f : (L.relu ? fmaxf(bv[g], 0.0f) : bv[g]);
+        acc[g] =
+            __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(av), static_cast<double>(v), acc[g], 0, 0, 0);
+      }
+  };
+  constexpr int U = 8;  // steps of a round, whose loads are in flight together
+  int b = r0;
+  for (; b + 4 * U <= r1; b += 4 * U) {
+    float av[U], bv[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      av[u] = (L.dz + static_cast<int64_t>(b + 4 * u) * L.K)[offz];
+      const float* in = L.in + static_cast<int64_t>(b + 4 * u) * L.nin;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) bv[u][g] = in[off[g]];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) step(av[u], bv[u]);
+  }
+  for (; b < r1; b += 4) {
+    // rows past the range: a valid row's data, and dz = 0
+    const int up = b + kk < r1 ? 0 : b + kk - (r1 - 1);
+    float av = (L.dz + static_cast<int64_t>(b) * L.K)[offz - up * L.K], bv[4];
+    if (up > 0) av = 0.0f;
+    const float* in = L.in + static_cast<int64_t>(b) * L.nin;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) bv[g] = in[off[g] - up * L.nin];
+    step(av, bv);
+  }
+  // item r of the lane: k index l / 16 + 4 r, column l % 16
+  double* out = a.part + static_cast<int64_t>(s) * a.np;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int i = i0 + 16 * g + m;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int ko = k0 + kk + 4 * r;
+      if (ko >= L.K || i > L.nin) continue;
+      if (i < L.nin)
+        out[L.oW + static_cast<int64_t>(ko) * L.nin + i] = acc[g][r];
       else
-        v = in[static_cast<int64_t>(b0 + r) * nin + i];
+        out[L.ob + ko] = acc[g][r];
     }
-    xs[idx] = v;
   }
-  __syncthreads();
-  const int k = threadIdx.x;
-  if (k >= H) return;
-  float acc[kRows];
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) acc[r] = 0.0f;
-  const float* wk = W + static_cast<int64_t>(k) * nin;
-  for (int i = 0; i < nin; ++i) {
-    const float w = wk[i];
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) acc[r] = fmaf(xs[r * nin + i], w, acc[r]);
-  }
-  const float bk = bias[k];
-#pragma unroll
-  for (int r = 0; r < kRows; ++r)
-    if (b0 + r < B) out[static_cast<int64_t>(b0 + r) * H + k] = bf16_bits(fmaxf(acc[r] + bk, 0.0f));
 }
 
-// y_b = softplus(sum_k h2[b][k] w3[k] + b3) from the stored bf16 activations
-__global__ void k_head_bf16(const uint16_t* __restrict__ h2, const float* __restrict__ w3,
-                            const float* __restrict__ b3, float* __restrict__ z3, float* __restrict__ y, int B, int H) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  float acc = 0.0f;
-  const uint16_t* hr = h2 + static_cast<int64_t>(b) * H;
-  for (int k = 0; k < H; ++k) acc = fmaf(bf16_value(hr[k]), w3[k], acc);
-  const float z = acc + b3[0];
-  z3[b] = z;
-  y[b] = fmaxf(z, 0.0f) + log1pf(expf(-fabsf(z)));
-}
-
-// pooled[k] = mean_b h2[b][k] over the stored bf16 activations (fixed order)
-__global__ void k_pool_bf16(const uint16_t* __restrict__ h2, float* __restrict__ pooled, int B, int H) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= H) return;
+// g = sum of the row ranges' parts in order; the penalty head's gradients
+__global__ __launch_bounds__(kNt) void k_mlp_grads(MlpArgs a) {
+  const int64_t j = static_cast<int64_t>(blockIdx.x) * kNt + threadIdx.x;
+  if (j >= a.np) return;
+  if (j >= a.owr) {
+    const float dlr = static_cast<float>(a.sc[2]);
+    a.g[j] = j < a.obr ? dlr * a.pooled[j - a.owr] : dlr;
+    return;
+  }
   double s = 0.0;
-  for (int b = 0; b < B; ++b) s += bf16_value(h2[static_cast<int64_t>(b) * H + k]);
-  pooled[k] = static_cast<float>(s / B);
-}
-
-// y_b = softplus(sum_k relu(z2[b][k]) w3[k] + b3); z3 stored for the backward pass
-__global__ void k_head(const float* __restrict__ z2, const float* __restrict__ w3, const float* __restrict__ b3,
-                       float* __restrict__ z3, float* __restrict__ y, int B, int H, int bf16_in) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  float acc = 0.0f;
-  const float* zr = z2 + static_cast<int64_t>(b) * H;
-  for (int k = 0; k < H; ++k) {
-    float h = fmaxf(zr[k], 0.0f);
-    if (bf16_in) h = bf16_round(h);
-    acc = fmaf(h, w3[k], acc);
-  }
-  const float z = acc + b3[0];
-  z3[b] = z;
-  y[b] = fmaxf(z, 0.0f) + log1pf(expf(-fabsf(z)));
-}
-
-// pooled[k] = mean_b relu(z2[b][k])  (fixed order)
-__global__ void k_pool(const float* __restrict__ z2, float* __restrict__ pooled, int B, int H) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= H) return;
-  double s = 0.0;
-  for (int b = 0; b < B; ++b) s += fmaxf(z2[static_cast<int64_t>(b) * H + k], 0.0f);
-  pooled[k] = static_cast<float>(s / B);
-}
-
-// penalty head and loss scalars (one thread): lr, L, dlr
-__global__ void k_scalars(const float* __restrict__ pooled, const float* __restrict__ wr,
-                          const float* __restrict__ br, const float* __restrict__ y, const float* __restrict__ t,
-                          int B, int H, float lr_t, float lam, double* __restrict__ out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  double lr = br[0];
-  for (int k = 0; k < H; ++k) lr += static_cast<double>(pooled[k]) * wr[k];
-  double se = 0.0;
-  if (t != nullptr)
-    for (int b = 0; b < B; ++b) {
-      const double d = static_cast<double>(y[b]) - t[b];
-      se += d * d;
-    }
-  out[0] = lr;
-  out[1] = se / B + lam * (lr - lr_t) * (lr - lr_t);
-  out[2] = 2.0 * lam * (lr - lr_t);  // dL/dlr
-}
-
-// dz3_b = 2 (y_b - t_b) / B * sigmoid(z3_b)
-__global__ void k_dz3(const float* __restrict__ y, const float* __restrict__ t, const float* __restrict__ z3,
-                      float* __restrict__ dz3, int B) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  const float s = 1.0f / (1.0f + expf(-z3[b]));
-  dz3[b] = 2.0f * (y[b] - t[b]) / B * s;
-}
-
-// head gradients: g_w3[k] = sum_b dz3_b relu(z2[b][k]); g_b3 = sum_b dz3_b;
-// g_wr[k] = dlr * pooled[k]; g_br = dlr
-__global__ void k_head_grad(const float* __restrict__ z2, const float* __restrict__ dz3,
-                            const float* __restrict__ pooled, const double* __restrict__ sc, float* __restrict__ gw3,
-                            float* __restrict__ gb3, float* __restrict__ gwr, float* __restrict__ gbr, int B, int H) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  const float dlr = static_cast<float>(sc[2]);
-  if (k < H) {
-    double s = 0.0;
-    for (int b = 0; b < B; ++b) s += static_cast<double>(dz3[b]) * fmaxf(z2[static_cast<int64_t>(b) * H + k], 0.0f);
-    gw3[k] = static_cast<float>(s);
-    gwr[k] = dlr * pooled[k];
-  }
-  if (k == 0) {
-    double s = 0.0;
-    for (int b = 0; b < B; ++b) s += dz3[b];
-    gb3[0] = static_cast<float>(s);
-    gbr[0] = dlr;
-  }
-}
-
-// dz2[b][k] = (dz3_b w3[k] + dlr wr[k] / B) [z2[b][k] > 0]
-__global__ void k_dz2(const float* __restrict__ z2, const float* __restrict__ dz3, const float* __restrict__ w3,
-                      const float* __restrict__ wr, const double* __restrict__ sc, float* __restrict__ dz2, int B,
-                      int H) {
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (idx >= static_cast<int64_t>(B) * H) return;
-  const int b = static_cast<int>(idx / H), k = static_cast<int>(idx % H);
-  const float g = dz3[b] * w3[k] + static_cast<float>(sc[2]) * wr[k] / B;
-  dz2[idx] = z2[idx] > 0.0f ? g : 0.0f;
-}
-
-// dz1[b][i] = (sum_k dz2[b][k] W2[k][i]) [z1[b][i] > 0]; block: nin threads, kRows rows
-__global__ void k_back_data(const float* __restrict__ dz, const float* __restrict__ W, const float* __restrict__ z,
-                            float* __restrict__ dzin, int B, int H, int nin) {
-  extern __shared__ float ds[];  // kRows x H
-  const int b0 = blockIdx.x * kRows;
-  for (int idx = threadIdx.x; idx < kRows * H; idx += blockDim.x) {
-    const int r = idx / H, k = idx % H;
-    ds[idx] = (b0 + r < B) ? dz[static_cast<int64_t>(b0 + r) * H + k] : 0.0f;
-  }
-  __syncthreads();
-  const int i = threadIdx.x;
-  if (i >= nin) return;
-  float acc[kRows];
+  int p = 0;
+  for (; p + 8 <= a.splits; p += 8) {
+    double q[8];
 #pragma unroll
-  for (int r = 0; r < kRows; ++r) acc[r] = 0.0f;
-  for (int k = 0; k < H; ++k) {
-    const float w = W[static_cast<int64_t>(k) * nin + i];
+    for (int u = 0; u < 8; ++u) q[u] = a.part[(p + u) * a.np + j];
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) acc[r] = fmaf(ds[r * H + k], w, acc[r]);
+    for (int u = 0; u < 8; ++u) s += q[u];
   }
-#pragma unroll
-  for (int r = 0; r < kRows; ++r)
-    if (b0 + r < B) {
-      const int64_t o = static_cast<int64_t>(b0 + r) * nin + i;
-      dzin[o] = z[o] > 0.0f ? acc[r] : 0.0f;
-    }
-}
-
-// weight gradient gW[k][i] = sum_b dz[b][k] act(in[b][i]); gb[k] = sum_b dz[b][k]
-__global__ void k_weight_grad(const float* __restrict__ dz, const float* __restrict__ in, int relu_in,
-                              float* __restrict__ gW, float* __restrict__ gb, int B, int H, int nin) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int k = blockIdx.y;
-  if (i < nin) {
-    double s = 0.0;
-    for (int b = 0; b < B; ++b) {
-      float x = in[static_cast<int64_t>(b) * nin + i];
-      if (relu_in) x = fmaxf(x, 0.0f);
-      s += static_cast<double>(dz[static_cast<int64_t>(b) * H + k]) * x;
-    }
-    gW[static_cast<int64_t>(k) * nin + i] = static_cast<float>(s);
-  }
-  if (i == 0) {
-    double s = 0.0;
-    for (int b = 0; b < B; ++b) s += dz[static_cast<int64_t>(b) * H + k];
-    gb[k] = static_cast<float>(s);
-  }
+  for (; p < a.splits; ++p) s += a.part[p * a.np + j];
+  a.g[j] = static_cast<float>(s);
 }
 
 __global__ void k_adam(float* __restrict__ th, const float* __restrict__ g, float* __restrict__ m,
@@ -300,7 +451,7 @@ struct admm_mlp {
   int cap = 0;  // rows the activation buffers hold
   float *X = nullptr, *t = nullptr, *z1 = nullptr, *z2 = nullptr, *z3 = nullptr, *y = nullptr, *dz3 = nullptr;
   float *dz2 = nullptr, *dz1 = nullptr, *pooled = nullptr;
-  uint16_t *h1b = nullptr, *h2b = nullptr;  // bf16 inference: hidden activations as bf16
+  double *blk = nullptr, *part = nullptr;
   double* sc = nullptr;
   double* h_sc = nullptr;
   int64_t step = 0;
@@ -312,6 +463,7 @@ struct admm_mlp {
     for (void* p : {static_cast<void*>(th), static_cast<void*>(g), static_cast<void*>(m), static_cast<void*>(v)})
       if (p) (void)hipFree(p);
     free_rows();
+    if (part) (void)hipFree(part);
     if (sc) (void)hipFree(sc);
     if (h_sc) (void)hipHostFree(h_sc);
     if (own_stream && stream) (void)hipStreamDestroy(stream);
@@ -319,10 +471,9 @@ struct admm_mlp {
   void free_rows() {
     for (float* p : {X, t, z1, z2, z3, y, dz3, dz2, dz1, pooled})
       if (p) (void)hipFree(p);
-    for (uint16_t* p : {h1b, h2b})
-      if (p) (void)hipFree(p);
+    if (blk) (void)hipFree(blk);
     X = t = z1 = z2 = z3 = y = dz3 = dz2 = dz1 = pooled = nullptr;
-    h1b = h2b = nullptr;
+    blk = nullptr;
     cap = 0;
   }
   void ensure(int B) {
@@ -340,29 +491,70 @@ struct admm_mlp {
     a(&dz2, static_cast<int64_t>(c) * H);
     a(&dz1, static_cast<int64_t>(c) * H);
     a(&pooled, H);
-    ck(hipMalloc(reinterpret_cast<void**>(&h1b), sizeof(uint16_t) * static_cast<int64_t>(c) * H));
-    ck(hipMalloc(reinterpret_cast<void**>(&h2b), sizeof(uint16_t) * static_cast<int64_t>(c) * H));
+    ck(hipMalloc(reinterpret_cast<void**>(&blk), sizeof(double) * ((c + kRows - 1) / kRows) * (H + 1)));
     cap = c;
   }
-  void forward(int B, int bf16) {
-    const int nb = (B + kRows - 1) / kRows;
-    if (bf16) {
-      // inference only: the hidden layers are stored as bf16 (fp32 weights and accumulation)
-      hipLaunchKernelGGL(k_dense_bf16<float>, dim3(nb), dim3(H), sizeof(float) * kRows * F, stream, X, F, th + oW1,
-                         th + ob1, h1b, B, H);
-      hipLaunchKernelGGL(k_dense_bf16<uint16_t>, dim3(nb), dim3(H), sizeof(float) * kRows * H, stream, h1b, H,
-                         th + oW2, th + ob2, h2b, B, H);
-      hipLaunchKernelGGL(k_head_bf16, dim3((B + 255) / 256), dim3(256), 0, stream, h2b, th + ow3, th + ob3, z3, y, B,
-                         H);
-      hipLaunchKernelGGL(k_pool_bf16, dim3((H + 127) / 128), dim3(128), 0, stream, h2b, pooled, B, H);
-      return;
-    }
-    hipLaunchKernelGGL(k_dense, dim3(nb), dim3(H), sizeof(float) * kRows * F, stream, X, F, th + oW1, th + ob1, z1, B,
-                       H, 0, 0);
-    hipLaunchKernelGGL(k_dense, dim3(nb), dim3(H), sizeof(float) * kRows * H, stream, z1, H, th + oW2, th + ob2, z2, B,
-                       H, 1, bf16);
-    hipLaunchKernelGGL(k_head, dim3((B + 255) / 256), dim3(256), 0, stream, z2, th + ow3, th + ob3, z3, y, B, H, bf16);
-    hipLaunchKernelGGL(k_pool, dim3((H + 127) / 128), dim3(128), 0, stream, z2, pooled, B, H);
+  // Row ranges of the weight gradients, whole rounds of 32 rows: the tiles of
+  // all three layers times the ranges make up to 640 blocks (B = 2 981, H = 128:
+  // 11 tiles, 47 ranges of 64 rows).  Longer ranges leave the chip idle behind
+  // the rounds' load latency, shorter ones only write more parts.
+  int max_splits() const {
+    const int tiles = wgrad_tiles(H, H) + wgrad_tiles(H, F) + wgrad_tiles(1, H);
+    return std::max(1, 640 / tiles);
+  }
+  MlpArgs plan(int B) const {
+    MlpArgs a{};
+    a.X = X;
+    a.t = t;
+    a.z1 = z1;
+    a.z2 = z2;
+    a.z3 = z3;
+    a.y = y;
+    a.dz3 = dz3;
+    a.dz2 = dz2;
+    a.dz1 = dz1;
+    a.pooled = pooled;
+    a.th = th;
+    a.blk = blk;
+    a.sc = sc;
+    a.part = part;
+    a.g = g;
+    a.oW1 = oW1;
+    a.ob1 = ob1;
+    a.oW2 = oW2;
+    a.ob2 = ob2;
+    a.ow3 = ow3;
+    a.ob3 = ob3;
+    a.owr = owr;
+    a.obr = obr;
+    a.np = np;
+    a.B = B;
+    a.F = F;
+    a.H = H;
+    a.nblk = (B + kRows - 1) / kRows;
+    const int want = std::min(max_splits(), std::max(1, B / 64));
+    a.rows_per_split = ((B + want - 1) / want + 31) & ~31;
+    a.splits = (B + a.rows_per_split - 1) / a.rows_per_split;
+    return a;
+  }
+  // the layers and the scalars
+  void forward(const MlpArgs& a, bool bf16) {
+    const int smem = 4 * kRows * (lds_stride(H) + std::max(lds_stride(F), lds_stride(H)));
+    auto kern = bf16 ? k_mlp_forward<true> : k_mlp_forward<false>;
+    if (smem > 65536)
+      ck(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+    hipLaunchKernelGGL(kern, dim3(a.nblk), dim3(kNt), smem, stream, a);
+    hipLaunchKernelGGL(k_mlp_scalars, dim3(1), dim3(1024), 0, stream, a);
+  }
+  void backward(const MlpArgs& a) {
+    const int smem = 4 * kRows * lds_stride(H);
+    if (smem > 65536)
+      ck(hipFuncSetAttribute(reinterpret_cast<const void*>(k_mlp_backward), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             smem));
+    hipLaunchKernelGGL(k_mlp_backward, dim3(a.nblk), dim3(kNt), smem, stream, a);
+    const int tiles = wgrad_tiles(H, H) + wgrad_tiles(H, F) + wgrad_tiles(1, H);
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3(tiles, a.splits), dim3(kNt), 0, stream, a);
+    hipLaunchKernelGGL(k_mlp_grads, dim3(static_cast<unsigned>((np + kNt - 1) / kNt)), dim3(kNt), 0, stream, a);
   }
 };
 
@@ -414,6 +606,7 @@ admm_status mlp_create(int32_t nin, int32_t hidden, uint64_t seed, void* stream,
     }
     for (float** p : {&n->th, &n->g, &n->m, &n->v}) ck(hipMalloc(reinterpret_cast<void**>(p), sizeof(float) * n->np));
     ck(hipMalloc(reinterpret_cast<void**>(&n->sc), sizeof(double) * 4));
+    ck(hipMalloc(reinterpret_cast<void**>(&n->part), sizeof(double) * n->max_splits() * n->np));
     ck(hipHostMalloc(reinterpret_cast<void**>(&n->h_sc), sizeof(double) * 4, hipHostMallocDefault));
     // He-uniform weights from a splitmix64 stream, zero biases
     std::vector<float> th(static_cast<size_t>(n->np), 0.0f);
@@ -486,9 +679,11 @@ admm_status mlp_forward(admm_mlp* n, const float* X, int32_t rows, int32_t preci
   try {
     n->ensure(rows);
     ck(hipMemcpyAsync(n->X, X, sizeof(float) * rows * n->F, hipMemcpyHostToDevice, n->stream));
-    n->forward(rows, precision == ADMM_PREC_BF16 ? 1 : 0);
-    hipLaunchKernelGGL(k_scalars, dim3(1), dim3(1), 0, n->stream, n->pooled, n->th + n->owr, n->th + n->obr, n->y,
-                       static_cast<const float*>(nullptr), rows, n->H, 0.0f, 0.0f, n->sc);
+    MlpArgs a = n->plan(rows);
+    a.t = nullptr;
+    a.z1 = a.z2 = a.z3 = nullptr;
+    n->forward(a, precision == ADMM_PREC_BF16);
+    ck(hipGetLastError());
     if (y_out) ck(hipMemcpyAsync(y_out, n->y, sizeof(float) * rows, hipMemcpyDeviceToHost, n->stream));
     ck(hipMemcpyAsync(n->h_sc, n->sc, sizeof(double) * 3, hipMemcpyDeviceToHost, n->stream));
     ck(hipStreamSynchronize(n->stream));
@@ -506,26 +701,15 @@ admm_status mlp_loss_grad(admm_mlp* n, const float* X, const float* target, int3
   (void)hipGetLastError();  // report only this call's errors
   if (!n || !X || !target || rows < 1 || !std::isfinite(target_log_rho) || !(lam >= 0)) return ADMM_E_ARG;
   try {
-    const int B = rows, H = n->H, F = n->F;
+    const int B = rows, F = n->F;
     n->ensure(B);
     ck(hipMemcpyAsync(n->X, X, sizeof(float) * B * F, hipMemcpyHostToDevice, n->stream));
     ck(hipMemcpyAsync(n->t, target, sizeof(float) * B, hipMemcpyHostToDevice, n->stream));
-    n->forward(B, 0);
-    hipLaunchKernelGGL(k_scalars, dim3(1), dim3(1), 0, n->stream, n->pooled, n->th + n->owr, n->th + n->obr, n->y,
-                       n->t, B, H, target_log_rho, lam, n->sc);
-    hipLaunchKernelGGL(k_dz3, dim3((B + 255) / 256), dim3(256), 0, n->stream, n->y, n->t, n->z3, n->dz3, B);
-    hipLaunchKernelGGL(k_head_grad, dim3((H + 127) / 128), dim3(128), 0, n->stream, n->z2, n->dz3, n->pooled, n->sc,
-                       n->g + n->ow3, n->g + n->ob3, n->g + n->owr, n->g + n->obr, B, H);
-    const int64_t BH = static_cast<int64_t>(B) * H;
-    hipLaunchKernelGGL(k_dz2, dim3(static_cast<unsigned>((BH + 255) / 256)), dim3(256), 0, n->stream, n->z2, n->dz3,
-                       n->th + n->ow3, n->th + n->owr, n->sc, n->dz2, B, H);
-    hipLaunchKernelGGL(k_weight_grad, dim3((H + 127) / 128, H), dim3(128), 0, n->stream, n->dz2, n->z1, 1,
-                       n->g + n->oW2, n->g + n->ob2, B, H, H);
-    const int nb = (B + kRows - 1) / kRows;
-    hipLaunchKernelGGL(k_back_data, dim3(nb), dim3(H), sizeof(float) * kRows * H, n->stream, n->dz2, n->th + n->oW2,
-                       n->z1, n->dz1, B, H, H);
-    hipLaunchKernelGGL(k_weight_grad, dim3((F + 127) / 128, H), dim3(128), 0, n->stream, n->dz1, n->X, 0,
-                       n->g + n->oW1, n->g + n->ob1, B, H, F);
+    MlpArgs a = n->plan(B);
+    a.lr_t = target_log_rho;
+    a.lam = lam;
+    n->forward(a, false);
+    n->backward(a);
     ck(hipGetLastError());
     ck(hipMemcpyAsync(n->h_sc, n->sc, sizeof(double) * 3, hipMemcpyDeviceToHost, n->stream));
     if (grad_out) ck(hipMemcpyAsync(grad_out, n->g, sizeof(float) * n->np, hipMemcpyDeviceToHost, n->stream));

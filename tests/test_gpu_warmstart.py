@@ -37,6 +37,32 @@ def test_mlp_forward_and_gradient_parity(F, H, B):
     _close(g, gr, 1e-3, 1e-4 * max(1e-6, np.abs(gr).max()))
 
 
+@pytest.mark.parametrize("F,H,B", [(1, 1, 5), (16, 16, 16), (17, 65, 33), (33, 100, 257), (64, 63, 130),
+                                   (700, 600, 40)])
+def test_mlp_tile_edges(F, H, B):
+    """Sizes on and beside the 16-wide tiles, the 64-wide gradient tiles and the
+    row ranges, and one whose activation tiles take more than 64 KiB of LDS."""
+    import paper_2304_14568_amd as A
+    rng = np.random.default_rng(F + 7 * H + 13 * B)
+    net = A.Mlp(F, H, seed=4)
+    th = net.get_params().astype(np.float64)
+    X = rng.normal(size=(B, F)).astype(np.float32)
+    t = rng.uniform(0, 2, size=B).astype(np.float32)
+    L, g = net.loss_grad(X, t, target_log_rho=-0.3, lam=0.2)
+    Lr, gr = mlp.loss_and_grad(th, X, t, -0.3, 0.2, F, H)
+    # fp32 sums of at most max(F, H) products per activation, two layers deep:
+    # 2 max(F, H) 2^-24 relative to the largest entry, fp64 beyond that
+    tol = 4 * max(F, H, 16) * 2.0 ** -24
+    assert abs(L - Lr) <= tol * max(1.0, Lr)
+    assert np.abs(g - gr).max() <= tol * max(1e-6, np.abs(gr).max()) * 4
+    L2, g2 = net.loss_grad(X, t, target_log_rho=-0.3, lam=0.2)
+    assert L2 == L and np.array_equal(g, g2)  # fixed-order sums
+    y, lr = net.forward(X)
+    yr, lrr, _ = mlp.forward(th, X, F, H)
+    assert np.abs(y - yr).max() <= tol * max(1.0, np.abs(yr).max())
+    assert abs(lr - lrr) <= tol * max(1.0, abs(lrr))
+
+
 def test_mlp_adam_step_parity():
     import paper_2304_14568_amd as A
     rng = np.random.default_rng(5)
