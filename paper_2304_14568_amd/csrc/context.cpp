@@ -348,59 +348,57 @@ struct admm_ctx {
 
   // Gram matrices G_s of the scenarios [g0, g0 + cs) of patient pt into the
   // chunk buffer (the upper tiles are what the next steps read): per-tile row
-  // lists and one LDS accumulation per tile; where the lists do not fit in
-  // device memory, one fp64 atomic per product (also taken when the
+  // lists and one fp64 MFMA accumulation per tile; where the lists do not fit
+  // in device memory, one fp64 atomic per product (also taken when the
   // environment sets ADMMBB_GRAM_ATOMIC, which tests use to compare the two).
+  // The lists live in the sweep's work matrices, which are free until the Gram
+  // matrices are done, or in a buffer of their own where those are too small
+  // (few spots: a list entry takes 16 bytes, a work matrix 8 npad^2).
   void gram_chunk(const Pat& pt, int g0, int cs, int64_t nn) {
     struct DevBuf {
       void* p = nullptr;
       ~DevBuf() {
         if (p) (void)hipFree(p);
       }
-    } bc, bo, bl, bsc;
+    } bl, bc;
     const int nb = pt.nbk;
     const int64_t ntl = static_cast<int64_t>(nb) * (nb + 1) / 2, nt = ntl * cs;
-    bool lists = std::getenv("ADMMBB_GRAM_ATOMIC") == nullptr &&
-                 hipMalloc(&bc.p, sizeof(int32_t) * 2 * nt) == hipSuccess &&
-                 hipMalloc(&bo.p, sizeof(int64_t) * (nt + 1)) == hipSuccess;
+    auto up = [](int64_t b) { return (b + 255) & ~int64_t{255}; };
+    // waves that list a scenario's rows: 8 192 over the chunk's scenarios, at
+    // most one per 64 voxels, and few enough that their counts take at most an
+    // eighth of the work matrices
+    const int nchunk = static_cast<int>(
+        std::max<int64_t>(1, std::min<int64_t>({8192 / cs > 256 ? 8192 / cs : 256, 2048, (pt.m + 63) / 64})));
+    const int64_t b_row = up(4 * static_cast<int64_t>(pt.m) * cs);
+    const int64_t b_cnt = up(4 * nt * nchunk), b_tot = up(4 * nt), b_off = up(8 * (nt + 1));
+    const int64_t room = 8 * nn * cs;
+    bool lists = std::getenv("ADMMBB_GRAM_ATOMIC") == nullptr;
+    char* base = reinterpret_cast<char*>(d_Aw);
+    int64_t used = b_row + b_cnt + b_tot + b_off;
+    if (lists && used > room) {
+      lists = hipMalloc(&bc.p, static_cast<size_t>(used)) == hipSuccess;
+      base = static_cast<char*>(bc.p);
+      used = 0;  // the list may have all of the work matrices
+    }
     if (lists) {
-      int32_t* cnt = static_cast<int32_t*>(bc.p);
-      int32_t* cur = cnt + nt;
-      int64_t* off = static_cast<int64_t*>(bo.p);
-      launch_fill_f32(reinterpret_cast<float*>(cnt), 0.0f, 2 * nt, stream);  // counts and cursors
-      for (int s = 0; s < cs; ++s) launch_gram_rows(csr32, H.scen[g0 + s], nb, cnt + s * ntl, nullptr, nullptr, stream);
-      launch_gram_scan(cnt, nt, off, stream);
+      int32_t* row_of = reinterpret_cast<int32_t*>(base);
+      uint32_t* cnt = reinterpret_cast<uint32_t*>(base + b_row);
+      int32_t* tot = reinterpret_cast<int32_t*>(base + b_row + b_cnt);
+      int64_t* off = reinterpret_cast<int64_t*>(base + b_row + b_cnt + b_tot);
+      launch_gram_lists(csr32, d_scen, g0, cs, nb, pt.m, row_of, nchunk, cnt, tot, off, stream);
       check(hipMemcpyAsync(h_scr, off + nt, sizeof(int64_t), hipMemcpyDeviceToHost, stream), "D2H");
       check(hipStreamSynchronize(stream), "sync");
       int64_t total = 0;
       std::memcpy(&total, h_scr, sizeof(total));
-      lists = total >= 0 && hipMalloc(&bl.p, sizeof(GramEntry) * static_cast<size_t>(std::max<int64_t>(total, 1))) ==
-                                hipSuccess;
-      // fixed-point scale of each scenario's tiles: a power of two that keeps
-      // 2 max_j (G_s)_jj, a bound of every partial sum, below 2^62 (from the
-      // fp64 diagonal).  A diagonal beyond fp64 range, or so small that the
-      // scale would leave it, takes the fp64 atomic path instead.
-      std::vector<double> gs(static_cast<size_t>(cs), 1.0);
-      for (int s = 0; s < cs; ++s) {
-        const double gmax = H.gdiag_max[static_cast<size_t>(g0 + s)];
-        int e = 0;
-        if (!(2.0 * gmax <= std::numeric_limits<double>::max())) {
-          lists = false;
-        } else if (gmax > 0.0) {
-          (void)std::frexp(2.0 * gmax, &e);  // 2 gmax = f 2^e, 1/2 <= f < 1
-          if (62 - e > 1000) lists = false;
-          gs[static_cast<size_t>(s)] = std::ldexp(1.0, std::min(62 - e, 1000));
-        }
-      }
-      lists = lists && hipMalloc(&bsc.p, sizeof(double) * static_cast<size_t>(cs)) == hipSuccess;
-      if (lists) {
-        check(hipMemcpy(bsc.p, gs.data(), sizeof(double) * static_cast<size_t>(cs), hipMemcpyHostToDevice), "H2D");
-        GramEntry* list = static_cast<GramEntry*>(bl.p);
-        for (int s = 0; s < cs; ++s)
-          launch_gram_rows(csr32, H.scen[g0 + s], nb, cur + s * ntl, off + s * ntl, list, stream);
-        launch_gram_tiles(csr32, d_rw64, d_scen, g0, cs, nb, off, list, static_cast<const double*>(bsc.p), d_G,
-                          pt.npad, stream);
-      }
+      const int64_t b_list = static_cast<int64_t>(sizeof(GramEntry)) * std::max<int64_t>(total, 1);
+      GramEntry* list = nullptr;
+      if (used + b_list <= room)
+        list = reinterpret_cast<GramEntry*>(reinterpret_cast<char*>(d_Aw) + used);
+      else if (hipMalloc(&bl.p, static_cast<size_t>(b_list)) == hipSuccess)
+        list = static_cast<GramEntry*>(bl.p);
+      lists = list != nullptr;
+      if (lists)
+        launch_gram_tiles(csr32, d_rw64, d_scen, g0, cs, nb, pt.m, row_of, nchunk, cnt, off, list, d_G, pt.npad, stream);
     }
     if (!lists) {
       (void)hipGetLastError();  // the failed allocation
@@ -408,7 +406,7 @@ struct admm_ctx {
       for (int s = 0; s < cs; ++s) launch_gram(csr32, d_rw64, H.scen[g0 + s], d_G + s * nn, pt.npad, stream);
     }
     check(hipGetLastError(), "Gram launch");
-    check(hipStreamSynchronize(stream), "sync");  // before the lists are freed
+    if (bl.p || bc.p) check(hipStreamSynchronize(stream), "sync");  // before the buffers are freed
   }
 
   // (Re)build the cached inverses of patient p at its current penalty, a

@@ -42,6 +42,8 @@ namespace admmbb {
 
 namespace {
 
+typedef double v4d __attribute__((ext_vector_type(4)));
+
 constexpr int kFb = 64;  // sweep block size and packed tile size
 
 __host__ __device__ __forceinline__ int64_t tile_index(int I, int J, int nb) {
@@ -90,17 +92,31 @@ __global__ __launch_bounds__(256) void k_gram(MatDev mat, const double* __restri
 
 // Gram matrix by output tiles.  Every stored row adds w_i a_i a_i^T to the
 // 64 x 64 tiles (I, J), I <= J, of the blocks its nonzeros fall in.  Lists of
-// the rows that reach each tile are built first (count, scan, fill); one
-// workgroup per tile then adds its rows' products in LDS and writes the tile
-// once, instead of one global fp64 atomic per product.
+// the rows that reach each tile are built first, then one workgroup per tile
+// adds its rows' products and writes the tile once.
+//
+// The lists: the voxels of a scenario, in groups of 64, are dealt to `nchunk`
+// waves (group i to wave i mod nchunk).  Each wave counts its rows' entries per
+// tile in LDS (k_gram_rows<false>), k_gram_prefix turns the counts of a tile
+// into each wave's first slot, k_gram_scan the totals into tile offsets, and the
+// same waves write the entries (k_gram_rows<true>).  One launch each covers
+// every scenario of the chunk, no counter is shared between waves (counting and
+// filling with one global atomic per entry and a launch per scenario took 6.2
+// ms for 13 scenarios of 1 700 spots, against 0.5 ms), and a list's order is
+// fixed: the sums below repeat bit for bit, and neighbouring voxels, which the
+// same spots reach, stand together.
 
-template <bool C16>
-__device__ __forceinline__ int col_at(const MatDev& mat, int64_t e) {
-  if constexpr (C16)
-    return static_cast<const uint16_t*>(mat.col)[e];
-  else
-    return static_cast<const int32_t*>(mat.col)[e];
+// row_of[s * ms + voxel] = the stored row of the voxel (preset to -1: no nonzero)
+__global__ __launch_bounds__(256) void k_gram_order(MatDev mat, const Scen* __restrict__ scen, int g0, int ms,
+                                                    int32_t* __restrict__ row_of) {
+  const Scen sc = scen[g0 + static_cast<int>(blockIdx.y)];
+  int32_t* to = row_of + static_cast<int64_t>(blockIdx.y) * ms;
+  for (int r = static_cast<int>(blockIdx.x) * 256 + threadIdx.x; r < sc.rows; r += static_cast<int>(gridDim.x) * 256)
+    to[mat.rorig[sc.row_base + r]] = r;
 }
+
+// Columns are uint16 in every dense context (n <= 8128).
+__device__ __forceinline__ int col_at(const MatDev& mat, int64_t e) { return static_cast<const uint16_t*>(mat.col)[e]; }
 
 // LDS written by some lanes of a wave and then read by others of the same wave
 __device__ __forceinline__ void wave_lds_sync() {
@@ -111,44 +127,103 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 constexpr int kMaxBlocks = 128;  // 64-column blocks of a patient (n <= 8192)
 
-// FILL = false: count[t] += 1 for every tile t = (b_p, b_q), p <= q, of the
-// distinct blocks b_1 < ... < b_r of each row; FILL = true: the row and its
-// extent at off[t] + (a slot taken from cur[t]).  One wave per stored row.
-template <bool C16, bool FILL>
-__global__ __launch_bounds__(256) void k_gram_rows(MatDev mat, Scen sc, int nb, int32_t* __restrict__ cnt,
-                                                   const int64_t* __restrict__ off, GramEntry* __restrict__ list) {
-  __shared__ int bl[4][kMaxBlocks];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int row = static_cast<int>(blockIdx.x) * 4 + w;
-  if (row >= sc.rows) return;  // no workgroup barrier below
-  const uint32_t c0 = mat.rp[sc.rp_base + row], c1 = mat.rp[sc.rp_base + row + 1];
-  const int64_t e0 = sc.nnz_base + 4 * static_cast<int64_t>(c0);
-  const int k = 4 * static_cast<int>(c1 - c0);
-  int r = 0;
-  for (int base = 0; base < k; base += 64) {
-    const int kk = base + lane;
-    int b = -1, bp = -1;
-    if (kk < k) {
-      b = col_at<C16>(mat, e0 + kk) >> 6;
-      if (kk > 0) bp = col_at<C16>(mat, e0 + kk - 1) >> 6;
-    }
-    const bool start = kk < k && b != bp;  // columns are non-decreasing along a row
-    const uint64_t m = __ballot(start);
-    const int at = r + __popcll(m & ((uint64_t{1} << lane) - 1));
-    if (start && at < kMaxBlocks) bl[w][at] = b;
-    r += __popcll(m);
-  }
-  if (r > kMaxBlocks) r = kMaxBlocks;  // cannot happen for n <= 8192
+// One wave per workgroup: blockIdx.x the chunk, blockIdx.y the scenario.
+// cnt[(s * nchunk + chunk) * nt + tile]: FILL = false writes the wave's entries
+// per tile, FILL = true reads its first slot in the tile's list.
+template <bool FILL>
+__global__ __launch_bounds__(64) void k_gram_rows(MatDev mat, const Scen* __restrict__ scen, int g0, int nb,
+                                                  const int32_t* __restrict__ row_of, int ms, int nchunk,
+                                                  uint32_t* __restrict__ cnt,
+                                                  const int64_t* __restrict__ off, GramEntry* __restrict__ list) {
+  extern __shared__ __align__(16) uint32_t slot[];  // one per tile
+  __shared__ int bl[kMaxBlocks], st[kMaxBlocks + 1];  // the row's blocks, and where each starts
+  const int lane = threadIdx.x;
+  const int chunk = static_cast<int>(blockIdx.x), s = static_cast<int>(blockIdx.y);
+  const Scen sc = scen[g0 + s];
+  const int nt = nb * (nb + 1) / 2;
+  uint32_t* mine = cnt + (static_cast<int64_t>(s) * nchunk + chunk) * nt;
+  for (int t = lane; t < nt; t += 64) slot[t] = FILL ? mine[t] : 0u;
   wave_lds_sync();
-  for (int t = lane; t < r * r; t += 64) {
-    const int p = t / r, q = t - p * r;
-    if (p > q) continue;
-    const int64_t ti = tile_index(bl[w][p], bl[w][q], nb);
-    if constexpr (FILL)
-      list[off[ti] + atomicAdd(&cnt[ti], 1)] = GramEntry{row, c0, c1, 0};
-    else
-      atomicAdd(&cnt[ti], 1);
+  const uint32_t* rp = mat.rp + sc.rp_base;
+  const int32_t* rows = row_of + static_cast<int64_t>(s) * ms;
+  for (int64_t v0 = 64 * chunk; v0 < sc.m; v0 += 64 * nchunk) {
+    // the extents of the group's rows, one per lane
+    const int myrow = v0 + lane < sc.m ? rows[v0 + lane] : -1;
+    uint32_t myc0 = 0, myc1 = 0;
+    if (myrow >= 0) {
+      myc0 = rp[myrow];
+      myc1 = rp[myrow + 1];
+    }
+    for (uint64_t left = __ballot(myrow >= 0); left != 0; left &= left - 1) {
+      const int from = __ffsll(static_cast<unsigned long long>(left)) - 1;
+      const int row = __builtin_amdgcn_readlane(myrow, from);
+      const uint32_t c0 = __builtin_amdgcn_readlane(myc0, from), c1 = __builtin_amdgcn_readlane(myc1, from);
+      const int64_t e0 = sc.nnz_base + 4 * static_cast<int64_t>(c0);
+      const int k = 4 * static_cast<int>(c1 - c0);
+      int r = 0, last = -1;
+      for (int base = 0; base < k; base += 64) {
+        const int kk = base + lane;
+        const int b = kk < k ? col_at(mat, e0 + kk) >> 6 : -1;
+        const int up = __shfl_up(b, 1, 64);
+        const bool start = kk < k && b != (lane == 0 ? last : up);  // columns are non-decreasing along a row
+        const uint64_t m = __ballot(start);
+        const int at = r + __popcll(m & ((uint64_t{1} << lane) - 1));
+        if (start && at < kMaxBlocks) {
+          bl[at] = b;
+          st[at] = kk;
+        }
+        r += __popcll(m);
+        last = __shfl(b, 63, 64);
+      }
+      if (r > kMaxBlocks) r = kMaxBlocks;  // cannot happen for n <= 8192
+      if (lane == 0) st[r] = k;
+      wave_lds_sync();
+      for (int t = lane; t < r * r; t += 64) {
+        const int p = t / r, q = t - p * r;
+        if (p > q) continue;
+        const int ti = static_cast<int>(tile_index(bl[p], bl[q], nb));
+        const uint32_t at = slot[ti];  // the row's tiles are distinct: no two lanes share one
+        slot[ti] = at + 1;
+        if constexpr (FILL)
+          list[off[static_cast<int64_t>(s) * nt + ti] + at] =
+              GramEntry{row, c0, static_cast<uint32_t>(st[p]) | static_cast<uint32_t>(st[p + 1] - st[p]) << 16,
+                        static_cast<uint32_t>(st[q]) | static_cast<uint32_t>(st[q + 1] - st[q]) << 16};
+      }
+      wave_lds_sync();
+    }
   }
+  if constexpr (!FILL) {
+    wave_lds_sync();
+    for (int t = lane; t < nt; t += 64) mine[t] = slot[t];
+  }
+}
+
+// Per tile: cnt of every chunk replaced by the sum of the chunks before it, the
+// total to tot.  Workgroup: 64 tiles (lanes) of one scenario, eight waves an
+// eighth of the chunks each.
+constexpr int kPrefixWaves = 8;
+__global__ __launch_bounds__(64 * kPrefixWaves) void k_gram_prefix(uint32_t* __restrict__ cnt, int nt, int nchunk,
+                                                                   int32_t* __restrict__ tot) {
+  __shared__ uint32_t part[kPrefixWaves][64];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int t = static_cast<int>(blockIdx.x) * 64 + lane, s = static_cast<int>(blockIdx.y);
+  const int per = (nchunk + kPrefixWaves - 1) / kPrefixWaves;
+  const int b = w * per < nchunk ? w * per : nchunk, e = b + per < nchunk ? b + per : nchunk;
+  uint32_t* c = cnt + static_cast<int64_t>(s) * nchunk * nt + t;
+  uint32_t sum = 0;
+  if (t < nt)
+    for (int i = b; i < e; ++i) sum += c[static_cast<int64_t>(i) * nt];
+  part[w][lane] = sum;
+  __syncthreads();
+  if (t >= nt) return;
+  uint32_t run = 0;
+  for (int q = 0; q < w; ++q) run += part[q][lane];
+  for (int i = b; i < e; ++i) {
+    const uint32_t v = c[static_cast<int64_t>(i) * nt];
+    c[static_cast<int64_t>(i) * nt] = run;
+    run += v;
+  }
+  if (w == kPrefixWaves - 1) tot[static_cast<int64_t>(s) * nt + t] = static_cast<int32_t>(run);
 }
 
 // off[i] = cnt[0] + ... + cnt[i - 1] for i <= nt (one workgroup)
@@ -162,50 +237,48 @@ __global__ __launch_bounds__(1024) void k_gram_scan(const int32_t* __restrict__ 
   for (int64_t i = b; i < e; ++i) sum += cnt[i];
   part[t] = sum;
   __syncthreads();
-  if (t == 0) {
-    int64_t run = 0;
-    for (int i = 0; i < 1024; ++i) {
-      const int64_t v = part[i];
-      part[i] = run;
-      run += v;
-    }
-    off[nt] = run;
+  for (int d = 1; d < 1024; d <<= 1) {
+    const int64_t v = t >= d ? part[t - d] : 0;
+    __syncthreads();
+    part[t] += v;
+    __syncthreads();
   }
-  __syncthreads();
-  int64_t run = part[t];
+  int64_t run = part[t] - sum;
   for (int64_t i = b; i < e; ++i) {
     off[i] = run;
     run += cnt[i];
   }
+  if (t == 1023) off[nt] = part[1023];
 }
 
-// One workgroup per tile (I, J) of scenario g0 + blockIdx.y: the rows of its
-// list add c_s w_i a_ij a_ik for j in block I, k in block J (j <= k inside a
-// diagonal tile) to an fp64 LDS tile, which is then written to G (upper part).
-// The tile is accumulated in 64-bit fixed point (gscale[s], a power of two,
-// keeps every partial sum below 2^61: all products are nonnegative, so no
-// partial sum exceeds its entry G_jk <= sqrt(G_jj G_kk) <= max_j G_jj), which
-// makes it exact and independent of the order of the atomics.
-// A row's nonzeros in one block are contiguous (at most 64, plus padding of
-// value 0).  Each wave takes one listed row at a time: its columns and values
-// are read once (with the next list entry already in flight) and staged in the
-// wave's LDS area, from which the products are formed; rows longer than the
-// staging area are read from memory instead.
-constexpr int kGramWaves = 8;
-constexpr int kGramStage = 320;
+// One workgroup per tile (I, J) of scenario g0 + blockIdx.y: sum over the rows
+// of its list of (c_s w_i a_i,I) a_i,J^T, a 64 x rows x 64 product on the fp64
+// 16x16x4 MFMA.  32 listed rows at a time, each wave expands eight: their
+// segments of the two blocks (13 of 64 columns on average, contiguous, two
+// 16-byte loads of four elements per lane) go to zeroed LDS rows, the first
+// block's times its weight in fp64; then each wave adds all 32 rows to its 32 x
+// 32 quarter of the tile, leaving out the 16-column groups that no row of a
+// step uses (listed in voxel order, four rows need a third of the products; in
+// the order of the stored rows, four fifths).  The next rows are requested
+// before the products of the current ones, and four workgroups per CU hide the
+// rest of the loads' latency, which bounds the kernel: 5.3 ms for 13 scenarios
+// of 2 981 spots (1.2 ms of MFMA issue), 10.3 ms with a whole tile per wave and
+// two waves per SIMD, 6.5 ms without the skipped groups.  One product at a time
+// through LDS atomics, with one row at a time per wave, took 17.7 ms.  Padding
+// (value 0, the last column repeated) is left out.
+constexpr int kGramWaves = 4;
+constexpr int kGramRows = 8;       // listed rows a wave expands at a time
+constexpr int kGramLd = kFb + 16;  // row stride: four rows that one load reads start 32 (16) banks apart
 
-template <bool C16>
-__global__ __launch_bounds__(64 * kGramWaves) void k_gram_tiles(MatDev mat, const double* __restrict__ rw64,
+__global__ __launch_bounds__(64 * kGramWaves, 4) void k_gram_tiles(MatDev mat, const double* __restrict__ rw64,
                                                                 const Scen* __restrict__ scen, int g0, int nb,
                                                                 const int64_t* __restrict__ off,
                                                                 const GramEntry* __restrict__ list,
-                                                                const double* __restrict__ gscale,
                                                                 double* __restrict__ G, int ld) {
-  // row stride kFb + 1: the lanes of one atomic instruction mostly share a
-  // column and differ in the row, so rows must fall in different banks
-  __shared__ unsigned long long acc[kFb * (kFb + 1)];
-  __shared__ float sval[kGramWaves][kGramStage];
-  __shared__ uint8_t scol[kGramWaves][kGramStage];
+  constexpr int kStep = kGramWaves * kGramRows;
+  __shared__ __align__(16) double bufI[kStep * kGramLd];
+  __shared__ __align__(16) float bufJ[kStep * kGramLd];
+  __shared__ uint32_t occ[kStep / 4];  // per four rows: 16-column groups in use, block I in bits 0-3, J in 4-7
   const int64_t ntiles = static_cast<int64_t>(nb) * (nb + 1) / 2;
   const int64_t t = blockIdx.x;
   const int s = static_cast<int>(blockIdx.y);
@@ -216,78 +289,134 @@ __global__ __launch_bounds__(64 * kGramWaves) void k_gram_tiles(MatDev mat, cons
     ++I;
   }
   const int J = I + static_cast<int>(rem);
-  for (int e = threadIdx.x; e < kFb * (kFb + 1); e += 64 * kGramWaves) acc[e] = 0ull;
-  __syncthreads();
   const Scen sc = scen[g0 + s];
-  const double scale = gscale[s];
   const float* val = static_cast<const float*>(mat.val);
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  float* sv = sval[w];
-  uint8_t* scl = scol[w];
-  const int64_t le = off[s * ntiles + t + 1];
-  int64_t li = off[s * ntiles + t] + w;
-  GramEntry cur{};
-  if (li < le) cur = list[li];
-  for (; li < le; li += kGramWaves) {
-    GramEntry nxt{};
-    if (li + kGramWaves < le) nxt = list[li + kGramWaves];
-    const int64_t e0 = sc.nnz_base + 4 * static_cast<int64_t>(cur.c0);
-    const int k = 4 * static_cast<int>(cur.c1 - cur.c0);
-    const bool staged = k <= kGramStage;
-    const double rw = rw64[sc.row_base + cur.row];
-    int fI = 0, nI = 0, fJ = 0, nJ = 0;
-    for (int base = 0; base < k; base += 64) {
-      const int kk = base + lane;
-      int b = -1;
-      if (kk < k) {
-        const int c = col_at<C16>(mat, e0 + kk);
-        b = c >> 6;
-        if (staged) {
-          sv[kk] = val[e0 + kk];
-          scl[kk] = static_cast<uint8_t>(c & (kFb - 1));
-        }
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int g = tid >> 3, sub = lane & 7;  // eight lanes expand row g of the 32
+  const int m = lane & 15, kk = lane >> 4;
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  const int qi = 32 * (wu >> 1), qj = 32 * (wu & 1);  // the wave's quarter
+  const int64_t l0 = off[s * ntiles + t], le = off[s * ntiles + t + 1];
+  v4d acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
+  // one row's share of a lane: of either segment, the chunk (four elements,
+  // aligned, so a neighbouring block's may be among them) at its place of the
+  // eight, and the one eight further on
+  struct Row {
+    uint32_t cI, cJ;  // the segments' first chunks
+    int nI, nJ;       // their chunks
+    double rw;
+    float4 vI[2], vJ[2];
+    uint2 kI[2], kJ[2];
+  };
+  const float4* valc = reinterpret_cast<const float4*>(val + sc.nnz_base);
+  const uint2* colc = reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(mat.col) + sc.nnz_base);
+  auto entry = [&](int64_t li, GramEntry& e) {
+    e = GramEntry{0, 0, 0, 0};  // no row: empty segments
+    if (li < le) e = list[li];
+  };
+  auto chunks = [](uint32_t c0, uint32_t seg, uint32_t& first, int& n) {
+    const uint32_t st = seg & 0xffffu, len = seg >> 16;
+    first = c0 + (st >> 2);
+    n = len ? static_cast<int>(((st + len + 3) >> 2) - (st >> 2)) : 0;
+  };
+  auto request = [&](const GramEntry& e, Row& r) {
+    chunks(e.c0, e.segI, r.cI, r.nI);
+    chunks(e.c0, e.segJ, r.cJ, r.nJ);
+    r.rw = r.nI > 0 ? rw64[sc.row_base + e.row] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int p = sub + 8 * u;
+      r.vI[u] = r.vJ[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);  // value 0: nothing is placed
+      r.kI[u] = r.kJ[u] = make_uint2(0u, 0u);
+      if (p < r.nI) {
+        r.vI[u] = valc[r.cI + p];
+        r.kI[u] = colc[r.cI + p];
       }
-      const uint64_t mI = __ballot(b == I), mJ = __ballot(b == J);
-      if (nI == 0 && mI) fI = base + __ffsll(static_cast<unsigned long long>(mI)) - 1;
-      if (nJ == 0 && mJ) fJ = base + __ffsll(static_cast<unsigned long long>(mJ)) - 1;
-      nI += __popcll(mI);
-      nJ += __popcll(mJ);
+      if (p < r.nJ) {
+        r.vJ[u] = valc[r.cJ + p];
+        r.kJ[u] = colc[r.cJ + p];
+      }
     }
+  };
+  double* rI = bufI + g * kGramLd;
+  float* rJ = bufJ + g * kGramLd;
+  auto put = [&](auto* dst, int blk, const float4& v, const uint2& c, auto scale, uint32_t& used) {
+    const float vv[4] = {v.x, v.y, v.z, v.w};
+    const uint32_t cc[4] = {c.x & 0xffffu, c.x >> 16, c.y & 0xffffu, c.y >> 16};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (vv[q] != 0.0f && static_cast<int>(cc[q] >> 6) == blk) {
+        dst[cc[q] & (kFb - 1)] = scale * vv[q];
+        used |= 1u << ((cc[q] >> 4) & 3);
+      }
+  };
+  GramEntry e1;
+  Row cur;
+  entry(l0 + g, e1);
+  request(e1, cur);
+  entry(l0 + kStep + g, e1);
+  for (int64_t li = l0; li < le; li += kStep) {
+    // zero the row (its 64 columns, eight lanes), then place the segments
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *reinterpret_cast<double2*>(rI + 16 * q + 2 * sub) = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      *reinterpret_cast<float4*>(rJ + 32 * q + 4 * sub) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     wave_lds_sync();
-    // a = p / nJ as (p * mJ) >> 19: exact for p < 67 * 67 and nJ <= 67, the
-    // largest segments (64 columns of a block plus 3 entries of padding)
-    const int np = nI * nJ;
-    const uint32_t mJ = nJ > 0 ? (uint32_t{1} << 19) / static_cast<uint32_t>(nJ) + 1 : 0;
-    for (int p = lane; p < np; p += 64) {
-      const int a = static_cast<int>((static_cast<uint32_t>(p) * mJ) >> 19), q = p - a * nJ;
-      if (I == J && a > q) continue;
-      const int pa = fI + a, pb = fJ + q;
-      double va, vb;
-      int ca, cb;
-      if (staged) {
-        va = sv[pa];
-        vb = sv[pb];
-        ca = scl[pa];
-        cb = scl[pb];
-      } else {
-        va = val[e0 + pa];
-        vb = val[e0 + pb];
-        ca = col_at<C16>(mat, e0 + pa) & (kFb - 1);
-        cb = col_at<C16>(mat, e0 + pb) & (kFb - 1);
-      }
-      const double prod = (rw * va) * vb;
-      if (prod != 0.0) atomicAdd(&acc[ca * (kFb + 1) + cb], __double2ull_rn(prod * scale));
+    uint32_t uI = 0, uJ = 0;
+    put(rI, I, cur.vI[0], cur.kI[0], cur.rw, uI);
+    put(rJ, J, cur.vJ[0], cur.kJ[0], 1.0f, uJ);
+    if (sub + 8 < cur.nI) put(rI, I, cur.vI[1], cur.kI[1], cur.rw, uI);
+    if (sub + 8 < cur.nJ) put(rJ, J, cur.vJ[1], cur.kJ[1], 1.0f, uJ);
+    for (int p = sub + 16; p < cur.nI; p += 8) put(rI, I, valc[cur.cI + p], colc[cur.cI + p], cur.rw, uI);
+    for (int p = sub + 16; p < cur.nJ; p += 8) put(rJ, J, valc[cur.cJ + p], colc[cur.cJ + p], 1.0f, uJ);
+    {
+      // over the 32 lanes of four rows
+      uint32_t u = uI | uJ << 4;
+#pragma unroll
+      for (int d = 1; d < 32; d <<= 1) u |= __shfl_xor(u, d, 64);
+      if ((lane & 31) == 0) occ[tid >> 5] = u;
     }
-    wave_lds_sync();  // the next row overwrites the staging area
-    cur = nxt;
+    request(e1, cur);  // the next row's, in flight over the products
+    entry(li + 2 * kStep + g, e1);
+    __syncthreads();
+    uint32_t use[kStep / 4];
+#pragma unroll
+    for (int h = 0; h < kStep / 4; ++h) use[h] = __builtin_amdgcn_readfirstlane(occ[h]);
+#pragma unroll
+    for (int h = 0; h < kStep / 4; ++h) {
+      const uint32_t ui = (use[h] >> (qi / 16)) & 3u, uj = (use[h] >> (4 + qj / 16)) & 3u;
+      if (ui == 0 || uj == 0) continue;
+      double av[2], bv[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        av[q] = bufI[(4 * h + kk) * kGramLd + qi + 16 * q + m];
+        bv[q] = static_cast<double>(bufJ[(4 * h + kk) * kGramLd + qj + 16 * q + m]);
+      }
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          if ((ui >> a & 1u) && (uj >> b & 1u))
+            acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+    }
+    __syncthreads();  // the next rows overwrite the buffers
   }
-  __syncthreads();
+  // item r of a lane is row l / 16 + 4 r and column l % 16 of its 16 x 16 block
   double* Gs = G + static_cast<int64_t>(s) * ld * ld;
-  const double unscale = 1.0 / scale;  // exact: a power of two
-  for (int e = threadIdx.x; e < kFb * kFb; e += 64 * kGramWaves) {
-    const int r = e / kFb, c = e % kFb;
-    if (I != J || r <= c) Gs[static_cast<int64_t>(I * kFb + r) * ld + J * kFb + c] = static_cast<double>(acc[r * (kFb + 1) + c]) * unscale;
-  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = qi + 16 * a + kk + 4 * r, col = qj + 16 * b + m;
+        if (I != J || row <= col) Gs[static_cast<int64_t>(I * kFb + row) * ld + J * kFb + col] = acc[a][b][r];
+      }
 }
 
 // For the chunk of scenarios [scen_begin, scen_begin + nscen) of one patient
@@ -1029,36 +1158,25 @@ void launch_gram(const MatDev& m, const double* rw64, const Scen& sc, double* G,
     hipLaunchKernelGGL(k_gram<false>, dim3(nb), dim3(256), 0, st, m, rw64, sc, G, ld);
 }
 
-void launch_gram_rows(const MatDev& m, const Scen& sc, int nb, int32_t* cnt, const int64_t* off, GramEntry* list,
-                      hipStream_t st) {
-  if (sc.rows <= 0) return;
-  const unsigned g = static_cast<unsigned>((sc.rows + 3) / 4);
-  if (m.col16) {
-    if (list)
-      hipLaunchKernelGGL((k_gram_rows<true, true>), dim3(g), dim3(256), 0, st, m, sc, nb, cnt, off, list);
-    else
-      hipLaunchKernelGGL((k_gram_rows<true, false>), dim3(g), dim3(256), 0, st, m, sc, nb, cnt, off, list);
-  } else {
-    if (list)
-      hipLaunchKernelGGL((k_gram_rows<false, true>), dim3(g), dim3(256), 0, st, m, sc, nb, cnt, off, list);
-    else
-      hipLaunchKernelGGL((k_gram_rows<false, false>), dim3(g), dim3(256), 0, st, m, sc, nb, cnt, off, list);
-  }
+void launch_gram_lists(const MatDev& m, const Scen* scen, int g0, int nscen, int nb, int ms, int32_t* row_of,
+                       int nchunk, uint32_t* cnt, int32_t* tot, int64_t* off, hipStream_t st) {
+  const int nt = nb * (nb + 1) / 2;
+  launch_fill_f32(reinterpret_cast<float*>(row_of), __builtin_bit_cast(float, -1), static_cast<int64_t>(ms) * nscen, st);
+  hipLaunchKernelGGL(k_gram_order, dim3(64, nscen), dim3(256), 0, st, m, scen, g0, ms, row_of);
+  hipLaunchKernelGGL(k_gram_rows<false>, dim3(nchunk, nscen), dim3(64), 4 * nt, st, m, scen, g0, nb, row_of, ms, nchunk,
+                     cnt, static_cast<const int64_t*>(nullptr), static_cast<GramEntry*>(nullptr));
+  hipLaunchKernelGGL(k_gram_prefix, dim3((nt + 63) / 64, nscen), dim3(64 * kPrefixWaves), 0, st, cnt, nt, nchunk, tot);
+  hipLaunchKernelGGL(k_gram_scan, dim3(1), dim3(1024), 0, st, tot, static_cast<int64_t>(nt) * nscen, off);
 }
 
-void launch_gram_scan(const int32_t* cnt, int64_t nt, int64_t* off, hipStream_t st) {
-  hipLaunchKernelGGL(k_gram_scan, dim3(1), dim3(1024), 0, st, cnt, nt, off);
-}
-
-void launch_gram_tiles(const MatDev& m, const double* rw64, const Scen* scen, int g0, int nscen, int nb,
-                       const int64_t* off, const GramEntry* list, const double* gscale, double* G, int ld,
-                       hipStream_t st) {
-  const unsigned nt = static_cast<unsigned>(static_cast<int64_t>(nb) * (nb + 1) / 2);
-  const dim3 grid(nt, static_cast<unsigned>(nscen)), block(64 * kGramWaves);
-  if (m.col16)
-    hipLaunchKernelGGL(k_gram_tiles<true>, grid, block, 0, st, m, rw64, scen, g0, nb, off, list, gscale, G, ld);
-  else
-    hipLaunchKernelGGL(k_gram_tiles<false>, grid, block, 0, st, m, rw64, scen, g0, nb, off, list, gscale, G, ld);
+void launch_gram_tiles(const MatDev& m, const double* rw64, const Scen* scen, int g0, int nscen, int nb, int ms,
+                       const int32_t* row_of, int nchunk, uint32_t* cnt, const int64_t* off, GramEntry* list, double* G,
+                       int ld, hipStream_t st) {
+  const int nt = nb * (nb + 1) / 2;
+  hipLaunchKernelGGL(k_gram_rows<true>, dim3(nchunk, nscen), dim3(64), 4 * nt, st, m, scen, g0, nb, row_of, ms, nchunk,
+                     cnt, off, list);
+  hipLaunchKernelGGL(k_gram_tiles, dim3(nt, nscen), dim3(64 * kGramWaves), 0, st, m, rw64, scen, g0, nb, off, list, G,
+                     ld);
 }
 
 void launch_gram_finish(FactorArgs f, int patient, int scen_begin, int nscen, int npad, int n, double rho,

@@ -289,19 +289,21 @@ void launch_fill_u8(uint8_t* p, uint8_t v, int64_t count, hipStream_t st);
 int pass_smem_bytes(int nmax, int acc);
 int dose_hist_smem_bytes(int G, int nbins);
 void launch_gram(const MatDev& m, const double* rw64, const Scen& sc, double* G, int ld, hipStream_t st);
-// Gram matrix by output tiles: per-tile row lists (count with list == nullptr,
-// then fill), their offsets, and one workgroup per tile and scenario
-struct GramEntry {  // one stored row in a tile's list: its index and its extent in 4-element chunks
+// Gram matrix by output tiles: the rows that reach each tile are listed by
+// nchunk waves per scenario (launch_gram_lists counts: row_of[nscen * ms], ms the
+// number of voxels, cnt[nscen * nchunk * nt] and tot[nscen * nt], off[nscen * nt
+// + 1] the lists' offsets), then filled and added up, one workgroup per tile and
+// scenario (launch_gram_tiles)
+struct GramEntry {  // one stored row in a tile's list
   int32_t row;
-  uint32_t c0, c1;
-  int32_t pad;
+  uint32_t c0;          // its first 4-element chunk
+  uint32_t segI, segJ;  // its nonzeros in the tile's two blocks: first (low half) and number (high half)
 };
-void launch_gram_rows(const MatDev& m, const Scen& sc, int nb, int32_t* cnt, const int64_t* off, GramEntry* list,
-                      hipStream_t st);
-void launch_gram_scan(const int32_t* cnt, int64_t nt, int64_t* off, hipStream_t st);
-void launch_gram_tiles(const MatDev& m, const double* rw64, const Scen* scen, int g0, int nscen, int nb,
-                       const int64_t* off, const GramEntry* list, const double* gscale, double* G, int ld,
-                       hipStream_t st);
+void launch_gram_lists(const MatDev& m, const Scen* scen, int g0, int nscen, int nb, int ms, int32_t* row_of,
+                       int nchunk, uint32_t* cnt, int32_t* tot, int64_t* off, hipStream_t st);
+void launch_gram_tiles(const MatDev& m, const double* rw64, const Scen* scen, int g0, int nscen, int nb, int ms,
+                       const int32_t* row_of, int nchunk, uint32_t* cnt, const int64_t* off, GramEntry* list, double* G,
+                       int ld, hipStream_t st);
 void launch_gram_finish(FactorArgs f, int patient, int scen_begin, int nscen, int npad, int n, double rho,
                         int accumulate_gsum, hipStream_t st);
 void launch_sweep_step(FactorArgs f, int scen_begin, int nscen, int npad, int k0, hipStream_t st);

@@ -301,6 +301,28 @@ def test_tile_gram_matches_the_normal_equations_and_the_atomic_gram(which, monke
         assert np.linalg.norm(x_tile[s] - x_atom[s]) <= 1e-6 * np.linalg.norm(x_atom[s])
 
 
+@pytest.mark.parametrize("spots,grid,zeros", [((1, 1), (10, 10, 10), False), ((7, 9), (9, 11, 7), False),
+                                              ((8, 8), (9, 11, 7), True), ((5, 13), (9, 11, 7), False)])
+def test_tile_gram_at_block_edges(spots, grid, zeros, monkeypatch):
+    """1, 63, 64 and 65 spots, 693 voxels (a ragged last group of 64), and
+    explicit zeros among the stored values (they count for no tile's sum)."""
+    P = synth.make_tiny(5, spots=spots, grid=grid, num_scen=2)
+    if zeros:
+        for a in P.A:
+            a.val[::7] = 0.0
+    W = wls.from_problem(P)
+    rho, x_tile = _first_x_update(P, monkeypatch, atomic=False)
+    rho_a, x_atom = _first_x_update(P, monkeypatch, atomic=True)
+    assert rho == rho_a
+    for s in range(P.num_scen):
+        b = W.A[s].T @ (W.c[s] * W.w * W.p)
+        r = wls.normal_apply(W, s, x_tile[s], rho) - b
+        assert np.linalg.norm(r) <= 1e-4 * np.linalg.norm(b)
+        # both forms sum in fp64; the inverses are then rounded to fp32 (2^-24
+        # each) and applied to the same right-hand side
+        assert np.linalg.norm(x_tile[s] - x_atom[s]) <= 1e-5 * np.linalg.norm(x_atom[s])
+
+
 def test_dense_set_up_and_iterations_are_bitwise_reproducible(monkeypatch):
     """The Gram tiles are summed in 64-bit fixed point (exact, independent of
     the order of the atomics) and everything after them in fixed order, so two
