@@ -424,7 +424,7 @@ struct admm_ctx {
       const int g0 = pt.scen_begin + c0;
       gram_chunk(pt, g0, cs, nn);
       launch_gram_finish(f, p, g0, cs, npad, pt.n, rho[p], accumulate_gsum ? 1 : 0, stream);
-      for (int k0 = 0; k0 < npad; k0 += 64) launch_sweep_step(f, g0, cs, npad, k0, stream);
+      launch_sweep(f, cs, npad, stream);
       launch_sweep_store(f, p, g0, cs, npad, stream);
     }
     check(hipGetLastError(), "factor launch");
@@ -1044,9 +1044,10 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
       fits_n = fits_n && n <= 8128;
       const int64_t per_scen = 16 * npad * npad;
       const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(N, kChunkBytes / per_scen));
-      chunk_need = std::max(chunk_need, chunk * per_scen);
-      // every iteration: packed fp32 inverses, packed fp64 sum of G, tile partials; U, R panels
-      need += tiles * 4096 * (4 * N + 8) + tiles * 1024 * N + 2 * 8 * 64 * npad * N;
+      // the chunk's Gram and sweep matrices with the sweep's U, R panels
+      chunk_need = std::max(chunk_need, chunk * (per_scen + 2 * 8 * 128 * npad));
+      // every iteration: packed fp32 inverses, packed fp64 sum of G, tile partials
+      need += tiles * 4096 * (4 * N + 8) + tiles * 1024 * N;
     }
     need += chunk_need;
     size_t free_b = 0, total_b = 0;
@@ -1158,9 +1159,11 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
       c->d_b64 = c->upload(H.b64);
       c->d_Gp = c->alloc<double>(static_cast<size_t>(goff));
       c->gp_elems = goff;
-      c->d_Pb = c->alloc<double>(static_cast<size_t>(c->G) * 64 * 64);
-      c->d_U = c->alloc<double>(static_cast<size_t>(c->G) * 64 * c->ld_max);
-      c->d_R = c->alloc<double>(static_cast<size_t>(c->G) * 64 * c->ld_max);
+      // the sweep's pivot inverses and panels of the largest chunk
+      const size_t cmax = static_cast<size_t>(*std::max_element(c->chunk_scen.begin(), c->chunk_scen.end()));
+      c->d_Pb = c->alloc<double>(cmax * 128 * 128);
+      c->d_U = c->alloc<double>(cmax * 128 * c->ld_max);
+      c->d_R = c->alloc<double>(cmax * 128 * c->ld_max);
       c->d_fpart = c->alloc<double>(fjobs.size());
       c->d_xtiles = c->upload(xtiles);
       c->d_fjobs = c->upload(fjobs);

@@ -12,7 +12,7 @@
 //     A = G_s + rho/2 I (identity on the padding to npad) and sum_s G_s.
 //     Steps 1-3 run on chunks of scenarios, so that only a chunk's fp64
 //     set-up matrices occupy device memory at a time.
-//  3. block sweep (Gauss-Jordan on 64-blocks, no pivoting: the pivot blocks
+//  3. block sweep (Gauss-Jordan on 128-blocks, no pivoting: the pivot blocks
 //     are Schur complements of an SPD matrix): for each block K,
 //        P = A_KK^-1, U = A_:K P, R = A_K: (old),
 //        A_ij -= U_i R_j off the block row and column,
@@ -34,6 +34,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "internal.h"
 #include "scalars.h"
@@ -42,9 +43,10 @@ namespace admmbb {
 
 namespace {
 
+typedef double v2d __attribute__((ext_vector_type(2)));
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-constexpr int kFb = 64;  // sweep block size and packed tile size
+constexpr int kFb = 64;  // packed tile size
 
 __host__ __device__ __forceinline__ int64_t tile_index(int I, int J, int nb) {
   return static_cast<int64_t>(I) * nb - static_cast<int64_t>(I) * (I - 1) / 2 + (J - I);
@@ -452,174 +454,375 @@ __global__ __launch_bounds__(256) void k_gram_finish(FactorArgs f, int patient, 
 // block sweep
 // ---------------------------------------------------------------------------
 
-// P = A_KK^-1 by the scalar sweep (one workgroup per scenario)
-__global__ __launch_bounds__(256) void k_sweep_pivot(FactorArgs f, int scen_begin, int npad, int k0) {
-  // thread (i0, j) keeps rows i0, i0 + 4, ..., i0 + 60 of column j in
-  // registers; each step publishes only the pivot row and column (their values
-  // before the step) through LDS
-  __shared__ double prow[kFb], pcol[kFb];
-  const int g = scen_begin + static_cast<int>(blockIdx.x);
-  const double* A = f.A + static_cast<int64_t>(blockIdx.x) * npad * npad;  // chunk buffer
-  const int j = threadIdx.x & (kFb - 1), i0 = threadIdx.x >> 6;
-  double r[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) r[q] = A[static_cast<int64_t>(k0 + i0 + 4 * q) * npad + k0 + j];
-#pragma unroll
-  for (int t = 0; t < kFb; ++t) {
-    if (i0 == (t & 3)) prow[j] = r[t >> 2];
-    if (j == t) {
-#pragma unroll
-      for (int q = 0; q < 16; ++q) pcol[i0 + 4 * q] = r[q];
-    }
-    __syncthreads();
-    const double inv = 1.0 / prow[t];
-    const double atj = prow[j];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int i = i0 + 4 * q;
-      const double ait = pcol[i];
-      double v;
-      if (i == t && j == t)
-        v = -inv;
-      else if (i == t)
-        v = atj * inv;
-      else if (j == t)
-        v = ait * inv;
-      else
-        v = r[q] - ait * atj * inv;
-      r[q] = v;
-    }
-    __syncthreads();  // the next step overwrites the pivot row and column
-  }
-  // the swept block is -A_KK^-1
-  double* P = f.P + static_cast<int64_t>(g) * kFb * kFb;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) P[(i0 + 4 * q) * kFb + j] = -r[q];
+// The sweep takes pivot blocks of kKb = 128 (a last one of 64 where npad / 64 is
+// odd), so that every tile of the matrix is read and written once per 128
+// columns: at 13 scenarios of 2 981 spots one pass over the upper tiles moves
+// 0.96 GB, which bounded the rank-64 update (275 us a step, twice as many
+// steps); the rank-128 products run on the fp64 MFMA.
+constexpr int kKb = 128;
+
+// Value of lane t of the lane's row of 16, in every lane of the row.
+template <int t>
+__device__ __forceinline__ double row_bcast(double x) {
+  return dpp_move<0x150 + t>(x);  // row_newbcast
 }
 
-// U_I = A_IK P (64 x 64 per workgroup) and R tile = A_K,I (old row panel copy).
-// Only the upper tiles (I <= J) of the sweep matrix are kept up to date (it
-// stays symmetric), so blocks on the other side of the pivot are read from the
-// mirrored tile, transposed.
-__global__ __launch_bounds__(256) void k_sweep_panel(FactorArgs f, int scen_begin, int npad, int k0) {
-  __shared__ double at[kFb][kFb];  // A_IK
-  __shared__ double p[kFb][kFb];   // P
-  const int g = scen_begin + static_cast<int>(blockIdx.y);
-  const double* A = f.A + static_cast<int64_t>(blockIdx.y) * npad * npad;  // chunk buffer
-  const int i0 = static_cast<int>(blockIdx.x) * kFb;
-  const double* Pg = f.P + static_cast<int64_t>(g) * kFb * kFb;
-  double* Ut = f.U + static_cast<int64_t>(g) * f.npmax * kFb;
-  double* R = f.R + static_cast<int64_t>(g) * f.npmax * kFb;
-  for (int e = threadIdx.x; e < kFb * kFb; e += 256) {
-    const int r = e / kFb, c = e % kFb;
-    p[r][c] = Pg[e];
-    if (i0 <= k0) {
-      at[r][c] = A[static_cast<int64_t>(i0 + r) * npad + k0 + c];  // tile (I, K), stored
-    } else {
-      at[c][r] = A[static_cast<int64_t>(k0 + r) * npad + i0 + c];  // tile (K, I), transposed
+// In place, the sweep of a 16 x 16 matrix held by one wave in the MFMA's output
+// layout (item q of lane l: row l / 16 + 4 q, column l % 16): -inverse.
+template <int t>
+__device__ __forceinline__ void sweep16_steps(double (&r)[4], int m, int kk) {
+  constexpr int tk = t & 3, tq = t >> 2;
+  const double rowv = __shfl(r[tq], 16 * tk + m, 64);  // pivot row
+  const double inv = 1.0 / row_bcast<t>(rowv);
+  const double w = m == t ? -inv : rowv * inv;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double c = row_bcast<t>(r[q]);  // pivot column
+    r[q] = fma(-c, w, m == t ? 0.0 : r[q]);
+  }
+  if (kk == tk) r[tq] = w;
+  if constexpr (t < 15) sweep16_steps<t + 1>(r, m, kk);
+}
+
+// P = A_KK^-1 for a pivot block of KB = 128 or 64 (one workgroup of eight waves
+// per scenario): the same block sweep on 16-blocks, the upper 16 x 16 tiles kept
+// in LDS.  Per 16-block b: U_i^T = P16 M_bi (one wave per i), then M_ij -= U_i
+// M_bj by the MFMA; the wave that owns the next pivot tile updates it first and
+// inverts it in registers while the others work, so the chain is eight times 16
+// scalar steps of about 0.2 us.  A scalar sweep of 64 columns, two barriers a
+// step, took 65 us; this takes 32 us for 128 and 14 for 64.
+template <int KB>
+__global__ __launch_bounds__(512) void k_sweep_pivot(FactorArgs f, int npad, int k0) {
+  constexpr int NB = KB / 16, NT = NB * (NB + 1) / 2;
+  __shared__ double M[NT * 256];      // tile (i, j), i <= j, row-major
+  __shared__ double U[NB * 256];      // U_i^T
+  __shared__ double V[NB * 256];      // M_bi before the step
+  __shared__ double P16[2][256];
+  const int g = static_cast<int>(blockIdx.x);  // place in the chunk
+  const double* A = f.A + static_cast<int64_t>(blockIdx.x) * npad * npad;  // chunk buffer
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 15, kk = lane >> 4;
+  auto tile = [](int i, int j) { return 256 * (i * NB - i * (i - 1) / 2 + (j - i)); };
+  // upper 16 x 16 tile t -> (i, j)
+  auto place = [](int t, int& i, int& j) {
+    i = 0;
+    while (t >= NB - i) {
+      t -= NB - i;
+      ++i;
     }
-    // row panel R[t][i0 + j] = A[k0 + t][i0 + j]
-    if (i0 >= k0)
-      R[static_cast<int64_t>(r) * npad + i0 + c] = A[static_cast<int64_t>(k0 + r) * npad + i0 + c];
-    else
-      R[static_cast<int64_t>(c) * npad + i0 + r] = A[static_cast<int64_t>(i0 + r) * npad + k0 + c];
+    j = i + t;
+  };
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  constexpr int kPer = (NT + 7) / 8;  // tiles of a wave, all requested at once
+  double x[kPer][4];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    int i, j;
+    place(wu + 8 * u < NT ? wu + 8 * u : 0, i, j);
+    const double* T = A + static_cast<int64_t>(k0 + 16 * i) * npad + k0 + 16 * j;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[u][q] = T[static_cast<int64_t>(kk + 4 * q) * npad + m];
+  }
+#pragma unroll
+  for (int u = 0; u < kPer; ++u)
+    if (wu + 8 * u < NT) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) M[256 * (wu + 8 * u) + (kk + 4 * q) * 16 + m] = x[u][q];
+    }
+  __syncthreads();
+  auto invert = [&](double (&r)[4], double* out) {
+    sweep16_steps<0>(r, m, kk);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[(kk + 4 * q) * 16 + m] = -r[q];
+  };
+  if (w == 0) {
+    double r[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) r[q] = M[(kk + 4 * q) * 16 + m];
+    invert(r, P16[0]);
   }
   __syncthreads();
-  const int ti = threadIdx.x >> 4, tj = threadIdx.x & 15;  // 4 x 4 outputs each
-  double acc[4][4] = {};
-  for (int t = 0; t < kFb; ++t) {
-    double av[4], pv[4];
+  for (int b = 0; b < NB; ++b) {
+    const double* P = P16[b & 1];
+    // panel: wave i
+    if (w < NB && w != b) {
+      double v[4];
+      v4d d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        // M_bi [kk + 4 q][m]
+        v[q] = b < w ? M[tile(b, w) + (kk + 4 * q) * 16 + m] : M[tile(w, b) + m * 16 + kk + 4 * q];
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(P[(kk + 4 * q) * 16 + m], v[q], d, 0, 0, 0);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        V[w * 256 + (kk + 4 * q) * 16 + m] = v[q];
+        U[w * 256 + (kk + 4 * q) * 16 + m] = d[q];
+      }
+    }
+    __syncthreads();
+    auto update = [&](int i, int j, double (&r)[4]) {
+      double* T = M + tile(i, j);
+      v4d d;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) d[q] = -T[(kk + 4 * q) * 16 + m];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(U[i * 256 + (kk + 4 * q) * 16 + m], V[j * 256 + (kk + 4 * q) * 16 + m], d,
+                                                 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        r[q] = -d[q];
+        T[(kk + 4 * q) * 16 + m] = r[q];
+      }
+    };
+    double r[4];
+    if (w == 0 && b + 1 < NB) {
+      update(b + 1, b + 1, r);
+      invert(r, P16[(b + 1) & 1]);
+    } else {
+      // the other tiles, dealt to the other waves (to all of them in the last step)
+      const int first = b + 1 < NB ? 1 : 0, nw = 8 - first;
+      for (int t = wu - first; t < NT; t += nw) {
+          int i, j;
+          place(t, i, j);
+          if (i == b + 1 && j == b + 1) continue;
+          double* T = M + tile(i, j);
+          if (i != b && j != b) {
+            update(i, j, r);
+          } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int row = kk + 4 * q;
+              T[row * 16 + m] = i == j ? -P[row * 16 + m] : (i == b ? U[j * 256 + row * 16 + m] : U[i * 256 + m * 16 + row]);
+            }
+          }
+      }
+    }
+    __syncthreads();
+  }
+  // the swept block is -A_KK^-1; both triangles of P
+  double* P = f.P + static_cast<int64_t>(g) * kKb * kKb;
+  for (int t = wu; t < NT; t += 8) {
+    int i, j;
+    place(t, i, j);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      av[q] = at[4 * ti + q][t];
-      pv[q] = p[t][4 * tj + q];
+      const int r = kk + 4 * q;
+      P[(16 * i + r) * kKb + 16 * j + m] = -M[256 * t + r * 16 + m];
+      if (i != j) P[(16 * j + r) * kKb + 16 * i + m] = -M[256 * t + m * 16 + r];
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[q][r] = fma(av[q], pv[r], acc[q][r]);
   }
-  // stored transposed: Ut[c][i] = U[i][c]
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) Ut[static_cast<int64_t>(4 * tj + r) * npad + i0 + 4 * ti + q] = acc[q][r];
 }
 
-// rank-64 update of every upper tile off the pivot row and column; panel tiles replaced
-__global__ __launch_bounds__(256) void k_sweep_update(FactorArgs f, int scen_begin, int npad, int k0) {
-  __shared__ double ut[kFb][kFb];  // ut[t][i] = U[i0 + i][t]
-  __shared__ double rs[kFb][kFb];  // rs[t][j] = R[t][j0 + j]
-  const int nbk = npad / kFb;
+// Panels of a pivot block for 64 columns i of the matrix: R = A_K,i (old values)
+// and Ut = U^T = P A_K,i.  Only the upper tiles (I <= J) of the sweep matrix are
+// kept up to date (it stays symmetric), so blocks before the pivot are read from
+// the mirrored tile, transposed.  The columns of A_K,i go through LDS 32 rows at
+// a time; wave w forms KB / 4 rows of Ut, its operand P read by columns (P is
+// symmetric) straight from memory.
+template <int KB>
+__global__ __launch_bounds__(256) void k_sweep_panel(FactorArgs f, int npad, int k0) {
+  constexpr int kLd = kFb + 16;
+  __shared__ double ks[32][kLd];
+  const int g = static_cast<int>(blockIdx.y);  // place in the chunk
+  const double* A = f.A + static_cast<int64_t>(blockIdx.y) * npad * npad;  // chunk buffer
+  const int i0 = static_cast<int>(blockIdx.x) * kFb;
+  const double* Pg = f.P + static_cast<int64_t>(g) * kKb * kKb;
+  double* Ut = f.U + static_cast<int64_t>(g) * f.npmax * kKb;
+  double* R = f.R + static_cast<int64_t>(g) * f.npmax * kKb;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 15, kk = lane >> 4;
+  constexpr int NC = KB / 64;  // 16-row groups of Ut per wave
+  v4d acc[NC][4];
+#pragma unroll
+  for (int a = 0; a < NC; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
+  for (int s0 = 0; s0 < KB; s0 += 32) {
+    double x[8];
+    const bool stored = i0 / kFb >= (k0 + s0) / kFb;  // tile (K, I) of the upper tiles
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int e = tid + 256 * q;
+      if (stored)
+        x[q] = A[static_cast<int64_t>(k0 + s0 + e / kFb) * npad + i0 + e % kFb];
+      else
+        x[q] = A[static_cast<int64_t>(i0 + e / 32) * npad + k0 + s0 + e % 32];
+    }
+    __syncthreads();  // the last slab has been read
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int e = tid + 256 * q;
+      if (stored)
+        ks[e / kFb][e % kFb] = x[q];
+      else
+        ks[e % 32][e / 32] = x[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int e = tid + 256 * q;
+      R[static_cast<int64_t>(s0 + e / kFb) * npad + i0 + e % kFb] = ks[e / kFb][e % kFb];
+    }
+#pragma unroll
+    for (int h = 0; h < 8; ++h) {
+      double av[NC], bv[4];
+#pragma unroll
+      for (int a = 0; a < NC; ++a) av[a] = Pg[(s0 + 4 * h + kk) * kKb + (w * NC + a) * 16 + m];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) bv[b] = ks[4 * h + kk][16 * b + m];
+#pragma unroll
+      for (int a = 0; a < NC; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < NC; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        Ut[static_cast<int64_t>((w * NC + a) * 16 + kk + 4 * r) * npad + i0 + 16 * b + m] = acc[a][b][r];
+}
+
+// Element at a wave-uniform base and a byte offset per lane: one scalar pointer
+// and one 32-bit register address it.
+template <class T>
+__device__ __forceinline__ T* at_bytes(T* base, uint32_t bytes) {
+  return reinterpret_cast<T*>(reinterpret_cast<std::conditional_t<std::is_const_v<T>, const char*, char*>>(base) + bytes);
+}
+
+// Rank-KB update A_ij -= U_i R_j of one upper 64 x 64 tile off the pivot row and
+// column, whose tiles are replaced by the panels.  Waves 2 x 2, 32 rows and
+// columns each, on the fp64 MFMA: the accumulators start from -A_ij, the panels
+// pass through LDS in slabs of 16 columns, the next slab's loads in flight over
+// the current one's products.  13 scenarios of 2 981 spots: 328 us a step of 128
+// (47 TFLOP/s, the products' issue; the rank-64 vector form took 2 x 275 us),
+// 351 us with blocks of 128 x 128 (at 1 700 spots 129 against 104 us: too few
+// blocks), and the same with an XCD's tiles next to each other.
+template <int KB>
+__global__ __launch_bounds__(256, 4) void k_sweep_update(FactorArgs f, int npad, int k0) {
+  constexpr int MT = kFb, kLd = MT + 16, kSlab = 16;
+  constexpr int W = MT / 32;                 // 16-wide groups of a wave
+  constexpr int kQ = kSlab * MT / 2 / 256;   // double2 per thread, slab and panel
+  __shared__ __align__(16) double us[2][kSlab * kLd], rs[2][kSlab * kLd];
+  const int nm = npad / MT;
   // upper tile number -> (bi, bj), bi <= bj
   int t0 = static_cast<int>(blockIdx.x), bi = 0;
-  while (t0 >= nbk - bi) {
-    t0 -= nbk - bi;
+  while (t0 >= nm - bi) {
+    t0 -= nm - bi;
     ++bi;
   }
   const int bj = bi + t0;
-  const int g = scen_begin + static_cast<int>(blockIdx.y);
+  const int g = static_cast<int>(blockIdx.y);  // place in the chunk
   double* A = f.A + static_cast<int64_t>(blockIdx.y) * npad * npad;  // chunk buffer
-  const int i0 = bi * kFb, j0 = bj * kFb, kb = k0 / kFb;
-  const double* Ut = f.U + static_cast<int64_t>(g) * f.npmax * kFb;
-  const double* R = f.R + static_cast<int64_t>(g) * f.npmax * kFb;
-  if (bi == kb || bj == kb) {
-    const double* Pg = f.P + static_cast<int64_t>(g) * kFb * kFb;
-    for (int e = threadIdx.x; e < kFb * kFb; e += 256) {
-      const int i = e / kFb, j = e % kFb;
-      double v;
-      if (bi == kb && bj == kb)
-        v = -Pg[e];
-      else if (bj == kb)
-        v = Ut[static_cast<int64_t>(j) * npad + i0 + i];  // U[i0 + i][j]
-      else
-        v = Ut[static_cast<int64_t>(i) * npad + j0 + j];  // U[j0 + j][i]
-      A[static_cast<int64_t>(i0 + i) * npad + j0 + j] = v;
+  const int i0 = bi * MT, j0 = bj * MT;
+  const double* Ut = f.U + static_cast<int64_t>(g) * f.npmax * kKb;
+  const double* R = f.R + static_cast<int64_t>(g) * f.npmax * kKb;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 15, kk = lane >> 4;
+  const bool rowK = i0 / kKb == k0 / kKb, colK = j0 / kKb == k0 / kKb;
+  if (rowK || colK) {
+    const double* Pg = f.P + static_cast<int64_t>(g) * kKb * kKb;
+    double* tr = us[0];  // 32 x 33, for the transposed copies
+    for (int sub = 0; sub < MT / 32 * (MT / 32); ++sub) {
+      const int r0 = i0 + 32 * (sub / (MT / 32)), c0 = j0 + 32 * (sub % (MT / 32));
+      if (rowK) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int r = r0 + (tid >> 5) + 8 * q, c = c0 + (tid & 31);
+          A[static_cast<int64_t>(r) * npad + c] = colK ? -Pg[(r - k0) * kKb + c - k0] : Ut[static_cast<int64_t>(r - k0) * npad + c];
+        }
+      } else {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int c = c0 + (tid >> 5) + 8 * q, r = r0 + (tid & 31);
+          tr[((tid >> 5) + 8 * q) * 33 + (tid & 31)] = Ut[static_cast<int64_t>(c - k0) * npad + r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int r = r0 + (tid >> 5) + 8 * q, c = c0 + (tid & 31);
+          A[static_cast<int64_t>(r) * npad + c] = tr[(tid & 31) * 33 + (tid >> 5) + 8 * q];
+        }
+      }
     }
     return;
   }
-  // thread (ti, tj) updates rows 4 ti .. 4 ti + 3 and columns tj, tj + 16,
-  // tj + 32, tj + 48 of the tile; its old values and both panels are all
-  // requested before the first use
-  const int ti = threadIdx.x >> 4, tj = threadIdx.x & 15;
-  double a_old[4][4];
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  const int wi = (MT / 2) * (wu >> 1), wj = (MT / 2) * (wu & 1);
+  // every address: a wave-uniform base and a 32-bit byte offset per lane
+  uint32_t oi[kQ], oj[kQ];
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) a_old[q][r] = A[static_cast<int64_t>(i0 + 4 * ti + q) * npad + j0 + tj + 16 * r];
-  double us[16], rr[16];
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int e = threadIdx.x + 256 * k;
-    const int t = e / kFb, c = e % kFb;
-    us[k] = Ut[static_cast<int64_t>(t) * npad + i0 + c];
-    rr[k] = R[static_cast<int64_t>(t) * npad + j0 + c];
+  for (int q = 0; q < kQ; ++q) {
+    const int e = tid + 256 * q, r = e / (MT / 2), c = 2 * (e % (MT / 2));
+    oi[q] = 8u * static_cast<uint32_t>(r * npad + i0 + c);
+    oj[q] = 8u * static_cast<uint32_t>(r * npad + j0 + c);
   }
+  v2d ub[kQ], rb[kQ];
+  auto fetch = [&](int s) {
+    const double* u = Ut + static_cast<int64_t>(s) * kSlab * npad;
+    const double* r = R + static_cast<int64_t>(s) * kSlab * npad;
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int e = threadIdx.x + 256 * k;
-    ut[e / kFb][e % kFb] = us[k];
-    rs[e / kFb][e % kFb] = rr[k];
-  }
-  __syncthreads();
-  double acc[4][4] = {};
-  for (int t = 0; t < kFb; ++t) {
-    double uv[4], rv[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      uv[q] = ut[t][4 * ti + q];
-      rv[q] = rs[t][tj + 16 * q];
+    for (int q = 0; q < kQ; ++q) {
+      ub[q] = *reinterpret_cast<const v2d*>(at_bytes(u, oi[q]));
+      rb[q] = *reinterpret_cast<const v2d*>(at_bytes(r, oj[q]));
     }
+  };
+  auto stage = [&](int buf) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < kQ; ++q) {
+      const int e = tid + 256 * q, r = e / (MT / 2), c = 2 * (e % (MT / 2));
+      *reinterpret_cast<v2d*>(&us[buf][r * kLd + c]) = ub[q];
+      *reinterpret_cast<v2d*>(&rs[buf][r * kLd + c]) = rb[q];
+    }
+  };
+  fetch(0);
+  v4d acc[W][W];
+  double* Aw = A + static_cast<int64_t>(i0 + wi) * npad + j0 + wj;
+  const uint32_t oa = 8u * static_cast<uint32_t>(kk * npad + m);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[q][r] = fma(uv[q], rv[r], acc[q][r]);
+  for (int a = 0; a < W; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double* row = Aw + static_cast<int64_t>(16 * a + 4 * r) * npad;
+#pragma unroll
+      for (int b = 0; b < W; ++b) acc[a][b][r] = -*at_bytes(row + 16 * b, oa);
+    }
+  stage(0);
+  __syncthreads();
+  constexpr int ns = KB / kSlab;
+#pragma unroll 2
+  for (int s = 0; s < ns; ++s) {
+    fetch(s + 1 < ns ? s + 1 : 0);  // the last round's is not used
+    __builtin_amdgcn_sched_barrier(0);  // requested before the products, waited for after them
+    const double* u = &us[s & 1][kk * kLd + wi + m];
+    const double* v = &rs[s & 1][kk * kLd + wj + m];
+#pragma unroll
+    for (int h = 0; h < kSlab / 4; ++h) {
+      double av[W], bv[W];
+#pragma unroll
+      for (int q = 0; q < W; ++q) {
+        av[q] = u[4 * h * kLd + 16 * q];
+        bv[q] = v[4 * h * kLd + 16 * q];
+      }
+#pragma unroll
+      for (int a = 0; a < W; ++a)
+#pragma unroll
+        for (int b = 0; b < W; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    stage((s + 1) & 1);
+    __syncthreads();
   }
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+  for (int a = 0; a < W; ++a)
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      A[static_cast<int64_t>(i0 + 4 * ti + q) * npad + j0 + tj + 16 * r] = a_old[q][r] - acc[q][r];
+    for (int r = 0; r < 4; ++r) {
+      double* row = Aw + static_cast<int64_t>(16 * a + 4 * r) * npad;
+#pragma unroll
+      for (int b = 0; b < W; ++b) *at_bytes(row + 16 * b, oa) = -acc[a][b][r];
+    }
 }
 
 // Position of entry (r, c) inside a stored 64 x 64 tile of M_s.  Thread t of
@@ -1187,11 +1390,20 @@ void launch_gram_finish(FactorArgs f, int patient, int scen_begin, int nscen, in
                      nscen, npad, n, rho, accumulate_gsum);
 }
 
-void launch_sweep_step(FactorArgs f, int scen_begin, int nscen, int npad, int k0, hipStream_t st) {
-  const int nbk = npad / kFb;
-  hipLaunchKernelGGL(k_sweep_pivot, dim3(nscen), dim3(256), 0, st, f, scen_begin, npad, k0);
-  hipLaunchKernelGGL(k_sweep_panel, dim3(nbk, nscen), dim3(256), 0, st, f, scen_begin, npad, k0);
-  hipLaunchKernelGGL(k_sweep_update, dim3(nbk * (nbk + 1) / 2, nscen), dim3(256), 0, st, f, scen_begin, npad, k0);
+void launch_sweep(FactorArgs f, int nscen, int npad, hipStream_t st) {
+  const int n64 = npad / 64, nt = n64 * (n64 + 1) / 2;
+  auto step = [&](auto kbc, int k0) {
+    constexpr int KB = decltype(kbc)::value;
+    hipLaunchKernelGGL(k_sweep_pivot<KB>, dim3(nscen), dim3(512), 0, st, f, npad, k0);
+    hipLaunchKernelGGL(k_sweep_panel<KB>, dim3(n64, nscen), dim3(256), 0, st, f, npad, k0);
+    hipLaunchKernelGGL(k_sweep_update<KB>, dim3(nt, nscen), dim3(256), 0, st, f, npad, k0);
+  };
+  for (int k0 = 0; k0 < npad; k0 += kKb) {
+    if (npad - k0 >= kKb)
+      step(std::integral_constant<int, kKb>{}, k0);
+    else
+      step(std::integral_constant<int, 64>{}, k0);
+  }
 }
 
 void launch_gq_pack(const double* Gp, uint32_t* Gq, int64_t ntiles, hipStream_t st) {

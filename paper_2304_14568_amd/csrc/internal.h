@@ -250,9 +250,9 @@ struct FactorArgs {
   float* Mp;          // per scenario: packed (G_s + rho/2 I)^-1, fp32
   double* Gp;         // per patient: packed sum_s G_s, fp64
   const double* g0;   // per patient: 2 sum_s A_s^T c_s W p, fp64 (zvec layout)
-  double* P;          // per scenario: 64 x 64 pivot-block inverse
-  double* U;          // per scenario: 64 x npmax column panel, transposed
-  double* R;          // per scenario: 64 x npmax row panel
+  double* P;          // set-up chunk, per scenario: 128 x 128 pivot-block inverse
+  double* U;          // set-up chunk, per scenario: 128 x npmax column panel, transposed
+  double* R;          // set-up chunk, per scenario: 128 x npmax row panel
   double* xpart;      // per packed tile of every scenario: T c_J (64) and T^T c_I (64), fp64
   const XTile* xtiles; // x-update: one per packed tile of every scenario
   int32_t nxtiles;
@@ -306,7 +306,7 @@ void launch_gram_tiles(const MatDev& m, const double* rw64, const Scen* scen, in
                        int ld, hipStream_t st);
 void launch_gram_finish(FactorArgs f, int patient, int scen_begin, int nscen, int npad, int n, double rho,
                         int accumulate_gsum, hipStream_t st);
-void launch_sweep_step(FactorArgs f, int scen_begin, int nscen, int npad, int k0, hipStream_t st);
+void launch_sweep(FactorArgs f, int nscen, int npad, hipStream_t st);
 void launch_sweep_store(FactorArgs f, int patient, int scen_begin, int nscen, int npad, hipStream_t st);
 void launch_gq_pack(const double* Gp, uint32_t* Gq, int64_t ntiles, hipStream_t st);
 void launch_xsym(const FactorArgs& f, const double* c, int njobs, hipStream_t st, hipEvent_t e0 = nullptr,

@@ -323,6 +323,27 @@ def test_tile_gram_at_block_edges(spots, grid, zeros, monkeypatch):
         assert np.linalg.norm(x_tile[s] - x_atom[s]) <= 1e-5 * np.linalg.norm(x_atom[s])
 
 
+@pytest.mark.parametrize("spots,num_scen", [((8, 16), 1), ((3, 43), 2), ((12, 16), 3), ((13, 20), 2)])
+def test_sweep_at_pivot_block_edges(spots, num_scen):
+    """128, 129, 192 and 260 spots: whole pivot blocks of 128, a last one of 64
+    (npad = 192, 320), and one scenario per pivot launch; x_s of the first
+    iteration against fp64 solves of the same systems."""
+    import paper_2304_14568_amd as A
+    P = synth.make_tiny(6, spots=spots, spacing=1.5, num_scen=num_scen)
+    W = wls.from_problem(P)
+    with A.Solver(P, xupdate="dense") as S:
+        rho = S.rho()
+        S.iterate(1)
+        st = S.get_state()
+    x = np.asarray(st["d"]).reshape(P.num_scen, P.n) + np.asarray(st["z"])[None, :]
+    for s in range(P.num_scen):
+        a = W.A[s].toarray()
+        B = a.T @ ((W.c[s] * W.w)[:, None] * a) + 0.5 * rho * np.eye(P.n)
+        ref = np.linalg.solve(B, a.T @ (W.c[s] * W.w * W.p))
+        # the inverse is stored in fp32: entries 2^-24 off, |M||b| / |M b| below 130
+        assert np.linalg.norm(x[s] - ref) <= 130 * 2.0 ** -24 * np.linalg.norm(ref)
+
+
 def test_dense_set_up_and_iterations_are_bitwise_reproducible(monkeypatch):
     """The Gram tiles are summed in 64-bit fixed point (exact, independent of
     the order of the atomics) and everything after them in fixed order, so two
