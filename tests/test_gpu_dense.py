@@ -323,6 +323,30 @@ def test_tile_gram_at_block_edges(spots, grid, zeros, monkeypatch):
         assert np.linalg.norm(x_tile[s] - x_atom[s]) <= 1e-5 * np.linalg.norm(x_atom[s])
 
 
+@pytest.mark.parametrize("chunk_mb", ["", "1"])
+def test_new_penalty_equals_a_fresh_set_up(chunk_mb, monkeypatch):
+    """Two patients of different sizes in one context, their penalties changed in
+    turn: the inverses equal those of contexts set up with the penalty, bit for
+    bit, whether the Gram matrices of the patient are still on the device or
+    not, and with chunks of one scenario (1 MiB)."""
+    import paper_2304_14568_amd as A
+    if chunk_mb:
+        monkeypatch.setenv("ADMMBB_DENSE_CHUNK_MB", chunk_mb)
+    Ps = [synth.make_tiny(7, spots=(13, 20), spacing=1.5), synth.make_tiny(8)]
+    with A.Solver(Ps, xupdate="dense") as S:
+        rho = [S.rho(0), S.rho(1)]
+        for p, f in ((1, 2.0), (1, 0.5), (0, 2.0), (0, 3.0), (1, 1.5)):
+            S.warm_start(p, None, f * rho[p])
+        S.iterate(2)
+        got = [S.get_state(0), S.get_state(1)]
+    for p, f in ((0, 3.0), (1, 1.5)):
+        with A.Solver(Ps[p], xupdate="dense", rho=f * rho[p]) as S:
+            S.iterate(2)
+            want = S.get_state()
+        for key in ("z", "y", "d"):
+            assert np.array_equal(got[p][key], want[key]), (p, key)
+
+
 @pytest.mark.parametrize("spots,num_scen", [((8, 16), 1), ((3, 43), 2), ((12, 16), 3), ((13, 20), 2)])
 def test_sweep_at_pivot_block_edges(spots, num_scen):
     """128, 129, 192 and 260 spots: whole pivot blocks of 128, a last one of 64
