@@ -81,6 +81,9 @@ struct admm_ctx {
   float *d_x = nullptr, *d_r = nullptr, *d_v = nullptr, *d_q = nullptr, *d_zp = nullptr, *d_y = nullptr;
   float *d_b = nullptr, *d_dinv = nullptr, *d_z = nullptr, *d_lb = nullptr, *d_ub = nullptr;
   float *d_pvec = nullptr, *d_pvec2 = nullptr, *d_pvec3 = nullptr, *d_mvec = nullptr;
+  int mvec_scen = 1;        // m-vectors of the largest patient that d_mvec holds
+  void* d_dose = nullptr;   // staging of the dose statistics, grown to the largest call
+  size_t dose_bytes = 0;
   float* d_tmax = nullptr;  // kAbsMaxBlocks partial maxima of the transpose product's input
   double* d_dprev = nullptr;
   float* d_part = nullptr;
@@ -211,6 +214,7 @@ struct admm_ctx {
     if (ev_a) (void)hipEventDestroy(ev_a);
     if (ev_b) (void)hipEventDestroy(ev_b);
     for (void* p : allocs) (void)hipFree(p);
+    if (d_dose) (void)hipFree(d_dose);
     if (h_ps) (void)hipHostFree(h_ps);
     if (h_scr) (void)hipHostFree(h_scr);
     if (own_stream && stream) (void)hipStreamDestroy(stream);
@@ -1271,7 +1275,9 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
     c->d_pvec = c->alloc<float>(H.zvec_total);
     c->d_pvec2 = c->alloc<float>(H.zvec_total);
     c->d_pvec3 = c->alloc<float>(H.zvec_total);
-    c->d_mvec = c->alloc<float>(H.mmax);
+    // voxel vectors of up to 16 scenarios, which the dose statistics take together
+    for (const Pat& pt : H.pat) c->mvec_scen = std::max(c->mvec_scen, std::min(pt.num_scen, 16));
+    c->d_mvec = c->alloc<float>(static_cast<size_t>(H.mmax) * c->mvec_scen);
     c->d_tmax = c->alloc<float>(kAbsMaxBlocks);
     c->d_part = c->alloc<float>(static_cast<size_t>(H.part_total));
     c->d_objpart = c->alloc<double>(c->T);
@@ -1643,6 +1649,7 @@ admm_status admm_matvec(admm_ctx* ctx, int32_t patient, int32_t scen, const floa
   pa.src = ctx->d_pvec;
   pa.src_per_scen = 0;
   pa.tout = ctx->d_mvec;
+  pa.tout_scen = g;
   pa.objpart = nullptr;
   ctx->pass_launch(PASS_MATVEC, pa, sc.tile_begin, sc.tile_end - sc.tile_begin);
   check(hipMemcpyAsync(out, ctx->d_mvec, sizeof(float) * pt.m, hipMemcpyDeviceToHost, ctx->stream), "D2H");
@@ -1665,42 +1672,72 @@ admm_status dose_stats_check(admm_ctx* ctx, int32_t patient, const double* x, co
       dose_hist_smem_bytes(num_groups, nbins) > 65536)
     return set_err(ctx, ADMM_E_ARG, "need 1 <= num_groups <= 256, nbins >= 1, 12 G + 4 G nbins <= 65536, dmax > 0");
   const Pat& pt = ctx->H.pat[patient];
-  for (int i = 0; i < pt.m; ++i)
-    if (voxel_group[i] >= num_groups) return set_err(ctx, ADMM_E_ARG, "voxel_group entry >= num_groups");
+  uint8_t top = 0;  // the largest group, without a branch per voxel
+  for (int i = 0; i < pt.m; ++i) top = std::max(top, voxel_group[i]);
+  if (top >= num_groups) return set_err(ctx, ADMM_E_ARG, "voxel_group entry >= num_groups");
   for (int j = 0; j < pt.n; ++j)
     if (!std::isfinite(x[j])) return set_err(ctx, ADMM_E_NONFINITE, "x is not finite");
   return ADMM_OK;
 }
 
-// Queue the dose statistics of the plan already in d_pvec (fp32) into the
-// device arrays grp / cnt / key / sum (cnt, key, sum cleared here by fill
-// kernels), and the doses into dose_out when given; then the copies of the
-// counts, sums and max keys (into maxes, as 32-bit keys) back to the host, and
-// wait for them.
-void dose_stats_queue(admm_ctx* ctx, int32_t patient, const uint8_t* d_grp, uint32_t* d_cnt, uint32_t* d_key,
-                      double* d_sum, int G, int nbins, double dmax, uint32_t* counts, double* sums, float* maxes,
-                      float* dose_out) {
+// Device staging of a dose-statistics call, one block: voxel groups, counts,
+// max keys, sums and the plan in fp64, each part rounded up to 256 bytes.
+struct DoseStaging {
+  size_t cnt, key, sum, x, bytes;
+  DoseStaging(const Pat& pt, int num_groups, int nbins) {
+    const size_t N = static_cast<size_t>(pt.num_scen), G = static_cast<size_t>(num_groups);
+    auto up = [](size_t b) { return (b + 255) & ~static_cast<size_t>(255); };
+    cnt = up(static_cast<size_t>(pt.m));
+    key = cnt + up(sizeof(uint32_t) * N * G * static_cast<size_t>(nbins));
+    sum = key + up(sizeof(uint32_t) * N * G);
+    x = sum + up(sizeof(double) * N * G);
+    bytes = x + up(sizeof(double) * static_cast<size_t>(pt.n));
+  }
+};
+
+// The dose statistics of plan x (host) with the staging `base`: counts, sums and
+// keys cleared by a fill kernel, the doses of up to mvec_scen scenarios by one
+// pass over their tiles, their histograms by one launch (scenario by scenario, a
+// pass of 13 workgroups' worth of tiles left most of the chip idle), and the
+// doses copied to dose_out when given; then the copies of the counts, sums and
+// max keys (into maxes, as 32-bit keys) back to the host, and wait for them.
+void dose_stats_queue(admm_ctx* ctx, int32_t patient, const double* x, const uint8_t* voxel_group, void* base, int G,
+                      int nbins, double dmax, uint32_t* counts, double* sums, float* maxes, float* dose_out) {
   const Pat& pt = ctx->H.pat[patient];
   const int N = pt.num_scen, m = pt.m;
   const size_t per = static_cast<size_t>(G) * nbins;
+  const DoseStaging o(pt, G, nbins);
+  unsigned char* sp = static_cast<unsigned char*>(base);
+  uint8_t* d_grp = sp;
+  uint32_t* d_cnt = reinterpret_cast<uint32_t*>(sp + o.cnt);
+  uint32_t* d_key = reinterpret_cast<uint32_t*>(sp + o.key);
+  double* d_sum = reinterpret_cast<double*>(sp + o.sum);
+  double* d_x = reinterpret_cast<double*>(sp + o.x);
+  check(hipMemcpyAsync(d_grp, voxel_group, static_cast<size_t>(m), hipMemcpyHostToDevice, ctx->stream), "H2D");
+  check(hipMemcpyAsync(d_x, x, sizeof(double) * static_cast<size_t>(pt.n), hipMemcpyHostToDevice, ctx->stream), "H2D");
+  launch_f64_to_f32(d_x, ctx->d_pvec + pt.zvec_base, pt.n, ctx->stream);
   static_assert(sizeof(float) == sizeof(uint32_t), "fill by bit pattern");
-  launch_fill_f32(reinterpret_cast<float*>(d_cnt), 0.0f, static_cast<int64_t>(per * N), ctx->stream);
-  launch_fill_f32(reinterpret_cast<float*>(d_key), 0.0f, static_cast<int64_t>(G) * N, ctx->stream);
-  launch_fill_f64(d_sum, 0.0, static_cast<int64_t>(G) * N, ctx->stream);
+  // counts, keys and sums lie together
+  launch_fill_f32(reinterpret_cast<float*>(d_cnt), 0.0f, static_cast<int64_t>((o.x - o.cnt) / sizeof(float)),
+                  ctx->stream);
   const float inv_w = static_cast<float>(nbins / dmax);
-  for (int s = 0; s < N; ++s) {
-    const Scen& sc = ctx->H.scen[pt.scen_begin + s];
-    launch_fill_f32(ctx->d_mvec, 0.0f, m, ctx->stream);
+  for (int s0 = 0; s0 < N; s0 += ctx->mvec_scen) {
+    const int ns = std::min(ctx->mvec_scen, N - s0);
+    const Scen& a = ctx->H.scen[pt.scen_begin + s0];
+    const Scen& b = ctx->H.scen[pt.scen_begin + s0 + ns - 1];
+    launch_fill_f32(ctx->d_mvec, 0.0f, static_cast<int64_t>(m) * ns, ctx->stream);
     PassArgs pa = ctx->pass_args(ctx->mat32);
     pa.src = ctx->d_pvec;
     pa.src_per_scen = 0;
     pa.tout = ctx->d_mvec;
+    pa.tout_scen = pt.scen_begin + s0;
+    pa.tout_stride = m;
     pa.objpart = nullptr;
-    ctx->pass_launch(PASS_MATVEC, pa, sc.tile_begin, sc.tile_end - sc.tile_begin);
-    launch_dose_hist(ctx->d_mvec, d_grp, m, G, nbins, inv_w, d_cnt + per * s, d_sum + static_cast<size_t>(G) * s,
-                     d_key + static_cast<size_t>(G) * s, ctx->stream);
+    ctx->pass_launch(PASS_MATVEC, pa, a.tile_begin, b.tile_end - a.tile_begin);
+    launch_dose_hist(ctx->d_mvec, d_grp, m, ns, G, nbins, inv_w, d_cnt + per * s0, d_sum + static_cast<size_t>(G) * s0,
+                     d_key + static_cast<size_t>(G) * s0, ctx->stream);
     if (dose_out)
-      check(hipMemcpyAsync(dose_out + static_cast<size_t>(s) * m, ctx->d_mvec, sizeof(float) * m,
+      check(hipMemcpyAsync(dose_out + static_cast<size_t>(s0) * m, ctx->d_mvec, sizeof(float) * m * ns,
                            hipMemcpyDeviceToHost, ctx->stream),
             "D2H");
   }
@@ -1732,32 +1769,18 @@ admm_status admm_dose_stats(admm_ctx* ctx, int32_t patient, const double* x, con
   admm_status st = dose_stats_check(ctx, patient, x, voxel_group, num_groups, nbins, dmax, counts, sums, maxes);
   if (st != ADMM_OK) return st;
   GUARD_BEGIN
-  const Pat& pt = ctx->H.pat[patient];
-  const int N = pt.num_scen, m = pt.m, G = num_groups;
-  const size_t per = static_cast<size_t>(G) * nbins;
-  uint8_t* d_grp = nullptr;
-  uint32_t* d_cnt = nullptr;
-  uint32_t* d_key = nullptr;
-  double* d_sum = nullptr;
-  auto release = [&]() {
-    if (d_grp) (void)hipFree(d_grp);
-    if (d_cnt) (void)hipFree(d_cnt);
-    if (d_key) (void)hipFree(d_key);
-    if (d_sum) (void)hipFree(d_sum);
-  };
-  try {
-    check(hipMalloc(reinterpret_cast<void**>(&d_grp), m), "hipMalloc");
-    check(hipMalloc(reinterpret_cast<void**>(&d_cnt), sizeof(uint32_t) * per * N), "hipMalloc");
-    check(hipMalloc(reinterpret_cast<void**>(&d_key), sizeof(uint32_t) * G * N), "hipMalloc");
-    check(hipMalloc(reinterpret_cast<void**>(&d_sum), sizeof(double) * G * N), "hipMalloc");
-    check(hipMemcpyAsync(d_grp, voxel_group, m, hipMemcpyHostToDevice, ctx->stream), "H2D");
-    ctx->upload_pvec(patient, x, ctx->d_pvec);
-    dose_stats_queue(ctx, patient, d_grp, d_cnt, d_key, d_sum, G, nbins, dmax, counts, sums, maxes, dose_out);
-  } catch (...) {
-    release();
-    throw;
+  const DoseStaging o(ctx->H.pat[patient], num_groups, nbins);
+  if (o.bytes > ctx->dose_bytes) {
+    if (ctx->d_dose) {
+      check(hipStreamSynchronize(ctx->stream), "sync");
+      (void)hipFree(ctx->d_dose);
+      ctx->d_dose = nullptr;
+      ctx->dose_bytes = 0;
+    }
+    check(hipMalloc(&ctx->d_dose, o.bytes), "hipMalloc");
+    ctx->dose_bytes = o.bytes;
   }
-  release();
+  dose_stats_queue(ctx, patient, x, voxel_group, ctx->d_dose, num_groups, nbins, dmax, counts, sums, maxes, dose_out);
   return ADMM_OK;
   GUARD_END(ctx)
 }
@@ -1767,32 +1790,16 @@ admm_status admm_dose_stats_noalloc(admm_ctx* ctx, int32_t patient, const double
                                     float* maxes, float* dose_out) {
   admm_status st = dose_stats_check(ctx, patient, x, voxel_group, num_groups, nbins, dmax, counts, sums, maxes);
   if (st != ADMM_OK) return st;
-  const Pat& pt = ctx->H.pat[patient];
-  const size_t N = static_cast<size_t>(pt.num_scen), G = static_cast<size_t>(num_groups);
-  auto up = [](size_t b) { return (b + 255) & ~static_cast<size_t>(255); };
-  const size_t o_cnt = up(static_cast<size_t>(pt.m));
-  const size_t o_key = o_cnt + up(sizeof(uint32_t) * N * G * static_cast<size_t>(nbins));
-  const size_t o_sum = o_key + up(sizeof(uint32_t) * N * G);
-  const size_t o_x = o_sum + up(sizeof(double) * N * G);
-  const size_t need = o_x + up(sizeof(double) * static_cast<size_t>(pt.n));
-  if (need > kNoAllocScratchBytes)
+  const DoseStaging o(ctx->H.pat[patient], num_groups, nbins);
+  if (o.bytes > kNoAllocScratchBytes)
     return set_err(ctx, ADMM_E_ARG,
-                   "admm_dose_stats_noalloc needs " + std::to_string(need) + " bytes of scratch (m + 4 N G nbins + "
+                   "admm_dose_stats_noalloc needs " + std::to_string(o.bytes) + " bytes of scratch (m + 4 N G nbins + "
                    "12 N G + 8 n, each rounded up to 256); the fixed scratch holds " +
                        std::to_string(kNoAllocScratchBytes));
   GUARD_BEGIN
   void* base = nullptr;
   check(noalloc_scratch(&base), "hipGetSymbolAddress");
-  unsigned char* sp = static_cast<unsigned char*>(base);
-  uint8_t* d_grp = sp;
-  uint32_t* d_cnt = reinterpret_cast<uint32_t*>(sp + o_cnt);
-  uint32_t* d_key = reinterpret_cast<uint32_t*>(sp + o_key);
-  double* d_sum = reinterpret_cast<double*>(sp + o_sum);
-  double* d_x = reinterpret_cast<double*>(sp + o_x);
-  check(hipMemcpyAsync(d_grp, voxel_group, static_cast<size_t>(pt.m), hipMemcpyHostToDevice, ctx->stream), "H2D");
-  check(hipMemcpyAsync(d_x, x, sizeof(double) * static_cast<size_t>(pt.n), hipMemcpyHostToDevice, ctx->stream), "H2D");
-  launch_f64_to_f32(d_x, ctx->d_pvec + pt.zvec_base, pt.n, ctx->stream);
-  dose_stats_queue(ctx, patient, d_grp, d_cnt, d_key, d_sum, num_groups, nbins, dmax, counts, sums, maxes, dose_out);
+  dose_stats_queue(ctx, patient, x, voxel_group, base, num_groups, nbins, dmax, counts, sums, maxes, dose_out);
   return ADMM_OK;
   GUARD_END(ctx)
 }

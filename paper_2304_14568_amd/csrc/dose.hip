@@ -2,14 +2,20 @@
 // voxel doses d = A_s x of one scenario, for the dose-volume evaluation of
 // Sec. 3 (dose-volume histograms and D98 / Dmax / D3 / Dmean metrics).
 //
-// One launch per scenario over the m voxel doses (original voxel order).
+// One launch over the m voxel doses (original voxel order) of several
+// scenarios, blockIdx.y the scenario.
 // Each block keeps the histogram of every group in LDS (32-bit counters),
 // plus per-group double sums and order-preserving 32-bit max keys, and merges
-// them into the global arrays with one atomic per nonzero entry.  Counts and
+// them into the global arrays with one atomic per nonzero entry.  Most voxels
+// get no dose, so the lanes of a wave mostly count in one bin: the lanes that
+// share the first active lane's bin add their number once (13 scenarios of
+// 251 000 voxels, 7 groups of 2 048 bins: 24 us in one launch, 151 us in one
+// launch per scenario with an atomic per voxel).  Counts and
 // maxima are exact and order-independent; the sums are double atomics
 // (order-dependent only in the last bits).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <mutex>
 
@@ -30,6 +36,10 @@ __global__ __launch_bounds__(kThreads) void k_dose_hist(const float* __restrict_
                                                         float inv_w, uint32_t* __restrict__ counts,
                                                         double* __restrict__ sums, uint32_t* __restrict__ maxkey) {
   extern __shared__ __align__(8) unsigned char smem[];
+  dose += static_cast<int64_t>(blockIdx.y) * m;
+  counts += static_cast<int64_t>(blockIdx.y) * G * nbins;
+  sums += static_cast<int64_t>(blockIdx.y) * G;
+  maxkey += static_cast<int64_t>(blockIdx.y) * G;
   double* ssum = reinterpret_cast<double*>(smem);             // G
   uint32_t* smax = reinterpret_cast<uint32_t*>(ssum + G);     // G
   uint32_t* hist = smax + G;                                  // G * nbins
@@ -51,7 +61,13 @@ __global__ __launch_bounds__(kThreads) void k_dose_hist(const float* __restrict_
     int b = static_cast<int>(d * inv_w);
     b = b < 0 ? 0 : (b >= nbins ? nbins - 1 : b);
     if (!(d >= 0.0f)) b = 0;  // negative doses (and NaN) fall in the first bin
-    atomicAdd(&hist[g * nbins + b], 1u);
+    const int at = g * nbins + b;
+    const int at0 = __builtin_amdgcn_readfirstlane(at);
+    const uint64_t same = __ballot(at == at0);
+    if (at != at0)
+      atomicAdd(&hist[at], 1u);
+    else if ((threadIdx.x & 63) == __ffsll(static_cast<unsigned long long>(same)) - 1)
+      atomicAdd(&hist[at0], static_cast<uint32_t>(__popcll(same)));
     if (g != cur) {
       if (cur >= 0) {
         atomicAdd(&ssum[cur], acc);
@@ -121,11 +137,16 @@ void launch_f64_to_f32(const double* in, float* out, int n, hipStream_t st) {
   hipLaunchKernelGGL(k_f64_to_f32, dim3(nb), dim3(kThreads), 0, st, in, out, n);
 }
 
-void launch_dose_hist(const float* dose, const uint8_t* grp, int m, int G, int nbins, float inv_w, uint32_t* counts,
-                      double* sums, uint32_t* maxkey, hipStream_t st) {
+void launch_dose_hist(const float* dose, const uint8_t* grp, int m, int nscen, int G, int nbins, float inv_w,
+                      uint32_t* counts, double* sums, uint32_t* maxkey, hipStream_t st) {
+  // at least eight voxels a thread, and no more blocks than the chip holds at
+  // once (LDS; at most eight per CU): a block clears and merges a histogram of up
+  // to 64 KB, whatever its voxels
   int nb = (m + kThreads * 8 - 1) / (kThreads * 8);
-  nb = nb < 1 ? 1 : (nb > 1024 ? 1024 : nb);
-  hipLaunchKernelGGL(k_dose_hist, dim3(nb), dim3(kThreads), dose_hist_smem_bytes(G, nbins), st, dose, grp, m, G,
+  const int per_cu = 163840 / dose_hist_smem_bytes(G, nbins);
+  const int most = std::max(8, 256 * std::min(per_cu, 8) / nscen);
+  nb = nb < 1 ? 1 : (nb > most ? most : nb);
+  hipLaunchKernelGGL(k_dose_hist, dim3(nb, nscen), dim3(kThreads), dose_hist_smem_bytes(G, nbins), st, dose, grp, m, G,
                      nbins, inv_w, counts, sums, maxkey);
 }
 

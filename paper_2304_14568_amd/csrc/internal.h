@@ -153,7 +153,9 @@ struct PassArgs {
   const float* tin;        // RMATVEC input (m-vector of the scenario)
   const float* tmax;       // RMATVEC: kAbsMaxBlocks partial maxima of |tin| (launch_absmax); nullptr: each
                            // tile takes the maximum over its own rows first
-  float* tout;             // MATVEC output (m-vector of the scenario)
+  float* tout;             // MATVEC output: m-vector of scenario s at tout + (s - tout_scen) * tout_stride
+  int64_t tout_stride;
+  int32_t tout_scen;
   int32_t nmax;
   int32_t acc;             // LDS column accumulators: ACC_F32, ACC_F64 or ACC_FIX64
   int32_t threads;         // workgroup size of the pass: 256 or 512
@@ -323,8 +325,8 @@ void launch_xzres(const FactorArgs& f, const VecArgs& a, int npblk, hipStream_t 
 void launch_dense_x(const FactorArgs& f, const VecArgs& a, const double* c, int njobs, hipStream_t st,
                     hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 void launch_dense_tail_dual(const FactorArgs& f, const VecArgs& a, int nfobj, int nblk, hipStream_t st);
-void launch_dose_hist(const float* dose, const uint8_t* grp, int m, int G, int nbins, float inv_w, uint32_t* counts,
-                      double* sums, uint32_t* maxkey, hipStream_t st);
+void launch_dose_hist(const float* dose, const uint8_t* grp, int m, int nscen, int G, int nbins, float inv_w,
+                      uint32_t* counts, double* sums, uint32_t* maxkey, hipStream_t st);
 // Allocation-free dose statistics: device address of the fixed scratch array
 // (dose.hip) on the current device, looked up once per device; and a
 // double-to-float copy kernel for the plan it receives.

@@ -159,6 +159,7 @@ __device__ __forceinline__ void pass_rows(const PassArgs& a, const Tile& t, cons
   };
   const int64_t rb = sc.row_base;
   const int rend = t.row_end;
+  float* tout = MODE == PASS_MATVEC ? a.tout + (t.scen - a.tout_scen) * a.tout_stride : nullptr;
   float* __restrict__ qf = static_cast<float*>(qacc);
   double* __restrict__ qd = static_cast<double*>(qacc);
   unsigned long long* __restrict__ qi = static_cast<unsigned long long*>(qacc);
@@ -257,7 +258,7 @@ __device__ __forceinline__ void pass_rows(const PassArgs& a, const Tile& t, cons
       }
       dot = group_allsum<L>(dot);
       if constexpr (MODE == PASS_MATVEC) {
-        if (lane == 0) a.tout[a.mat.rorig[rb + r]] = static_cast<float>(dot);
+        if (lane == 0) tout[a.mat.rorig[rb + r]] = static_cast<float>(dot);
       } else if constexpr (kDot64) {
         const double res = dot - static_cast<double>(aux);
         const double wgt = static_cast<double>(rw);
@@ -333,6 +334,7 @@ __device__ __forceinline__ void pass_slices(const PassArgs& a, const Tile& t, co
   const uint32_t* __restrict__ soff = a.mat.soff + t.slice_begin;
   const int64_t rb = sc.row_base;
   const int nsl = (t.row_end - t.row_begin + G - 1) / G;
+  float* tout = MODE == PASS_MATVEC ? a.tout + (t.scen - a.tout_scen) * a.tout_stride : nullptr;
   float* __restrict__ qf = static_cast<float*>(qacc);
   double* __restrict__ qd = static_cast<double*>(qacc);
   unsigned long long* __restrict__ qi = static_cast<unsigned long long*>(qacc);
@@ -405,7 +407,7 @@ __device__ __forceinline__ void pass_slices(const PassArgs& a, const Tile& t, co
       }
       dot = group_allsum<L>(dot);
       if constexpr (MODE == PASS_MATVEC) {
-        if (real && (lane % L) == 0) a.tout[a.mat.rorig[rb + r]] = static_cast<float>(dot);
+        if (real && (lane % L) == 0) tout[a.mat.rorig[rb + r]] = static_cast<float>(dot);
       } else if constexpr (kDot64) {
         const double res = real ? dot - static_cast<double>(aux) : 0.0;
         const double wgt = static_cast<double>(rw);

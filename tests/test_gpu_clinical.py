@@ -46,6 +46,32 @@ def test_dose_stats_parity(plan):
                 assert maxes[s, g] == -np.inf and counts[s, g].sum() == 0
 
 
+@pytest.mark.parametrize("num_scen,nbins", [(1, 1), (16, 700), (17, 64), (35, 3)])
+def test_dose_stats_over_scenario_groups(num_scen, nbins):
+    """Up to 16 scenarios share a pass and a histogram launch: one, a whole
+    group, and one and three more than whole groups; 231 voxels (one block per
+    scenario, a ragged last wave) and doses beyond dmax."""
+    import paper_2304_14568_amd as A
+    P = synth.make_tiny(3, grid=(7, 11, 3), num_scen=num_scen,
+                        range_scales=tuple(np.linspace(0.95, 1.05, num_scen)))
+    rng = np.random.default_rng(num_scen)
+    x = rng.uniform(0.0, 1.0, P.n)
+    G, dmax = 3, 0.5
+    with A.Solver(P) as S:
+        counts, sums, maxes, dose = S.dose_stats(x, P.struct_id, G, nbins, dmax, want_dose=True)
+        one = [S.matvec(x.astype(np.float32), s) for s in range(num_scen)]
+    inv_w = np.float32(nbins / dmax)
+    for s in range(num_scen):
+        assert np.array_equal(dose[s], one[s])
+        b = np.minimum((dose[s] * inv_w).astype(np.int64), nbins - 1)
+        for g in range(G):
+            sel = P.struct_id == g
+            assert np.array_equal(counts[s, g], np.bincount(b[sel], minlength=nbins)[:nbins])
+            assert maxes[s, g] == (dose[s][sel].max() if sel.any() else -np.inf)
+            ref = float(np.sum(dose[s][sel].astype(np.float64)))
+            assert abs(sums[s, g] - ref) <= 1e-12 * max(1.0, abs(ref))  # fp64 sums in any order
+
+
 def test_clinical_metrics_match_definitions(plan):
     import paper_2304_14568_amd as A
     from paper_2304_14568_amd import clinical
