@@ -132,7 +132,7 @@ typedef struct {
                           2 64-bit fixed point (integer atomics: exact, order-independent sums);
                           -1 = chosen by the set-up autotuner among 1 and 2 */
   int32_t tile_nnz;    /* target nonzeros per workgroup tile; 0 = automatic, per patient
-                          (about 2048 tiles each, 8192 .. 4M nonzeros) */
+                          (512 to 2048 tiles each, 8192 .. 4M nonzeros) */
   int32_t pass_threads; /* fused-pass workgroup size 256, 512 or 1024 (1024: chunk-row layout
                           only); 0 = chosen per patient by the set-up autotuner */
   int32_t pass_unroll;  /* 1: row data loaded when the row starts; 2: next row's data in flight during the

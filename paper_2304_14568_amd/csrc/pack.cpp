@@ -240,16 +240,25 @@ admm_status pack_problems(const admm_problem* probs, int num_patients, const adm
   int64_t nnz_all = 0;
   for (int p = 0; p < num_patients; ++p)
     for (int s = 0; s < probs[p].num_scen; ++s) nnz_all += probs[p].A[s].nnz;
-  // about 2048 tiles (8 workgroups per CU) for every patient: the passes are
-  // launched per patient, so each patient's tiles are sized for its own
+  // at most about 2048 tiles (8 workgroups per CU) for every patient: the passes
+  // are launched per patient, so each patient's tiles are sized for its own
   // nonzeros (a small patient in a batch must not get a few huge tiles, nor a
-  // large one thousands of tiny ones)
+  // large one thousands of tiny ones).  Every tile of a scatter pass also clears,
+  // writes and has reduced a vector of n column sums (8 n bytes of traffic
+  // against 6 per nonzero), so a tile takes at least 10 n nonzeros, as long as
+  // that leaves every workgroup slot (12 n bytes of LDS each, four of 512 threads
+  // per CU at most) its share and 256 more.  A CG iteration of one scenario of
+  // 8 501 spots 772 -> 503 us (2 048 -> 512 tiles), three of 5 500 spots 770 ->
+  // 600 us, three of 2 981 spots 439 -> 389 us; 13 of 2 981 spots keep 2 048.
   (void)nnz_all;
   std::vector<int64_t> tile_chunks_of(num_patients);
   for (int p = 0; p < num_patients; ++p) {
     int64_t np = 0;
     for (int s = 0; s < probs[p].num_scen; ++s) np += probs[p].A[s].nnz;
-    int64_t tile_nnz = o.tile_nnz > 0 ? o.tile_nnz : np / (256 * 8);
+    const int64_t n = probs[p].n;
+    const int64_t slots = std::max<int64_t>(1, std::min<int64_t>(4, 163840 / (12 * n)));
+    const int64_t tiles = std::min<int64_t>(2048, std::max<int64_t>(np / (10 * n), 256 * (slots + 1)));
+    int64_t tile_nnz = o.tile_nnz > 0 ? o.tile_nnz : np / tiles;
     tile_nnz = std::max<int64_t>(8192, std::min<int64_t>(tile_nnz, 1 << 22));
     tile_chunks_of[p] = std::max<int64_t>(1, tile_nnz / 4);
   }
