@@ -97,7 +97,9 @@ struct admm_ctx {
   IterRecord* d_trace = nullptr;
   int trace_cap = 0;
   PatState* h_ps = nullptr;  // pinned
-  double* h_scr = nullptr;   // pinned scratch
+  double* h_scr = nullptr;   // pinned: 64 doubles of scratch, then
+  double* h_in = nullptr;    // a plan (nmax doubles) on its way to the device
+  float* h_out = nullptr;    // a gradient (nmax floats) written by the device
   hipGraphExec_t g_solve = nullptr, g_iter = nullptr;
   hipGraph_t gr_solve = nullptr, gr_iter = nullptr;
   int acc = ACC_F64;
@@ -794,29 +796,36 @@ struct admm_ctx {
     check(hipStreamSynchronize(stream), "sync");
   }
 
+  // x (n doubles) to dst of patient p in fp32: by a kernel that reads the pinned
+  // copy, which stays as it is until the caller's next wait for the stream.
   void upload_pvec(int p, const double* x, float* dst) {
     const Pat& pt = H.pat[p];
-    std::vector<float> v(pt.n);
-    StreamDrain drain{stream};
-    for (int j = 0; j < pt.n; ++j) v[j] = static_cast<float>(x[j]);
-    check(hipMemcpyAsync(dst + pt.zvec_base, v.data(), sizeof(float) * pt.n, hipMemcpyHostToDevice, stream), "H2D");
-    check(hipStreamSynchronize(stream), "sync");
+    std::memcpy(h_in, x, sizeof(double) * static_cast<size_t>(pt.n));
+    launch_f64_to_f32(h_in, dst + pt.zvec_base, pt.n, stream);
   }
 
-  // f(x) and (optionally) grad f(x) for patient p, x already in d_pvec at zvec_base
+  // f(x) and (optionally) grad f(x) for patient p, x already in d_pvec at
+  // zvec_base; the gradient stays on the device and is also left in h_out.  The
+  // kernels write f and h_out to pinned memory themselves: one wait, no copies.
   double objective_dev(int p, float* grad_dev) {
     if (!grad_dev) ensure_forward_tuned();
     const Pat& pt = H.pat[p];
+    const int nt = pt.tile_end - pt.tile_begin;
     PassArgs pa = pass_args(mat32);
     pa.src = d_pvec;
     pa.src_per_scen = 0;
-    pass_launch(grad_dev ? PASS_GRAD : PASS_OBJ, pa, pt.tile_begin, pt.tile_end - pt.tile_begin);
+    pass_launch(grad_dev ? PASS_GRAD : PASS_OBJ, pa, pt.tile_begin, nt);
     if (grad_dev)
-      launch_gsum(d_scen, d_pat, d_pblk, d_tiles, d_part, pt.blk_begin, pt.nblk, 2.0f, grad_dev, stream);
-    launch_objsum(d_tiles, d_objpart, pt.tile_begin, pt.tile_end - pt.tile_begin, d_scratch, stream);
-    check(hipMemcpyAsync(h_scr, d_scratch, sizeof(double), hipMemcpyDeviceToHost, stream), "D2H");
+      launch_gsum(patient_parts(pt), nt, pt.n, 2.0f, grad_dev, h_out, d_objpart + pt.tile_begin, h_scr, stream);
+    else
+      launch_objsum(d_objpart, pt.tile_begin, nt, h_scr, stream);
+    check(hipGetLastError(), "launch");
     check(hipStreamSynchronize(stream), "sync");
     return h_scr[0] + pt.fzero;
+  }
+  // the column sums of a patient's tiles, one n-vector after the other
+  const float* patient_parts(const Pat& pt) const {
+    return d_part + (pt.tile_end > pt.tile_begin ? H.tiles[static_cast<size_t>(pt.tile_begin)].part_off : 0);
   }
 };
 
@@ -1295,8 +1304,11 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
     c->d_trace = c->alloc<IterRecord>(static_cast<size_t>(c->P) * c->trace_cap);
     check(hipHostMalloc(reinterpret_cast<void**>(&c->h_ps), sizeof(PatState) * c->P, hipHostMallocDefault),
           "hipHostMalloc");
-    check(hipHostMalloc(reinterpret_cast<void**>(&c->h_scr), sizeof(double) * 64, hipHostMallocDefault),
+    check(hipHostMalloc(reinterpret_cast<void**>(&c->h_scr), sizeof(double) * (64 + 2 * static_cast<size_t>(H.nmax)),
+                        hipHostMallocDefault),
           "hipHostMalloc");
+    c->h_in = c->h_scr + 64;
+    c->h_out = reinterpret_cast<float*>(c->h_in + H.nmax);
     launch_fill_f32(c->d_v, 0.0f, V, c->stream);
     launch_fill_f32(c->d_q, 0.0f, V, c->stream);
     launch_fill_f32(c->d_r, 0.0f, V, c->stream);
@@ -1600,9 +1612,7 @@ admm_status admm_gradient(admm_ctx* ctx, int32_t patient, const double* x, doubl
   const Pat& pt = ctx->H.pat[patient];
   ctx->upload_pvec(patient, x, ctx->d_pvec);
   const double f = ctx->objective_dev(patient, ctx->d_pvec2 + pt.zvec_base);
-  std::vector<float> g(pt.n);
-  check(hipMemcpy(g.data(), ctx->d_pvec2 + pt.zvec_base, sizeof(float) * pt.n, hipMemcpyDeviceToHost), "D2H");
-  for (int j = 0; j < pt.n; ++j) grad_out[j] = g[j];
+  for (int j = 0; j < pt.n; ++j) grad_out[j] = ctx->h_out[j];
   if (f_out) *f_out = f;
   return ADMM_OK;
   GUARD_END(ctx)
@@ -2005,7 +2015,7 @@ admm_status pgd_solve_impl(admm_ctx* ctx, const pgd_options* popts, int32_t pati
       pa.src_per_scen = 0;
       pa.objpart = nullptr;
       ctx->pass_launch(PASS_CG, pa, pt.tile_begin, pt.tile_end - pt.tile_begin);
-      launch_gsum(ctx->d_scen, ctx->d_pat, ctx->d_pblk, ctx->d_tiles, ctx->d_part, pt.blk_begin, pt.nblk, 2.0f, g, s);
+      launch_gsum(ctx->patient_parts(pt), pt.tile_end - pt.tile_begin, n, 2.0f, g, nullptr, nullptr, nullptr, s);
       check(hipMemcpyAsync(v.data(), g, sizeof(float) * n, hipMemcpyDeviceToHost, s), "D2H");
       check(hipStreamSynchronize(s), "sync");
       double nrm = 0.0;
@@ -2034,14 +2044,13 @@ admm_status pgd_solve_impl(admm_ctx* ctx, const pgd_options* popts, int32_t pati
     double ft = 0.0;
     for (int trial = 0; trial < o.max_trials; ++trial) {
       launch_pgd_trial(x, g, lb, ub, static_cast<float>(t), xt, n, ctx->d_scratch + 8, s);
-      launch_dot_sum(ctx->d_scratch + 8, nb, ctx->d_scratch + 1, s);
+      launch_dot_sum(ctx->d_scratch + 8, nb, ctx->h_scr + 1, s);
       PassArgs pa = ctx->pass_args(ctx->mat32);
       pa.src = ctx->d_pvec3;
       pa.src_per_scen = 0;
       pa.part = nullptr;  // objective only
       ctx->pass_launch(PASS_OBJ, pa, pt.tile_begin, pt.tile_end - pt.tile_begin);
-      launch_objsum(ctx->d_tiles, ctx->d_objpart, pt.tile_begin, pt.tile_end - pt.tile_begin, ctx->d_scratch, s);
-      check(hipMemcpyAsync(ctx->h_scr, ctx->d_scratch, 2 * sizeof(double), hipMemcpyDeviceToHost, s), "D2H");
+      launch_objsum(ctx->d_objpart, pt.tile_begin, pt.tile_end - pt.tile_begin, ctx->h_scr, s);
       check(hipStreamSynchronize(s), "sync");
       ft = ctx->h_scr[0] + pt.fzero;
       const double gd = ctx->h_scr[1];

@@ -277,10 +277,9 @@ void launch_cg_update(const VecArgs& a, int nblk, hipStream_t st);
 void launch_cg_dir(const VecArgs& a, int nblk, hipStream_t st);
 void launch_zres(const VecArgs& a, int npblk, hipStream_t st);
 void launch_body_scalars(const VecArgs& a, hipStream_t st);
-void launch_gsum(const Scen* scen, const Pat* pat, const Blk* pblk, const Tile* tiles, const float* part,
-                 int patient_blk_begin, int nblk, float scale, float* out, hipStream_t st);
-void launch_objsum(const Tile* tiles, const double* objpart, int tile_begin, int tile_count, double* out,
-                   hipStream_t st);
+void launch_gsum(const float* part, int ntiles, int n, float scale, float* out, float* hout, const double* objpart,
+                 double* objout, hipStream_t st);
+void launch_objsum(const double* objpart, int tile_begin, int tile_count, double* out, hipStream_t st);
 void launch_pgd_trial(const float* x, const float* g, const float* lb, const float* ub, float t, float* xt,
                       int n, double* dotpart, hipStream_t st);
 void launch_dot_sum(const double* part, int count, double* out, hipStream_t st);

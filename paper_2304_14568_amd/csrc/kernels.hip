@@ -40,13 +40,13 @@ void launch_pass(int mode, const PassArgs& a, int tile_begin, int tile_count, hi
 // ---------------------------------------------------------------------------
 
 // Sum of the partial column sums of tiles [0, ntiles) (tile t's partials at
-// part[t * n + j]) for column j: the NW waves of the block take every NW-th
-// tile, four loads in flight each, then wave 0 adds the NW results pairwise
-// in a fixed order.  Returns the total in wave 0 (lane = column offset).
-template <int NW>
+// part[t * n + j]) for column j: the kRedWaves waves of the block take every
+// kRedWaves-th tile, four loads in flight each, then wave 0 adds the results
+// pairwise in a fixed order.  Returns the total in wave 0 (lane = column offset).
+constexpr int kRedWaves = 16;
 __device__ __forceinline__ double tile_column_sum(const float* __restrict__ part, int ntiles, int n, int j,
                                                   double (*red)[64]) {
-  static_assert(NW == 4 || NW == 16, "pairwise tree over 4 or 16 waves");
+  constexpr int NW = kRedWaves;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
   if (j < n) {
@@ -62,11 +62,8 @@ __device__ __forceinline__ double tile_column_sum(const float* __restrict__ part
   red[w][lane] = (s0 + s1) + (s2 + s3);
   __syncthreads();
   auto q4 = [&](int b) { return (red[b][lane] + red[b + 1][lane]) + (red[b + 2][lane] + red[b + 3][lane]); };
-  if constexpr (NW == 4) return q4(0);
-  else return (q4(0) + q4(4)) + (q4(8) + q4(12));
+  return (q4(0) + q4(4)) + (q4(8) + q4(12));
 }
-
-constexpr int kRedWaves = 16;  // waves per column block of k_reduce
 
 // One workgroup of kRedWaves waves per scenario column block; every address
 // comes from the block's job entry, and the partial sums are requested
@@ -82,7 +79,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduce(VecArgs a, int blk_be
     if (mode == RED_CG) skip = skip || !a.act[cj.scen * kRing + a.step];
   }
   const int j = cj.col0 + static_cast<int>(threadIdx.x & 63);
-  const double s = tile_column_sum<kRedWaves>(a.part + cj.part_off, cj.ntiles, cj.n, j, red);
+  const double s = tile_column_sum(a.part + cj.part_off, cj.ntiles, cj.n, j, red);
   if (skip || threadIdx.x >= 64) return;
   double loc[3] = {0.0, 0.0, 0.0};
   if (j < cj.n) {
@@ -346,21 +343,57 @@ void launch_body_scalars(const VecArgs& a, hipStream_t st) {
 // small helpers: cross-scenario gradient sum, objective sum, PGD trial step
 // ---------------------------------------------------------------------------
 
-__global__ __launch_bounds__(kThreads) void k_gsum(const Scen* scen, const Pat* pat, const Blk* pblk,
-                                                   const Tile* tiles, const float* part, int blk_begin,
-                                                   float scale, float* out) {
-  __shared__ double red[4][64];
-  const Blk bk = pblk[blk_begin + blockIdx.x];
-  const Pat pt = pat[bk.owner];
-  const int j = bk.col0 + static_cast<int>(threadIdx.x & 63);
-  const double s = tile_column_sum<4>(part + tiles[pt.tile_begin].part_off, pt.tile_end - pt.tile_begin, pt.n, j, red);
-  if (threadIdx.x < 64 && j < pt.n) out[j] = static_cast<float>(scale * s);
+// out[j] = scale * sum over a patient's tiles of part[t * n + j] (and hout[j],
+// host memory, when given), 16 columns per workgroup: 64 groups of 16 lanes take
+// every 64th tile, eight loads in flight each, then fixed-order sums over the
+// groups.  One more workgroup adds the tiles' objective partials when given.
+// With 64 columns and four waves per workgroup the 12 workgroups of 707 spots
+// read 2 048 tiles each in 37.5 us; GSUM_NOTE.
+constexpr int kGsumCols = 16, kGsumWaves = 16;
+__global__ __launch_bounds__(64 * kGsumWaves) void k_gsum(const float* __restrict__ part, int ntiles, int n,
+                                                          float scale, float* __restrict__ out,
+                                                          float* __restrict__ hout, const double* __restrict__ objpart,
+                                                          double* __restrict__ objout) {
+  __shared__ double red[kGsumWaves][kGsumCols];
+  const int tid = threadIdx.x, w = tid >> 6, c = tid & 15, grp = tid >> 4;
+  constexpr int kGroups = 4 * kGsumWaves;
+  double s = 0.0;
+  const bool obj = static_cast<int>(blockIdx.x) * kGsumCols >= n;  // the workgroup past the columns
+  const int j = static_cast<int>(blockIdx.x) * kGsumCols + c;
+  if (obj) {
+    for (int i = tid; i < ntiles; i += 64 * kGsumWaves) s += objpart[i];
+  } else if (j < n) {
+    int t = grp;
+    for (; t + 7 * kGroups < ntiles; t += 8 * kGroups) {
+      float q[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) q[u] = part[static_cast<int64_t>(t + u * kGroups) * n + j];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += static_cast<double>(q[u]);
+    }
+    for (; t < ntiles; t += kGroups) s += static_cast<double>(part[static_cast<int64_t>(t) * n + j]);
+  }
+  if (obj) s = group_allsum<16>(s);
+  s = swap_sum<32>(swap_sum<16>(s));
+  if ((tid & 63) < kGsumCols) red[w][c] = s;
+  __syncthreads();
+  if (tid >= kGsumCols) return;
+  auto q4 = [&](int b) { return (red[b][c] + red[b + 1][c]) + (red[b + 2][c] + red[b + 3][c]); };
+  s = (q4(0) + q4(4)) + (q4(8) + q4(12));
+  if (obj) {
+    if (tid == 0) *objout = s;
+  } else if (j < n) {
+    const float g = static_cast<float>(scale * s);
+    out[j] = g;
+    if (hout != nullptr) hout[j] = g;
+  }
 }
 
-void launch_gsum(const Scen* scen, const Pat* pat, const Blk* pblk, const Tile* tiles, const float* part,
-                 int patient_blk_begin, int nblk, float scale, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_gsum, dim3(nblk), dim3(kThreads), 0, st, scen, pat, pblk, tiles, part, patient_blk_begin,
-                     scale, out);
+void launch_gsum(const float* part, int ntiles, int n, float scale, float* out, float* hout, const double* objpart,
+                 double* objout, hipStream_t st) {
+  const int nb = (n + kGsumCols - 1) / kGsumCols + (objpart != nullptr ? 1 : 0);
+  hipLaunchKernelGGL(k_gsum, dim3(nb), dim3(64 * kGsumWaves), 0, st, part, ntiles, n, scale, out, hout, objpart,
+                     objout);
 }
 
 __global__ __launch_bounds__(kThreads) void k_objsum(const double* objpart, int tile_begin, int count, double* out) {
@@ -369,7 +402,7 @@ __global__ __launch_bounds__(kThreads) void k_objsum(const double* objpart, int 
   if (threadIdx.x == 0) *out = f;
 }
 
-void launch_objsum(const Tile*, const double* objpart, int tile_begin, int tile_count, double* out, hipStream_t st) {
+void launch_objsum(const double* objpart, int tile_begin, int tile_count, double* out, hipStream_t st) {
   hipLaunchKernelGGL(k_objsum, dim3(1), dim3(kThreads), 0, st, objpart, tile_begin, tile_count, out);
 }
 

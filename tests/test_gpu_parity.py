@@ -269,3 +269,21 @@ def test_layouts_agree_bit_for_bit(small):
             out[fmt] = res
     for a, b in zip(out["csr"], out["sell"]):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("spots", [(1, 1), (3, 5), (4, 4), (1, 17), (5, 13)])
+def test_gradient_and_objective_at_column_group_edges(spots):
+    """The patient's column sums go 16 columns per workgroup, with one more for
+    the objective: 1, 15, 16, 17 and 65 spots, in repeated calls."""
+    P = synth.make_tiny(9, spots=spots)
+    W = wls.from_problem(P)
+    rng = np.random.default_rng(sum(spots))
+    with _solver(P) as S:
+        for _ in range(3):
+            x = rng.uniform(0.0, 1.0, P.n).astype(np.float32).astype(np.float64)
+            g, f = S.gradient(x)
+            fr, gr = wls.objective(W, x), wls.gradient(W, x)
+            # fp32 values of t_i and of the tiles' column sums, fp64 sums
+            assert abs(f - fr) <= 1e-7 * fr
+            assert np.all(np.abs(g - gr) <= 1e-6 * np.abs(gr).max())
+            assert abs(S.objective(x) - fr) <= 1e-7 * fr
