@@ -126,8 +126,11 @@ typedef struct {
   int32_t precision;   /* ADMM_PREC_*: value type of A_s inside CG; the objective and the
                           per-iteration residual always use the fp32 matrix; default FP32 */
   int32_t precond;     /* 1: Jacobi-preconditioned CG; default 0 */
-  int32_t use_graph;   /* 1: capture one iteration in a HIP graph and replay it (default) */
-  int32_t check_every; /* host reads the stop flags every k iterations; default 1 */
+  int32_t use_graph;   /* 1 (default): capture one iteration of the CG x-update (some 35 launches) in a
+                          HIP graph and replay it; the dense iteration's three or four launches
+                          are cheaper queued directly (12 against 18 us of host time) */
+  int32_t check_every; /* host reads the stop flags every k iterations; default 1 (it queues a few
+                          iterations ahead of the flags; the device skips those behind a stop) */
   int32_t lds_acc;     /* column accumulators of the fused pass in LDS: 0 fp32 atomics, 1 fp64 atomics,
                           2 64-bit fixed point (integer atomics: exact, order-independent sums);
                           -1 = chosen by the set-up autotuner among 1 and 2 */

@@ -97,6 +97,9 @@ struct admm_ctx {
   IterRecord* d_trace = nullptr;
   int trace_cap = 0;
   PatState* h_ps = nullptr;  // pinned
+  uint32_t* d_heads = nullptr;            // per patient: heads run so far
+  volatile uint32_t* h_progress = nullptr;  // pinned, written by every head: heads << 1 | stopped
+  uint32_t heads_queued = 0;              // heads queued so far
   double* h_scr = nullptr;   // pinned: 64 doubles of scratch, then
   double* h_in = nullptr;    // a plan (nmax doubles) on its way to the device
   float* h_out = nullptr;    // a gradient (nmax floats) written by the device
@@ -218,6 +221,7 @@ struct admm_ctx {
     for (void* p : allocs) (void)hipFree(p);
     if (d_dose) (void)hipFree(d_dose);
     if (h_ps) (void)hipHostFree(h_ps);
+    if (h_progress) (void)hipHostFree(const_cast<uint32_t*>(h_progress));
     if (h_scr) (void)hipHostFree(h_scr);
     if (own_stream && stream) (void)hipStreamDestroy(stream);
   }
@@ -311,6 +315,8 @@ struct admm_ctx {
     a.bpart = d_bpart;
     a.bpartp = d_bpartp;
     a.trace = d_trace;
+    a.heads = d_heads;
+    a.progress = const_cast<uint32_t*>(h_progress);
     a.prm.eps_abs = opts.eps_abs;
     a.prm.eps_rel = opts.eps_rel;
     a.prm.obj_rel_tol = opts.obj_rel_tol;
@@ -522,7 +528,7 @@ struct admm_ctx {
     if (timing) throw HipError{hipErrorInvalidValue, "graph capture refused while timing events are enabled"};
     check(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
     try {
-      if (!dense) launch_head(stop_enabled, 1);
+      launch_head(stop_enabled, 1);
       launch_body(stop_enabled, false);
     } catch (...) {
       hipGraph_t tmp = nullptr;
@@ -536,8 +542,10 @@ struct admm_ctx {
 
   void one_iteration(int stop_enabled) {
     // timed runs launch directly: events recorded around each pass launch must
-    // be readable after every iteration, which graph-captured events are not
-    if (opts.use_graph && !timing) {
+    // be readable after every iteration, which graph-captured events are not.
+    // So does the dense iteration: its three launches cost the host 12 us, the
+    // replay of a graph of them 18 us
+    if (opts.use_graph && !timing && !dense) {
       hipGraphExec_t& ge = stop_enabled ? g_solve : g_iter;
       hipGraph_t& gr = stop_enabled ? gr_solve : gr_iter;
       if (!ge) capture(stop_enabled, &gr, &ge);
@@ -546,6 +554,31 @@ struct admm_ctx {
       if (!dense) launch_head(stop_enabled, 1);
       launch_body(stop_enabled, timing);
     }
+    ++heads_queued;  // one per iteration in every order
+  }
+
+  // Waits until every patient has had its first `heads` heads (of those queued
+  // since the context's set-up) and returns whether all have stopped.  The heads
+  // report to pinned memory while the device goes on with what is queued behind
+  // them; where the stream has run dry without them (it failed), the state is
+  // read instead, which reports the failure.
+  bool all_stopped_by(uint32_t heads) {
+    uint32_t spins = 0;
+    bool all = true;
+    for (int p = 0; p < P; ++p) {
+      uint32_t w = h_progress[p];
+      while ((((w >> 1) - heads) & 0x7fffffffu) >= 0x40000000u) {
+        if ((++spins & 0xfffu) == 0 && hipStreamQuery(stream) != hipErrorNotReady) {
+          read_state();
+          bool st = true;
+          for (int q = 0; q < P; ++q) st = st && (h_ps[q].stopped != 0);
+          return st;
+        }
+        w = h_progress[p];
+      }
+      all = all && (w & 1u);
+    }
+    return all;
   }
 
   void accumulate_pass_times() {
@@ -574,32 +607,43 @@ struct admm_ctx {
   // update, as left by a checkpoint); in the four-launch order each iteration
   // then ends complete (stopping test, dual update, next right-hand sides), in
   // the three-launch order the stopping test of each iteration runs in the
-  // next one's first launch, and a final one follows the loop.  There the host
-  // sees a stop one iteration late; the iteration between is skipped on the
-  // device.
+  // next one's first launch, and a final one follows the loop.  The host sees a
+  // stop some iterations late; those queued behind it are skipped on the device.
   void run(int k, int stop_enabled) {
     if (timing) {
       check(hipEventRecord(ev_a, stream), "hipEventRecord");
       pass_ms_sum = 0.0;
       pass_count = 0;
     }
-    if (dense) launch_head(stop_enabled, 0);
+    if (dense) {
+      launch_head(stop_enabled, 0);
+      ++heads_queued;
+    }
     const int every = std::max(1, opts.check_every);
+    // iterations queued beyond the one whose head the host waits for: enough to
+    // keep the device busy while the report of a stop travels and the host
+    // queues, few enough that the skipped iterations behind a stop cost little
+    // (a large patient's still load its tiles: 45 us of 2 981 spots x 13).
+    // Waiting for each iteration cost 10 to 15 us of idle device each
+    const int ahead = dense && n_xjobs <= 4096 ? 4 : 2;
+    const uint32_t base = heads_queued;
     for (int it = 0; it < k; ++it) {
       one_iteration(stop_enabled);
-      const bool last = (it + 1 == k);
       // without the stopping test the device skips stopped patients by itself:
       // the host only waits when it needs the flags or the pass timings
-      if (timing || last || (stop_enabled && (it + 1) % every == 0)) {
+      if (timing) {
         read_state();
         accumulate_pass_times();
         bool all = true;
         for (int p = 0; p < P; ++p) all = all && (h_ps[p].stopped != 0);
         if (all) break;
+      } else if (stop_enabled && it >= ahead && (it + 1) % every == 0) {
+        if (all_stopped_by(base + static_cast<uint32_t>(it - ahead) + 1)) break;
       }
     }
     if (!dense) launch_head(stop_enabled, 0);
     if (dense && opts.dense_launches == 3) launch_dense_head(vec_args(stop_enabled), 0, stream);
+    if (!dense || opts.dense_launches == 3) ++heads_queued;
     if (timing) {
       check(hipEventRecord(ev_b, stream), "hipEventRecord");
       check(hipEventSynchronize(ev_b), "hipEventSynchronize");
@@ -1301,9 +1345,17 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
     c->d_cgcount = c->alloc<int32_t>(c->G);
     c->d_cgtotal = c->alloc<int64_t>(c->G);
     c->d_ps = c->alloc<PatState>(c->P);
+    c->d_heads = c->alloc<uint32_t>(c->P);
     c->d_trace = c->alloc<IterRecord>(static_cast<size_t>(c->P) * c->trace_cap);
     check(hipHostMalloc(reinterpret_cast<void**>(&c->h_ps), sizeof(PatState) * c->P, hipHostMallocDefault),
           "hipHostMalloc");
+    {
+      void* hp = nullptr;
+      check(hipHostMalloc(&hp, sizeof(uint32_t) * c->P, hipHostMallocCoherent), "hipHostMalloc");
+      c->h_progress = static_cast<uint32_t*>(hp);
+      for (int p = 0; p < c->P; ++p) c->h_progress[p] = 0;
+    }
+    launch_fill_f32(reinterpret_cast<float*>(c->d_heads), 0.0f, c->P, c->stream);
     check(hipHostMalloc(reinterpret_cast<void**>(&c->h_scr), sizeof(double) * (64 + 2 * static_cast<size_t>(H.nmax)),
                         hipHostMallocDefault),
           "hipHostMalloc");

@@ -220,6 +220,8 @@ struct VecArgs {
   const double* b64;       // dense x-update: A_s^T c_s W p in fp64 (stacked)
   AlgoParams prm;
   IterRecord* trace;
+  uint32_t* heads;         // per patient: heads run so far, with or without effect
+  uint32_t* progress;      // per patient, pinned host memory: heads << 1 | stopped
 };
 
 // Dense x-update (cached inverse of every B_s): device arrays and work tables.

@@ -261,6 +261,13 @@ __device__ __forceinline__ void head_scalars_run(const VecArgs& a, int p, int cg
     ps->bb_tau0 = ps->tau;
     ps->bb_iter0 = ps->iter;
   }
+  if (threadIdx.x == 0 && a.progress != nullptr) {
+    // for a host that runs ahead: how many heads the patient has had, and
+    // whether it has stopped, as one word of pinned memory
+    const uint32_t c = a.heads[p] + 1;
+    a.heads[p] = c;
+    __hip_atomic_store(a.progress + p, c << 1 | (ps->stopped ? 1u : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
   __syncthreads();
   if (DENSE || !cg_setup) return;
   // CG set-up, a wave per scenario: sums over its blocks, lane l taking blocks l,

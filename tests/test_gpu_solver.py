@@ -149,3 +149,42 @@ def test_device_resident_csr_input_matches_host_input():
         Sh.iterate(5)
         Sd.iterate(5)
         assert np.array_equal(Sh.z(), Sd.z())
+
+
+@pytest.mark.parametrize("xupdate", ["dense", "cg"])
+@pytest.mark.parametrize("launches", [3, 4])
+def test_solve_that_runs_ahead_of_the_stop_flags(xupdate, launches):
+    """The host queues iterations ahead of the stop flags: iteration counts, z,
+    the duals and the trace are the same however often it reads them, also with
+    patients that stop at different iterations, with fewer iterations allowed
+    than it queues ahead, and when a stopped context is solved again."""
+    import paper_2304_14568_amd as A
+    if xupdate == "cg" and launches == 4:
+        pytest.skip("the launch order is the dense x-update's")
+    Ps = [synth.make_tiny(0), synth.make_tiny(3, spots=(5, 7), num_scen=2)]
+    runs = []
+    for every in (1, 1, 5, 64):
+        with A.Solver(Ps, xupdate=xupdate, dense_launches=launches, check_every=every, max_iter=3000,
+                      deterministic=1) as S:
+            zs, info, st = S.solve()
+            runs.append((zs, info, st, [S.get_state(p) for p in range(2)], [S.trace(p) for p in range(2)]))
+            assert st == 0 and len(runs[-1][4][0]) == info[0]["iter"]
+            again, info2, _ = S.solve()  # already stopped: nothing moves
+            assert [i["iter"] for i in info2] == [i["iter"] for i in info]
+            assert all(np.array_equal(a, b) for a, b in zip(zs, again))
+            S.reset()
+            _, info3, _ = S.solve()  # the flags of the first run are not taken for the second's
+            assert [i["iter"] for i in info3] == [i["iter"] for i in info]
+    assert runs[0][1][0]["iter"] != runs[0][1][1]["iter"]
+    for r in runs[1:]:
+        assert [i["iter"] for i in r[1]] == [i["iter"] for i in runs[0][1]]
+        for p in range(2):
+            assert np.array_equal(r[0][p], runs[0][0][p]) and np.array_equal(r[3][p]["y"], runs[0][3][p]["y"])
+            assert r[4][p] == runs[0][4][p]
+    for k in (0, 1, 2, 3, 5):
+        with A.Solver(Ps, xupdate=xupdate, dense_launches=launches, max_iter=k, deterministic=1) as S:
+            zs, info, st = S.solve()
+            assert st == 1 and [i["iter"] for i in info] == [k, k]
+            S.reset()
+            S.iterate(k)
+            assert all(np.array_equal(zs[p], S.z(p)) for p in range(2))
