@@ -1929,9 +1929,9 @@ admm_status pgd_dense(admm_ctx* ctx, const pgd_options& o, int32_t patient, cons
   if (!ctx->d_pgd) {
     int64_t words = 0;
     for (const Pat& q : ctx->H.pat) {
-      const int64_t nj = q.fobj_end - q.fobj_begin, nbl = (q.npad + 255) / 256;
-      words = std::max(words, (2 + 2 * kPgdK) * static_cast<int64_t>(q.npad) + nj * kPgdK * 128 + q.nbk * kPgdK +
-                                  2 * nbl * kPgdK);
+      const int64_t nj = q.fobj_end - q.fobj_begin;
+      words = std::max(words, (4 + 3 * kPgdK) * static_cast<int64_t>(q.npad) + nj * kPgdK * 128 +
+                                  3 * static_cast<int64_t>(q.nbk) * kPgdK);
     }
     ctx->d_pgd = ctx->alloc<double>(static_cast<size_t>(words));
     ctx->d_pgdst = ctx->alloc<PgdDevState>(2);
@@ -1946,11 +1946,10 @@ admm_status pgd_dense(admm_ctx* ctx, const pgd_options& o, int32_t patient, cons
   a.nb = pt.nbk;
   a.n = n;
   a.np = pt.npad;
-  a.nblocks = (a.np + 255) / 256;
   a.x = ctx->d_pgd;
-  a.g = a.x + a.np;
-  a.xc = a.g + a.np;
-  a.u = a.xc + static_cast<int64_t>(kPgdK) * a.np;
+  a.g = a.x + 2 * static_cast<int64_t>(a.np);
+  a.xc = a.g + 2 * static_cast<int64_t>(a.np);
+  a.u = a.xc + 2 * static_cast<int64_t>(kPgdK) * a.np;
   a.part = a.u + static_cast<int64_t>(kPgdK) * a.np;
   a.fpart = a.part + static_cast<int64_t>(a.njobs) * kPgdK * 128;
   a.gdpart = a.fpart + static_cast<int64_t>(a.nb) * kPgdK;
@@ -1965,53 +1964,62 @@ admm_status pgd_dense(admm_ctx* ctx, const pgd_options& o, int32_t patient, cons
   // host sources stay alive and unchanged until the final synchronisation,
   // also when a failed call below leaves the function by an exception
   PgdDevState h0[2] = {}, h{};
-  std::vector<double> pv, hv(n);
+  std::vector<double> hv(n);
   StreamDrain drain{s};
   for (PgdDevState& e : h0) {
     e.alpha = o.alpha > 0 ? o.alpha : 1.0;
     e.pick = -1;
   }
+  volatile uint32_t* progress = reinterpret_cast<volatile uint32_t*>(ctx->h_scr + 32);
+  *progress = 0;
+  a.progress = const_cast<uint32_t*>(progress);
   check(hipMemcpyAsync(a.st, h0, sizeof(h0), hipMemcpyHostToDevice, s), "H2D");
-  launch_fill_f64(a.x, 0.0, 2 * static_cast<int64_t>(a.np), s);  // x and g, with their zero padding
-  if (!(o.alpha > 0)) {
-    // alpha = 10 / lambda_max(H), H = 2 sum_s G_s, 30 power iterations
-    pv.assign(n, 1.0 / std::sqrt(static_cast<double>(n)));
-    check(hipMemcpyAsync(a.x, pv.data(), sizeof(double) * n, hipMemcpyHostToDevice, s), "H2D");
-    for (int it = 0; it < 30; ++it) launch_pgd_power(a, a.x, s);
-  }
+  // x and g of both slots, with their zero padding
+  launch_fill_f64(a.x, 0.0, 4 * static_cast<int64_t>(a.np), s);
   for (int j = 0; j < n; ++j) {
     const double v = x0 ? x0[j] : 0.0;
     hv[j] = std::min(std::max(v, static_cast<double>(ctx->H.lb[pt.zvec_base + j])),
                      static_cast<double>(ctx->H.ub[pt.zvec_base + j]));
   }
   check(hipMemcpyAsync(a.x, hv.data(), sizeof(double) * n, hipMemcpyHostToDevice, s), "H2D");
-  launch_fill_f64(a.g, 0.0, n, s);
+  const bool power = !(o.alpha > 0);
+  if (power)  // alpha = 10 / lambda_max(H), H = 2 sum_s G_s, 30 power iterations
+    for (int it = 0; it < 30; ++it) launch_pgd_power(a, it == 0, 1.0 / std::sqrt(static_cast<double>(n)), s);
   static_assert(kPgdK % 2 == 0, "sub-buffers of the PGD work area stay 16-byte aligned");
-  // state slot 0 carries alpha from the power iteration; every launch of the
-  // step kernel reads slot par and writes slot par ^ 1
+  // every launch of the tiles reads slot par and writes slot par ^ 1
   int par = 0;
-  launch_pgd_prime(a, par, s);  // t_base = 0: every trial point is x
+  uint32_t seq = 0;
+  launch_pgd_prime(a, power ? 1 : 0, par, ++seq, s);  // every trial point is x
   par ^= 1;
-  launch_pgd_round(a, 1, par, s);
+  launch_pgd_round(a, 1, par, ++seq, s);
   par ^= 1;
   // every round either accepts a step or rejects kPgdK trial steps, so the
-  // device state reaches done within this many rounds
+  // device state reaches done within this many rounds; the host queues a few
+  // ahead of the last one that has reported
   const int64_t max_rounds =
       1 + static_cast<int64_t>(o.max_iter) * ((o.max_trials + kPgdK - 1) / kPgdK);
-  constexpr int kChunk = 16;
-  for (int64_t r = 1; r <= max_rounds; r += kChunk) {
-    const int64_t c = std::min<int64_t>(kChunk, max_rounds - r + 1);
-    for (int64_t k = 0; k < c; ++k) {
-      launch_pgd_round(a, 0, par, s);
-      par ^= 1;
+  constexpr uint32_t kAhead = 6;
+  bool done = false;
+  for (int64_t r = 1; r <= max_rounds && !done; ++r) {
+    launch_pgd_round(a, 0, par, ++seq, s);
+    par ^= 1;
+    uint32_t w = *progress, spins = 0;
+    while ((((w >> 1) - (seq - kAhead)) & 0x7fffffffu) >= 0x40000000u) {
+      if ((++spins & 0xfffu) == 0 && hipStreamQuery(s) != hipErrorNotReady) {
+        check(hipGetLastError(), "PGD launch");
+        check(hipStreamSynchronize(s), "sync");  // reports a failure; else the word is there now
+        if ((((*progress >> 1) - (seq - kAhead)) & 0x7fffffffu) >= 0x40000000u)
+          throw HipError{hipErrorUnknown, "PGD rounds did not report"};
+      }
+      w = *progress;
     }
-    check(hipGetLastError(), "PGD launch");
-    check(hipMemcpyAsync(&h, a.st + par, sizeof(h), hipMemcpyDeviceToHost, s), "D2H");
-    check(hipStreamSynchronize(s), "sync");
-    if (h.done) break;
+    done = (w & 1u) != 0;
   }
+  check(hipGetLastError(), "PGD launch");
   check(hipMemcpyAsync(&h, a.st + par, sizeof(h), hipMemcpyDeviceToHost, s), "D2H");
-  if (x_out) check(hipMemcpyAsync(x_out, a.x, sizeof(double) * n, hipMemcpyDeviceToHost, s), "D2H");
+  if (x_out)
+    check(hipMemcpyAsync(x_out, a.x + par * static_cast<int64_t>(a.np), sizeof(double) * n, hipMemcpyDeviceToHost, s),
+          "D2H");
   check(hipStreamSynchronize(s), "sync");
   const bool converged = h.done && h.status == 1;
   if (info) {

@@ -358,22 +358,24 @@ struct PgdArgs {
   const float* lb;
   const float* ub;
   const XJob* jobs;  // the patient's packed tiles in packed order
-  int32_t njobs, nb, n, nblocks;  // tiles, block rows, spots, 256-spot blocks of np
-  int32_t np, pad;   // n rounded up to whole 64-blocks: length of every vector below
-  double* x;         // np, zero beyond n
-  double* g;         // np, gradient at x
-  double* xc;        // kPgdK x np trial points, zero beyond n
+  int32_t njobs, nb, n;  // tiles, block rows, spots
+  int32_t np;        // n rounded up to whole 64-blocks: length of every vector below
+  double* x;         // [2] x np by round parity, zero beyond n
+  double* g;         // [2] x np, gradient at x
+  double* xc;        // [2] x kPgdK x np trial points, zero beyond n
   double* u;         // kPgdK x np: S x_k
   double* part;      // per tile and trial point: 64 row and 64 column products
   double* fpart;     // [k][block row]
-  double* gdpart;    // [2][k][block]: double-buffered by round parity
+  double* gdpart;    // [2][k][block row]
   PgdDevState* st;   // [2]: read slot par, write slot par ^ 1
+  uint32_t* progress;  // pinned host memory: the last round's sequence number << 1 | done
   double fconst, beta, gamma, tol;
   int32_t max_iter, max_trials;
 };
 
-void launch_pgd_power(const PgdArgs& a, double* v, hipStream_t st);
-void launch_pgd_prime(const PgdArgs& a, int par, hipStream_t st);
-void launch_pgd_round(const PgdArgs& a, int first, int par, hipStream_t st);
+// one step of the power iteration on 2 S (start: from v0 everywhere)
+void launch_pgd_power(const PgdArgs& a, int start, double v0, hipStream_t st);
+void launch_pgd_prime(const PgdArgs& a, int power, int par, uint32_t seq, hipStream_t st);
+void launch_pgd_round(const PgdArgs& a, int first, int par, uint32_t seq, hipStream_t st);
 
 }  // namespace admmbb

@@ -109,3 +109,24 @@ def test_stream_probe_reports_a_plausible_rate():
     import paper_2304_14568_amd as A
     gbs = A.stream_probe(64 << 20, reps=5)
     assert 100.0 < gbs < 20000.0, gbs
+
+
+@pytest.mark.parametrize("spots", [(1, 1), (8, 8), (5, 13), (13, 20), (16, 24)])
+@pytest.mark.parametrize("alpha,max_trials", [(0.0, 60), (50.0, 3), (50.0, 60), (1e9, 9)])
+def test_dense_pgd_tile_edges_and_retries(spots, alpha, max_trials):
+    """One block row (one diagonal tile), exactly 64 spots, 65, 260 (five rows, a
+    ragged last) and 384 spots; steps that pass at once, after whole rejected
+    rounds of eight (the decision is taken by the next launch), and never."""
+    import paper_2304_14568_amd as A
+    P = synth.make_tiny(10, spots=spots, spacing=1.5, num_scen=2)
+    W = wls.from_problem(P)
+    L = opgd.lipschitz(W)
+    a = alpha / L if alpha > 0 else 0.0
+    kw = dict(obj_rel_tol=0.0, max_iter=6, max_trials=max_trials)
+    q = opgd.pgd_armijo(W, record=False, **(dict(alpha=a) if a > 0 else {}), **kw)
+    with A.Solver(P, xupdate="dense") as S:
+        runs = [S.pgd(0, dense=1, alpha=a, **kw) for _ in range(2)]
+    x, info, st = runs[0]
+    assert np.array_equal(x, runs[1][0]) and info["obj"] == runs[1][1]["obj"]
+    assert np.linalg.norm(x - q.x) <= 1e-9 * max(1e-12, np.linalg.norm(q.x))
+    assert abs(info["obj"] - q.obj) <= 1e-10 * q.obj
