@@ -513,8 +513,7 @@ struct admm_ctx {
         pass_launch(PASS_CG, pa, 0, T);
       va.step = k;
       launch_reduce(RED_CG, va, 0, NB, stream);
-      launch_cg_update(va, NB, stream);
-      launch_cg_dir(va, NB, stream);
+      launch_cg_step(va, G, H.nmax, stream);
     }
     launch_zres(va, NPB, stream);
     launch_body_scalars(va, stream);
@@ -1259,8 +1258,6 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
         j.col0 = H.blk[b].col0;
         j.scen = H.blk[b].owner;
         j.patient = sc.patient;
-        j.blk0 = sc.blk_begin;
-        j.nblk = sc.nblk;
       }
       c->d_cjobs = c->upload(cj);
       std::vector<ZJob> zj(H.pblk.size());

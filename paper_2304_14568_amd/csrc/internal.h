@@ -162,16 +162,14 @@ struct PassArgs {
   int32_t unroll;          // rows per lane group in flight: 1, 2 or 4
 };
 
-// Column reduction of the tile partials and CG vector steps: one column block
-// of one scenario, with every address its loads need
+// Column reduction of the tile partials: one column block of one scenario, with
+// every address its loads need
 struct ColJob {
   int64_t part_off;   // the scenario's first tile partials
   int64_t vec_base;   // the scenario in the stacked n-vectors
   int64_t zvec_base;  // its patient in the per-patient n-vectors
   int32_t ntiles, n, col0, scen;
-  int32_t patient;
-  int32_t blk0, nblk;  // the scenario's column blocks
-  int32_t pad;
+  int32_t patient, pad;
 };
 
 // z-update: one patient column block, with every address its loads need
@@ -275,8 +273,7 @@ void launch_pass(int mode, const PassArgs& a, int tile_begin, int tile_count, hi
                  hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 void launch_reduce(int mode, const VecArgs& a, int blk_begin, int nblk, hipStream_t st);
 void launch_head_scalars(const VecArgs& a, int cg_setup, hipStream_t st);
-void launch_cg_update(const VecArgs& a, int nblk, hipStream_t st);
-void launch_cg_dir(const VecArgs& a, int nblk, hipStream_t st);
+void launch_cg_step(const VecArgs& a, int nscen, int nmax, hipStream_t st);
 void launch_zres(const VecArgs& a, int npblk, hipStream_t st);
 void launch_body_scalars(const VecArgs& a, hipStream_t st);
 void launch_gsum(const float* part, int ntiles, int n, float scale, float* out, float* hout, const double* objpart,

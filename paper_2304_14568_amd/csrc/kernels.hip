@@ -154,76 +154,74 @@ void launch_head_scalars(const VecArgs& a, int cg_setup, hipStream_t st) {
 // CG vector steps
 // ---------------------------------------------------------------------------
 
-// One wave per column block; every address comes from the block's job entry, and
-// the vectors are requested beside the partial sums that the step's scalar
-// needs, so that a launch is two dependent reads long (table, then everything
-// else) instead of four.  With the wave per scenario of the CG set-up, a solve of
-// 13 scenarios of 1 493 spots went from 109.5 to 107.4 ms.
-__global__ __launch_bounds__(kColBlock) void k_cg_update(VecArgs a) {
-  const int bi = static_cast<int>(blockIdx.x);
-  const ColJob cj = a.cjobs[bi];
-  const int g = cj.scen;
-  const int j = cj.col0 + static_cast<int>(threadIdx.x);
-  const bool in = j < cj.n;
-  const int64_t vi = cj.vec_base + (in ? j : 0);
-  const uint8_t act = a.act[g * kRing + a.step];
-  const double rz = a.rz[g * kRing + a.step];
-  const float vj = a.v[vi], qj = a.q[vi], xj = a.x[vi], r0 = a.r[vi];
-  const float dinv = a.dinv != nullptr ? a.dinv[vi] : 1.0f;
-  const double vq = wave_strided_sum(a.bpart + static_cast<int64_t>(cj.blk0) * 8 + 0, cj.nblk);
-  if (!act) return;
-  const float alpha = (vq > 0.0) ? static_cast<float>(rz / vq) : 0.0f;
-  double loc = 0.0;
-  if (in) {
-    a.x[vi] = fmaf(alpha, vj, xj);
-    const float rj = fmaf(-alpha, qj, r0);
-    a.r[vi] = rj;
-    float zpv = rj;
-    if (a.dinv != nullptr) {
-      zpv = rj * dinv;
-      a.zp[vi] = zpv;
-    }
-    loc = static_cast<double>(rj) * zpv;
-  }
-  loc = wave_sum(loc);
-  if (threadIdx.x == 0) a.bpart[(int64_t)bi * 8 + 3] = loc;
-}
-
-__global__ __launch_bounds__(kColBlock) void k_cg_dir(VecArgs a) {
-  const int bi = static_cast<int>(blockIdx.x);
-  const ColJob cj = a.cjobs[bi];
-  const int g = cj.scen;
-  const int k = a.step;
-  const int j = cj.col0 + static_cast<int>(threadIdx.x);
-  const bool in = j < cj.n;
-  const int64_t vi = cj.vec_base + (in ? j : 0);
+// One workgroup per scenario takes both vector steps of a CG step: alpha from
+// the blocks' <v, q>, x += alpha v, r -= alpha q, beta from the new <r, M^-1 r>,
+// v = M^-1 r + beta v, the spots NE to a thread in registers.  With one wave per
+// column block the step had a grid-wide sum in its middle and took two launches
+// of 4.9 us each; this one takes 4.9 us at 1 493 spots (a solve of 13 scenarios
+// 113.5 -> 110.7 ms) and 7.8 us at 8 200 and more, no slower than the two.
+template <int NE>
+__global__ __launch_bounds__(1024) void k_cg_step(VecArgs a) {
+  __shared__ double red[16];
+  const int g = static_cast<int>(blockIdx.x), k = a.step;
+  const Scen sc = a.scen[g];
+  const int tid = threadIdx.x;
   const uint8_t act = a.act[g * kRing + k];
   const double rz0 = a.rz[g * kRing + k], tol2 = a.tol2[g];
-  const float zpv = (a.dinv != nullptr) ? a.zp[vi] : a.r[vi];
-  const float v0 = a.v[vi];
-  const double rz1 = wave_strided_sum(a.bpart + static_cast<int64_t>(cj.blk0) * 8 + 3, cj.nblk);
+  float v[NE], q[NE], x[NE], r[NE], d[NE];
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const int j = tid + 1024 * e;
+    const int64_t vi = sc.vec_base + (j < sc.n ? j : 0);
+    v[e] = a.v[vi];
+    q[e] = a.q[vi];
+    x[e] = a.x[vi];
+    r[e] = a.r[vi];
+    d[e] = a.dinv != nullptr ? a.dinv[vi] : 1.0f;
+  }
+  const double vq = wave_strided_sum(a.bpart + static_cast<int64_t>(sc.blk_begin) * 8 + 0, sc.nblk);
   if (!act) {
-    if (threadIdx.x == 0) a.act[g * kRing + k + 1] = 0;
+    if (tid == 0) a.act[g * kRing + k + 1] = 0;
     return;
   }
+  const float alpha = (vq > 0.0) ? static_cast<float>(rz0 / vq) : 0.0f;
+  double loc = 0.0;
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const int j = tid + 1024 * e;
+    r[e] = fmaf(-alpha, q[e], r[e]);
+    d[e] = a.dinv != nullptr ? r[e] * d[e] : r[e];  // preconditioned residual
+    if (j < sc.n) {
+      a.x[sc.vec_base + j] = fmaf(alpha, v[e], x[e]);
+      a.r[sc.vec_base + j] = r[e];
+      if (a.dinv != nullptr) a.zp[sc.vec_base + j] = d[e];
+      loc += static_cast<double>(r[e]) * d[e];
+    }
+  }
+  loc = wave_sum(loc);
+  if ((tid & 63) == 0) red[tid >> 6] = loc;
+  __syncthreads();
+  double rz1 = 0.0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) rz1 += red[w];
   const float beta = (rz0 > 0.0) ? static_cast<float>(rz1 / rz0) : 0.0f;
-  if (in) a.v[vi] = fmaf(beta, v0, zpv);
-  if (threadIdx.x == 0) {
-    // every block of the scenario writes the same values
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const int j = tid + 1024 * e;
+    if (j < sc.n) a.v[sc.vec_base + j] = fmaf(beta, v[e], d[e]);
+  }
+  if (tid == 0) {
     a.rz[g * kRing + k + 1] = rz1;
     a.act[g * kRing + k + 1] = (rz1 > tol2 && rz1 > 0.0) ? 1 : 0;
-    if (cj.col0 == 0) {
-      a.cgcount[g] += 1;
-      a.cgtotal[g] += 1;
-    }
+    a.cgcount[g] += 1;
+    a.cgtotal[g] += 1;
   }
 }
 
-void launch_cg_update(const VecArgs& a, int nblk, hipStream_t st) {
-  hipLaunchKernelGGL(k_cg_update, dim3(nblk), dim3(kColBlock), 0, st, a);
-}
-void launch_cg_dir(const VecArgs& a, int nblk, hipStream_t st) {
-  hipLaunchKernelGGL(k_cg_dir, dim3(nblk), dim3(kColBlock), 0, st, a);
+void launch_cg_step(const VecArgs& a, int nscen, int nmax, hipStream_t st) {
+  static_assert(14 * 1024 >= 13600, "set-up refuses patients of more spots: the sparse pass holds them in LDS");
+  auto kern = nmax <= 2048 ? k_cg_step<2> : (nmax <= 4096 ? k_cg_step<4> : (nmax <= 8192 ? k_cg_step<8> : k_cg_step<14>));
+  hipLaunchKernelGGL(kern, dim3(nscen), dim3(1024), 0, st, a);
 }
 
 // ---------------------------------------------------------------------------

@@ -162,10 +162,15 @@ def test_solve_that_runs_ahead_of_the_stop_flags(xupdate, launches):
     if xupdate == "cg" and launches == 4:
         pytest.skip("the launch order is the dense x-update's")
     Ps = [synth.make_tiny(0), synth.make_tiny(3, spots=(5, 7), num_scen=2)]
+    # the CG pass configuration is named: each context times the candidates for
+    # itself, and a tile's objective partial (float64) is added in an order that
+    # depends on the workgroup size, so the traced objective of two contexts may
+    # differ by a rounding otherwise
+    cfg = dict(pass_threads=256, pass_unroll=1, format="csr") if xupdate == "cg" else {}
     runs = []
     for every in (1, 1, 5, 64):
         with A.Solver(Ps, xupdate=xupdate, dense_launches=launches, check_every=every, max_iter=3000,
-                      deterministic=1) as S:
+                      deterministic=1, **cfg) as S:
             zs, info, st = S.solve()
             runs.append((zs, info, st, [S.get_state(p) for p in range(2)], [S.trace(p) for p in range(2)]))
             assert st == 0 and len(runs[-1][4][0]) == info[0]["iter"]
@@ -188,3 +193,42 @@ def test_solve_that_runs_ahead_of_the_stop_flags(xupdate, launches):
             S.reset()
             S.iterate(k)
             assert all(np.array_equal(zs[p], S.z(p)) for p in range(2))
+
+
+@pytest.mark.parametrize("precond", [0, 1])
+@pytest.mark.parametrize("n", [65, 1025, 2048, 2049, 4097, 8193])
+def test_cg_step_at_spots_per_thread_edges(n, precond):
+    """A CG step is one workgroup of 1 024 threads per scenario, with 2, 4, 8 or
+    14 spots to a thread: both sides of those ranges, scenarios that need
+    different numbers of steps, against a sparse float64 solve.  Each row holds
+    one spot or two neighbours, so B_s has a condition number below 20; fp32
+    recurrences of some ten steps keep x to 20 * 10 * 2^-24 = 1.2e-5 of its
+    size."""
+    import scipy.sparse as sp
+    import scipy.sparse.linalg as spl
+
+    import paper_2304_14568_amd as A
+    rng = np.random.default_rng(n)
+    i = np.arange(n)
+    pair = np.sort(np.stack([i, (i + 1) % n], axis=1), axis=1)
+    As = []
+    for lo in (0.9, 0.5, 0.2):
+        As.append(synth.Csr(row_ptr=np.concatenate([2 * np.arange(n + 1), 2 * n + 1 + i]).astype(np.int64),
+                            col=np.concatenate([pair.ravel(), i]).astype(np.int32),
+                            val=rng.uniform(lo, 1.0, 3 * n).astype(np.float32)))
+    P = synth.Problem(m=2 * n, n=n, A=As, prob=np.full(3, 1 / 3), struct_id=np.repeat([0, 1], n).astype(np.uint8),
+                      struct_weight=np.array([0.3, 1.0]), presc=rng.uniform(0.5, 1.5, 2 * n), lb=np.zeros(n),
+                      ub=np.full(n, 10.0))
+    W = wls.from_problem(P)
+    with A.Solver(P, xupdate="cg", precond=precond, cg_max=64, cg_eta=1e-7, rho=0.5) as S:
+        rho = S.rho()
+        x = []
+        for s in range(3):
+            B = (W.A[s].T @ sp.diags(W.c[s] * W.w) @ W.A[s] + 0.5 * rho * sp.eye(n)).tocsc()
+            assert spl.norm(B, 1) / (0.5 * rho) < 20
+            x.append(spl.spsolve(B, W.A[s].T @ (W.c[s] * W.w * W.p)))
+        for _ in range(2):
+            S.reset()
+            S.iterate(1)
+            zr = wls.project(W, np.mean(x, axis=0))
+            assert np.abs(S.z() - zr).max() <= 1.2e-5 * np.abs(zr).max()
