@@ -614,20 +614,169 @@ __global__ __launch_bounds__(512) void k_sweep_pivot(FactorArgs f, int npad, int
   }
 }
 
+// Element at a wave-uniform base and a byte offset per lane: one scalar pointer
+// and one 32-bit register address it.
+template <class T>
+__device__ __forceinline__ T* at_bytes(T* base, uint32_t bytes) {
+  return reinterpret_cast<T*>(reinterpret_cast<std::conditional_t<std::is_const_v<T>, const char*, char*>>(base) + bytes);
+}
+
+// The 16 x 16 tiles (i, j), i <= j, of a pivot block of KB columns, in the
+// registers of four waves: wave 0 has the diagonal ones (tile (s, s) in slot s)
+// and, of 128 columns, the last of the others, which waves 1 to 3 take in turn.
+template <int KB>
+struct PivotTiles {
+  static constexpr int NB = KB / 16, kOff = NB * (NB - 1) / 2, kPer = NB == 8 ? 9 : 4;
+  v4d T[kPer];  // item q: row kk + 4 q, column m
+  int ij[kPer];  // 16 i + j, -1: none
+  __device__ __forceinline__ explicit PivotTiles(int wu) {
+#pragma unroll
+    for (int s = 0; s < kPer; ++s) {
+      int t = wu == 0 ? 27 : 3 * s + wu - 1;
+      ij[s] = -1;
+      if (wu == 0 && s < NB) {
+        ij[s] = 17 * s;
+      } else if (t < kOff && (wu == 0 || t != 27)) {
+        int i = 0;
+        while (t >= NB - 1 - i) {
+          t -= NB - 1 - i;
+          ++i;
+        }
+        ij[s] = 16 * i + i + 1 + t;
+      }
+    }
+  }
+};
+
+constexpr int kPivotLds = 8 * 256 * 2 + 2 * 256;  // doubles
+
+// k_sweep_pivot on a block held in PivotTiles, within the threads, registers and
+// LDS of k_sweep_update, with the same results bit for bit: the owners of row and
+// column b form V_i and U_i, wave 0 inverts.  With four waves the chain takes
+// 53 us for 128 columns, beside other work.
+template <int KB>
+__device__ __forceinline__ void sweep_pivot_block(PivotTiles<KB>& pt, double* lds, double* P) {
+  using PT = PivotTiles<KB>;
+  constexpr int NB = PT::NB, kPer = PT::kPer;
+  double* U = lds;              // U_i^T
+  double* V = lds + 8 * 256;    // M_bi before the step
+  double* P16 = lds + 16 * 256;  // two of 256
+  const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, kk = lane >> 4;
+  const int wu = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto invert = [&](const v4d& t, double* out) {
+    double r[4] = {t[0], t[1], t[2], t[3]};
+    sweep16_steps<0>(r, m, kk);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[(kk + 4 * q) * 16 + m] = -r[q];
+  };
+  auto update = [&](int i, int j, v4d t) {
+    v4d d = -t;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      d = __builtin_amdgcn_mfma_f64_16x16x4f64(U[i * 256 + (kk + 4 * q) * 16 + m], V[j * 256 + (kk + 4 * q) * 16 + m], d, 0,
+                                               0, 0);
+    return -d;
+  };
+  if (wu == 0) invert(pt.T[0], P16);
+  __syncthreads();
+#pragma unroll 1
+  for (int b = 0; b < NB; ++b) {
+    const double* Pb = P16 + 256 * (b & 1);
+#pragma unroll
+    for (int s = 0; s < kPer; ++s) {
+      __builtin_amdgcn_sched_barrier(0);  // a tile at a time: the registers are those of the update
+      int ij = pt.ij[s];
+      asm volatile("" : "+s"(ij));  // no address kept over the rounds
+      const int i = ij >> 4, j = ij & 15;
+      if (ij < 0 || (i == b) == (j == b)) continue;
+      const int o = i == b ? j : i;
+      double v[4];
+      if (i == b) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) V[o * 256 + (kk + 4 * q) * 16 + m] = v[q] = pt.T[s][q];
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) V[o * 256 + m * 16 + kk + 4 * q] = pt.T[s][q];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = V[o * 256 + (kk + 4 * q) * 16 + m];
+      }
+      v4d d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) d = __builtin_amdgcn_mfma_f64_16x16x4f64(Pb[(kk + 4 * q) * 16 + m], v[q], d, 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) U[o * 256 + (kk + 4 * q) * 16 + m] = d[q];
+    }
+    __syncthreads();
+    if (wu == 0 && b + 1 < NB) {
+      v4d t = pt.T[0];
+#pragma unroll
+      for (int s = 1; s < NB; ++s)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t[q] = s == b + 1 ? pt.T[s][q] : t[q];
+      t = update(b + 1, b + 1, t);
+#pragma unroll
+      for (int s = 1; s < NB; ++s)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) pt.T[s][q] = s == b + 1 ? t[q] : pt.T[s][q];
+      invert(t, P16 + 256 * ((b + 1) & 1));
+    }
+#pragma unroll
+    for (int s = 0; s < kPer; ++s) {
+      __builtin_amdgcn_sched_barrier(0);
+      int ij = pt.ij[s];
+      asm volatile("" : "+s"(ij));
+      const int i = ij >> 4, j = ij & 15;
+      if (ij < 0 || (i == b + 1 && j == b + 1)) continue;
+      if (i != b && j != b) {
+        pt.T[s] = update(i, j, pt.T[s]);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int row = kk + 4 * q;
+          pt.T[s][q] = i == j ? -Pb[row * 16 + m] : (i == b ? U[j * 256 + row * 16 + m] : U[i * 256 + m * 16 + row]);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  // the swept block is -A_KK^-1; both triangles of P
+#pragma unroll
+  for (int s = 0; s < kPer; ++s) {
+    __builtin_amdgcn_sched_barrier(0);
+    if (pt.ij[s] < 0) continue;
+    const int i = pt.ij[s] >> 4, j = pt.ij[s] & 15;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = kk + 4 * q;
+      P[(16 * i + r) * kKb + 16 * j + m] = -pt.T[s][q];
+      if (i != j) P[(16 * j + m) * kKb + 16 * i + r] = -pt.T[s][q];
+    }
+  }
+}
+
 // Panels of a pivot block for 64 columns i of the matrix: R = A_K,i (old values)
 // and Ut = U^T = P A_K,i.  Only the upper tiles (I <= J) of the sweep matrix are
 // kept up to date (it stays symmetric), so blocks before the pivot are read from
 // the mirrored tile, transposed.  The columns of A_K,i go through LDS 32 rows at
 // a time; wave w forms KB / 4 rows of Ut, its operand P read by columns (P is
-// symmetric) straight from memory.
+// symmetric) straight from memory.  The columns of the pivot block itself have
+// no panels: there the block is replaced by -P.
 template <int KB>
 __global__ __launch_bounds__(256) void k_sweep_panel(FactorArgs f, int npad, int k0) {
   constexpr int kLd = kFb + 16;
   __shared__ double ks[32][kLd];
   const int g = static_cast<int>(blockIdx.y);  // place in the chunk
-  const double* A = f.A + static_cast<int64_t>(blockIdx.y) * npad * npad;  // chunk buffer
+  double* A = f.A + static_cast<int64_t>(blockIdx.y) * npad * npad;  // chunk buffer
   const int i0 = static_cast<int>(blockIdx.x) * kFb;
   const double* Pg = f.P + static_cast<int64_t>(g) * kKb * kKb;
+  if (i0 / kKb == k0 / kKb) {
+    for (int e = threadIdx.x; e < (i0 + kFb - k0) * kFb; e += 256) {
+      const int r = e / kFb, c = i0 - k0 + e % kFb;
+      A[static_cast<int64_t>(k0 + r) * npad + k0 + c] = -Pg[r * kKb + c];
+    }
+    return;
+  }
   double* Ut = f.U + static_cast<int64_t>(g) * f.npmax * kKb;
   double* R = f.R + static_cast<int64_t>(g) * f.npmax * kKb;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 15, kk = lane >> 4;
@@ -685,11 +834,78 @@ __global__ __launch_bounds__(256) void k_sweep_panel(FactorArgs f, int npad, int
         Ut[static_cast<int64_t>((w * NC + a) * 16 + kk + 4 * r) * npad + i0 + 16 * b + m] = acc[a][b][r];
 }
 
-// Element at a wave-uniform base and a byte offset per lane: one scalar pointer
-// and one 32-bit register address it.
-template <class T>
-__device__ __forceinline__ T* at_bytes(T* base, uint32_t bytes) {
-  return reinterpret_cast<T*>(reinterpret_cast<std::conditional_t<std::is_const_v<T>, const char*, char*>>(base) + bytes);
+// Rank-KB update of the next pivot block (at k1, KBN columns) of scenario g, and
+// its inverse: the accumulators start from -A_ij, the panels' columns pass
+// through LDS in slabs of 8 rows, the next slab's loads in flight over the
+// current one's products.
+template <int KB, int KBN>
+__device__ __forceinline__ void sweep_next_pivot(const FactorArgs& f, int npad, int k1, int g, double* lds) {
+  constexpr int kLd = KBN + 16, kSlab = 8, kQ = (kSlab * KBN / 2 + 255) / 256;
+  constexpr int kPer = PivotTiles<KBN>::kPer;
+  static_assert(4 * kSlab * kLd <= 4 * 16 * 80 && kPivotLds <= 4 * 16 * 80 && kSlab * KBN / 2 % 256 == 0);
+  const double* A = f.A + static_cast<int64_t>(g) * npad * npad + static_cast<int64_t>(k1) * npad + k1;
+  const double* Ut = f.U + static_cast<int64_t>(g) * f.npmax * kKb + k1;
+  const double* R = f.R + static_cast<int64_t>(g) * f.npmax * kKb + k1;
+  const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, kk = lane >> 4;
+  PivotTiles<KBN> pt(__builtin_amdgcn_readfirstlane(tid >> 6));
+  uint32_t o[kQ];
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) {
+    const int e = tid + 256 * q, r = e / (KBN / 2), c = 2 * (e % (KBN / 2));
+    o[q] = 8u * static_cast<uint32_t>(r * npad + c);
+  }
+  v2d ub[kQ], rb[kQ];
+  auto fetch = [&](int s) {
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      ub[q] = *reinterpret_cast<const v2d*>(at_bytes(Ut + static_cast<int64_t>(s) * kSlab * npad, o[q]));
+      rb[q] = *reinterpret_cast<const v2d*>(at_bytes(R + static_cast<int64_t>(s) * kSlab * npad, o[q]));
+    }
+  };
+  auto stage = [&](int buf) {
+    double* u = lds + buf * kSlab * kLd;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      const int e = tid + 256 * q, r = e / (KBN / 2), c = 2 * (e % (KBN / 2));
+      *reinterpret_cast<v2d*>(&u[r * kLd + c]) = ub[q];
+      *reinterpret_cast<v2d*>(&u[2 * kSlab * kLd + r * kLd + c]) = rb[q];
+    }
+  };
+  fetch(0);
+#pragma unroll
+  for (int s = 0; s < kPer; ++s) {
+    const int ij = pt.ij[s] < 0 ? 0 : pt.ij[s];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      pt.T[s][q] = -*at_bytes(A + static_cast<int64_t>(16 * (ij >> 4) + 4 * q) * npad + 16 * (ij & 15),
+                              8u * static_cast<uint32_t>(kk * npad + m));
+  }
+  stage(0);
+  __syncthreads();
+  constexpr int ns = KB / kSlab;
+#pragma unroll 1
+  for (int s = 0; s < ns; ++s) {
+    fetch(s + 1 < ns ? s + 1 : 0);  // the last round's is not used
+    __builtin_amdgcn_sched_barrier(0);
+    const double* u = lds + (s & 1) * kSlab * kLd;
+    const double* v = u + 2 * kSlab * kLd;
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+      if (t % 3 == 0) __builtin_amdgcn_sched_barrier(0);
+      int ij = pt.ij[t] < 0 ? 0 : pt.ij[t];
+      asm volatile("" : "+s"(ij));
+#pragma unroll
+      for (int h = 0; h < kSlab / 4; ++h)
+        pt.T[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[(4 * h + kk) * kLd + 16 * (ij >> 4) + m],
+                                                       v[(4 * h + kk) * kLd + 16 * (ij & 15) + m], pt.T[t], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    stage((s + 1) & 1);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int s = 0; s < kPer; ++s) pt.T[s] = -pt.T[s];
+  sweep_pivot_block<KBN>(pt, lds, f.P + static_cast<int64_t>(g) * kKb * kKb);
 }
 
 // Rank-KB update A_ij -= U_i R_j of one upper 64 x 64 tile off the pivot row and
@@ -700,37 +916,54 @@ __device__ __forceinline__ T* at_bytes(T* base, uint32_t bytes) {
 // (47 TFLOP/s, the products' issue; the rank-64 vector form took 2 x 275 us),
 // 351 us with blocks of 128 x 128 (at 1 700 spots 129 against 104 us: too few
 // blocks), and the same with an XCD's tiles next to each other.
-template <int KB>
-__global__ __launch_bounds__(256, 4) void k_sweep_update(FactorArgs f, int npad, int k0) {
+//
+// The first workgroups, one per scenario, instead update the next pivot block
+// (KBN columns; 0: none) in registers, in the same order of products, and invert
+// it beside the other tiles' work: two inversions of 13 scenarios of 2 003 spots
+// and a warm start's other work 9.57 -> 8.74 ms.
+template <int KB, int KBN>
+__global__ __launch_bounds__(256, 4) void k_sweep_update(FactorArgs f, int npad, int k0, int nscen) {
   constexpr int MT = kFb, kLd = MT + 16, kSlab = 16;
   constexpr int W = MT / 32;                 // 16-wide groups of a wave
   constexpr int kQ = kSlab * MT / 2 / 256;   // double2 per thread, slab and panel
-  __shared__ __align__(16) double us[2][kSlab * kLd], rs[2][kSlab * kLd];
-  const int nm = npad / MT;
+  __shared__ __align__(16) double lds[4 * kSlab * kLd];
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 15, kk = lane >> 4;
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  const int k1 = k0 + KB;  // the next pivot block
+  int x = static_cast<int>(blockIdx.x);
+  if constexpr (KBN != 0) {
+    if (x < nscen) {
+      __builtin_amdgcn_s_setprio(2);  // the chain goes before the tiles that share its CU
+      sweep_next_pivot<KB, KBN>(f, npad, k1, x, lds);
+      return;
+    }
+    x -= nscen;
+  }
+  const int nm = npad / MT, nt = nm * (nm + 1) / 2;
+  const int g = x / nt;  // place in the chunk
   // upper tile number -> (bi, bj), bi <= bj
-  int t0 = static_cast<int>(blockIdx.x), bi = 0;
+  int t0 = x - g * nt, bi = 0;
   while (t0 >= nm - bi) {
     t0 -= nm - bi;
     ++bi;
   }
   const int bj = bi + t0;
-  const int g = static_cast<int>(blockIdx.y);  // place in the chunk
-  double* A = f.A + static_cast<int64_t>(blockIdx.y) * npad * npad;  // chunk buffer
+  double* A = f.A + static_cast<int64_t>(g) * npad * npad;  // chunk buffer
   const int i0 = bi * MT, j0 = bj * MT;
   const double* Ut = f.U + static_cast<int64_t>(g) * f.npmax * kKb;
   const double* R = f.R + static_cast<int64_t>(g) * f.npmax * kKb;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 15, kk = lane >> 4;
   const bool rowK = i0 / kKb == k0 / kKb, colK = j0 / kKb == k0 / kKb;
+  if (rowK && colK) return;  // already -P
+  if (KBN != 0 && i0 / kKb == k1 / kKb && j0 / kKb == k1 / kKb) return;
   if (rowK || colK) {
-    const double* Pg = f.P + static_cast<int64_t>(g) * kKb * kKb;
-    double* tr = us[0];  // 32 x 33, for the transposed copies
+    double* tr = lds;  // 32 x 33, for the transposed copies
     for (int sub = 0; sub < MT / 32 * (MT / 32); ++sub) {
       const int r0 = i0 + 32 * (sub / (MT / 32)), c0 = j0 + 32 * (sub % (MT / 32));
       if (rowK) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int r = r0 + (tid >> 5) + 8 * q, c = c0 + (tid & 31);
-          A[static_cast<int64_t>(r) * npad + c] = colK ? -Pg[(r - k0) * kKb + c - k0] : Ut[static_cast<int64_t>(r - k0) * npad + c];
+          A[static_cast<int64_t>(r) * npad + c] = Ut[static_cast<int64_t>(r - k0) * npad + c];
         }
       } else {
         __syncthreads();
@@ -749,7 +982,8 @@ __global__ __launch_bounds__(256, 4) void k_sweep_update(FactorArgs f, int npad,
     }
     return;
   }
-  const int wu = __builtin_amdgcn_readfirstlane(w);
+  double (*us)[kSlab * kLd] = reinterpret_cast<double (*)[kSlab * kLd]>(lds);
+  double (*rs)[kSlab * kLd] = us + 2;
   const int wi = (MT / 2) * (wu >> 1), wj = (MT / 2) * (wu & 1);
   // every address: a wave-uniform base and a 32-bit byte offset per lane
   uint32_t oi[kQ], oj[kQ];
@@ -1392,17 +1626,32 @@ void launch_gram_finish(FactorArgs f, int patient, int scen_begin, int nscen, in
 
 void launch_sweep(FactorArgs f, int nscen, int npad, hipStream_t st) {
   const int n64 = npad / 64, nt = n64 * (n64 + 1) / 2;
-  auto step = [&](auto kbc, int k0) {
-    constexpr int KB = decltype(kbc)::value;
-    hipLaunchKernelGGL(k_sweep_pivot<KB>, dim3(nscen), dim3(512), 0, st, f, npad, k0);
+  // The next pivot block goes beside the update where the update takes longer
+  // than the pivot's chain within it (85 to 105 us, against 32 in a launch of its
+  // own): per step, update and pivot 64 + 31 against 103 us with 2 730 tiles over
+  // the scenarios, 104 + 31 against 127 us with 4 914, 147 + 32 against 157 us
+  // with 6 864.
+  const bool beside = static_cast<int64_t>(nt) * nscen >= 4096;
+  auto step = [&](auto kbc, auto kbn, int k0) {
+    constexpr int KB = decltype(kbc)::value, KBN = decltype(kbn)::value;
+    if (k0 == 0 || !beside) hipLaunchKernelGGL(k_sweep_pivot<KB>, dim3(nscen), dim3(512), 0, st, f, npad, k0);
     hipLaunchKernelGGL(k_sweep_panel<KB>, dim3(n64, nscen), dim3(256), 0, st, f, npad, k0);
-    hipLaunchKernelGGL(k_sweep_update<KB>, dim3(nt, nscen), dim3(256), 0, st, f, npad, k0);
+    hipLaunchKernelGGL((k_sweep_update<KB, KBN>), dim3((nt + (KBN != 0 ? 1 : 0)) * nscen), dim3(256), 0, st, f, npad, k0,
+                       nscen);
   };
+  constexpr std::integral_constant<int, kKb> full{};
+  constexpr std::integral_constant<int, 64> half{};
+  constexpr std::integral_constant<int, 0> none{};
   for (int k0 = 0; k0 < npad; k0 += kKb) {
-    if (npad - k0 >= kKb)
-      step(std::integral_constant<int, kKb>{}, k0);
+    const int left = npad - k0;
+    if (left >= 2 * kKb && beside)
+      step(full, full, k0);
+    else if (left > kKb && beside)
+      step(full, half, k0);
+    else if (left >= kKb)
+      step(full, none, k0);
     else
-      step(std::integral_constant<int, 64>{}, k0);
+      step(half, none, k0);
   }
 }
 

@@ -368,6 +368,43 @@ def test_sweep_at_pivot_block_edges(spots, num_scen):
         assert np.linalg.norm(x[s] - ref) <= 130 * 2.0 ** -24 * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("n,num_scen", [(1250, 20), (1340, 18), (700, 63)])
+def test_sweep_with_the_next_pivot_beside_the_update(n, num_scen, monkeypatch):
+    """From 4 096 tiles over the chunk's scenarios on, the update's launch also
+    inverts the next pivot block, in the order of the pivot's own launch: x_s of
+    the first iteration equals, bit for bit, that of a set-up in chunks of one
+    scenario, with a last block of 128 (npad = 1 280) and of 64 (1 344, 704)."""
+    import paper_2304_14568_amd as A
+    nb = (n + 63) // 64
+    assert nb * (nb + 1) // 2 * num_scen >= 4096 > nb * (nb + 1) // 2
+    rng = np.random.default_rng(n)
+    m, per = 3 * n, 6
+    As = [synth.Csr(row_ptr=np.arange(0, per * m + 1, per, dtype=np.int64),
+                    col=np.sort(rng.integers(0, n // per, (m, per)) + n // per * np.arange(per), axis=1).astype(np.int32).ravel(),
+                    val=rng.uniform(0.2, 1.0, per * m).astype(np.float32)) for _ in range(num_scen)]
+    P = synth.Problem(m=m, n=n, A=As, prob=np.full(num_scen, 1 / num_scen), struct_id=(np.arange(m) % 2).astype(np.uint8),
+                      struct_weight=np.array([0.5, 1.0]), presc=rng.uniform(0.5, 1.5, m), lb=np.zeros(n),
+                      ub=np.full(n, 10.0))
+    W = wls.from_problem(P)
+    xs = []
+    for chunk_mb in ("", "1"):
+        if chunk_mb:
+            monkeypatch.setenv("ADMMBB_DENSE_CHUNK_MB", chunk_mb)
+        with A.Solver(P, xupdate="dense", rho=1.0) as S:
+            S.iterate(1)
+            st = S.get_state()
+            xs.append(np.asarray(st["d"]).reshape(num_scen, n) + np.asarray(st["z"])[None, :])
+    assert np.array_equal(xs[0], xs[1])
+    for s in (0, num_scen - 1):
+        a = W.A[s].toarray()
+        B = a.T @ ((W.c[s] * W.w)[:, None] * a) + 0.5 * np.eye(n)
+        ref = np.linalg.solve(B, a.T @ (W.c[s] * W.w * W.p))
+        # the inverse is stored in fp32: entries 2^-24 off, the products' sum
+        # |M||b| of a row bounded by ||M||_inf ||b||_inf
+        M = np.abs(np.linalg.inv(B)) @ np.abs(a.T @ (W.c[s] * W.w * W.p))
+        assert np.all(np.abs(xs[0][s] - ref) <= 2.0 ** -23 * M + 2.0 ** -23 * np.abs(ref).max())
+
+
 def test_dense_set_up_and_iterations_are_bitwise_reproducible(monkeypatch):
     """The Gram tiles are summed in 64-bit fixed point (exact, independent of
     the order of the atomics) and everything after them in fixed order, so two
