@@ -82,8 +82,8 @@ struct admm_ctx {
   float *d_b = nullptr, *d_dinv = nullptr, *d_z = nullptr, *d_lb = nullptr, *d_ub = nullptr;
   float *d_pvec = nullptr, *d_pvec2 = nullptr, *d_pvec3 = nullptr, *d_mvec = nullptr;
   int mvec_scen = 1;        // m-vectors of the largest patient that d_mvec holds
-  void* d_dose = nullptr;   // staging of the dose statistics, grown to the largest call
-  size_t dose_bytes = 0;
+  void* d_stage = nullptr;  // staging of the dose statistics and spot features, grown to the largest call
+  size_t stage_bytes = 0;
   float* d_tmax = nullptr;  // kAbsMaxBlocks partial maxima of the transpose product's input
   double* d_dprev = nullptr;
   float* d_part = nullptr;
@@ -219,7 +219,7 @@ struct admm_ctx {
     if (ev_a) (void)hipEventDestroy(ev_a);
     if (ev_b) (void)hipEventDestroy(ev_b);
     for (void* p : allocs) (void)hipFree(p);
-    if (d_dose) (void)hipFree(d_dose);
+    if (d_stage) (void)hipFree(d_stage);
     if (h_ps) (void)hipHostFree(h_ps);
     if (h_progress) (void)hipHostFree(const_cast<uint32_t*>(h_progress));
     if (h_scr) (void)hipHostFree(h_scr);
@@ -266,6 +266,20 @@ struct admm_ctx {
     pa.tin = t;
     pa.tmax = d_tmax;
     pass_launch(PASS_RMATVEC, pa, tile_begin, tile_count);
+  }
+
+  void* staging(size_t bytes) {
+    if (bytes > stage_bytes) {
+      if (d_stage) {
+        check(hipStreamSynchronize(stream), "sync");
+        (void)hipFree(d_stage);
+        d_stage = nullptr;
+        stage_bytes = 0;
+      }
+      check(hipMalloc(&d_stage, bytes), "hipMalloc");
+      stage_bytes = bytes;
+    }
+    return d_stage;
   }
 
   PassArgs pass_args(const MatDev& m) const {
@@ -1484,38 +1498,28 @@ admm_status admm_spot_features(admm_ctx* ctx, int32_t patient, const uint8_t* vo
   GUARD_BEGIN
   ctx->ensure_forward_tuned();
   const int n = pt.n, m = pt.m, N = pt.num_scen;
-  // indicator vectors of targets, organs at risk and all voxels
-  std::vector<float> ind(static_cast<size_t>(3) * m);
-  for (int i = 0; i < m; ++i) {
-    ind[i] = voxel_class[i] == 1 ? 1.0f : 0.0f;
-    ind[static_cast<size_t>(m) + i] = voxel_class[i] == 2 ? 1.0f : 0.0f;
-    ind[static_cast<size_t>(2) * m + i] = 1.0f;
-  }
-  float* d_ind = nullptr;
-  check(hipMalloc(reinterpret_cast<void**>(&d_ind), sizeof(float) * ind.size()), "hipMalloc");
+  // column sums over targets, organs at risk and all voxels: each class's
+  // indicator is formed on the device and multiplied through all scenarios at
+  // once (a pass, a reduction and a copy for each scenario and class took some
+  // 0.9 ms more at 13 scenarios); the stacked sums go to d_q, scratch between calls
+  const Scen& s0 = ctx->H.scen[pt.scen_begin];
+  const Scen& s1 = ctx->H.scen[pt.scen_begin + N - 1];
   std::vector<float> col(static_cast<size_t>(3) * N * n);
-  try {
-    check(hipMemcpy(d_ind, ind.data(), sizeof(float) * ind.size(), hipMemcpyHostToDevice), "H2D");
-    for (int s = 0; s < N; ++s) {
-      const Scen& sc = ctx->H.scen[pt.scen_begin + s];
-      for (int c = 0; c < 3; ++c) {
-        PassArgs pa = ctx->pass_args(ctx->mat32);
-        pa.objpart = nullptr;
-        ctx->rmatvec_launch(pa, d_ind + static_cast<size_t>(c) * m, m, sc.tile_begin, sc.tile_end - sc.tile_begin);
-        VecArgs va = ctx->vec_args(0);
-        va.out = ctx->d_pvec2 + pt.zvec_base;
-        launch_reduce(RED_RMAT, va, sc.blk_begin, sc.nblk, ctx->stream);
-        check(hipMemcpyAsync(col.data() + (static_cast<size_t>(c) * N + s) * n, va.out, sizeof(float) * n,
-                             hipMemcpyDeviceToHost, ctx->stream),
-              "D2H");
-      }
-    }
-    check(hipStreamSynchronize(ctx->stream), "sync");
-  } catch (...) {
-    (void)hipFree(d_ind);
-    throw;
+  uint8_t* cls = static_cast<uint8_t*>(ctx->staging(static_cast<size_t>(m)));
+  check(hipMemcpyAsync(cls, voxel_class, static_cast<size_t>(m), hipMemcpyHostToDevice, ctx->stream), "H2D");
+  for (int c = 0; c < 3; ++c) {
+    launch_class_indicator(cls, m, c + 1, ctx->d_mvec, ctx->stream);
+    PassArgs pa = ctx->pass_args(ctx->mat32);
+    pa.objpart = nullptr;
+    ctx->rmatvec_launch(pa, ctx->d_mvec, m, pt.tile_begin, pt.tile_end - pt.tile_begin);
+    VecArgs va = ctx->vec_args(0);
+    va.out = ctx->d_q;
+    launch_reduce(RED_RMAT_SCEN, va, s0.blk_begin, s1.blk_begin + s1.nblk - s0.blk_begin, ctx->stream);
+    check(hipMemcpyAsync(col.data() + static_cast<size_t>(c) * N * n, ctx->d_q + s0.vec_base, sizeof(float) * N * n,
+                         hipMemcpyDeviceToHost, ctx->stream),
+          "D2H");
   }
-  (void)hipFree(d_ind);
+  check(hipStreamSynchronize(ctx->stream), "sync");
   const int64_t vb = ctx->H.scen[pt.scen_begin].vec_base;
   for (int j = 0; j < n; ++j) {
     double ft_sum = 0, ft_min = 1e300, ft_max = -1e300, fo_sum = 0, fo_max = -1e300, mass_sum = 0, bsum = 0, gsum = 0;
@@ -1831,17 +1835,7 @@ admm_status admm_dose_stats(admm_ctx* ctx, int32_t patient, const double* x, con
   if (st != ADMM_OK) return st;
   GUARD_BEGIN
   const DoseStaging o(ctx->H.pat[patient], num_groups, nbins);
-  if (o.bytes > ctx->dose_bytes) {
-    if (ctx->d_dose) {
-      check(hipStreamSynchronize(ctx->stream), "sync");
-      (void)hipFree(ctx->d_dose);
-      ctx->d_dose = nullptr;
-      ctx->dose_bytes = 0;
-    }
-    check(hipMalloc(&ctx->d_dose, o.bytes), "hipMalloc");
-    ctx->dose_bytes = o.bytes;
-  }
-  dose_stats_queue(ctx, patient, x, voxel_group, ctx->d_dose, num_groups, nbins, dmax, counts, sums, maxes, dose_out);
+  dose_stats_queue(ctx, patient, x, voxel_group, ctx->staging(o.bytes), num_groups, nbins, dmax, counts, sums, maxes, dose_out);
   return ADMM_OK;
   GUARD_END(ctx)
 }

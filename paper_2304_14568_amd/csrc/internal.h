@@ -15,7 +15,8 @@ constexpr int kRegChunks = 4;       // 4-element chunks of a row kept in registe
 
 enum PassMode { PASS_GRAD = 0, PASS_CG = 1, PASS_OBJ = 2, PASS_MATVEC = 3, PASS_RMATVEC = 4 };
 enum ValKind { VAL_F32 = 0, VAL_BF16 = 1, VAL_F16 = 2 };
-enum RedMode { RED_HEAD = 0, RED_CG = 1, RED_NORMAL = 2, RED_RMAT = 3, RED_DUALINIT = 4 };
+// RED_RMAT: one scenario's column sums to out; RED_RMAT_SCEN: every scenario's at its place of the stacked n-vectors
+enum RedMode { RED_HEAD = 0, RED_CG = 1, RED_NORMAL = 2, RED_RMAT = 3, RED_DUALINIT = 4, RED_RMAT_SCEN = 5 };
 // LDS column accumulators of the fused pass: float atomics, double atomics, or
 // 64-bit fixed point (integer atomics, exact and order-independent sums).
 enum AccKind { ACC_F32 = 0, ACC_F64 = 1, ACC_FIX64 = 2 };
@@ -287,6 +288,8 @@ void launch_fill_f32(float* p, float v, int64_t count, hipStream_t st);
 constexpr int kAbsMaxBlocks = 256;
 void launch_absmax(const float* x, int64_t n, float* out, hipStream_t st);
 void launch_fill_f64(double* p, double v, int64_t count, hipStream_t st);
+// out[i] = 1 where cls[i] == which, or everywhere for which = 3, else 0
+void launch_class_indicator(const uint8_t* cls, int64_t m, int which, float* out, hipStream_t st);
 void launch_fill_u8(uint8_t* p, uint8_t v, int64_t count, hipStream_t st);
 int pass_smem_bytes(int nmax, int acc);
 int dose_hist_smem_bytes(int G, int nbins);

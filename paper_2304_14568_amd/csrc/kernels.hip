@@ -116,6 +116,8 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduce(VecArgs a, int blk_be
     } else if (mode == RED_DUALINIT) {
       // s = A_s^T c_s W (A_s z - p) = grad f_s(z) / 2
       a.y[vi] = static_cast<float>(-2.0 * s);
+    } else if (mode == RED_RMAT_SCEN) {
+      a.out[vi] = static_cast<float>(s);
     } else {
       a.out[j] = static_cast<float>(s);
     }
@@ -447,6 +449,16 @@ static void fill(T* p, T v, int64_t count, hipStream_t st) {
   int64_t nb = (count + kThreads - 1) / kThreads;
   if (nb > 4096) nb = 4096;
   hipLaunchKernelGGL(k_fill<T>, dim3(static_cast<unsigned>(nb)), dim3(kThreads), 0, st, p, v, count);
+}
+
+__global__ __launch_bounds__(256) void k_class_indicator(const uint8_t* __restrict__ cls, int64_t m, int which,
+                                                         float* __restrict__ out) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (i < m) out[i] = which == 3 || cls[i] == which ? 1.0f : 0.0f;
+}
+
+void launch_class_indicator(const uint8_t* cls, int64_t m, int which, float* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_class_indicator, dim3(static_cast<unsigned>((m + 255) / 256)), dim3(256), 0, st, cls, m, which, out);
 }
 
 __global__ __launch_bounds__(256) void k_absmax(const float* __restrict__ x, int64_t n, float* __restrict__ out) {

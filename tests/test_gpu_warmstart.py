@@ -127,6 +127,27 @@ def test_spot_features_parity():
 
 
 @pytest.mark.parametrize("xupdate", ["cg", "dense"])
+def test_spot_features_of_each_patient_between_iterations(xupdate):
+    """All scenarios' column sums of a class are formed at once, in the vector
+    that CG steps use: each patient of a batch (one scenario, 65 spots; three of
+    20) gets its own, and the iterates are the same with a call in between."""
+    import paper_2304_14568_amd as A
+    Ps = [synth.make_tiny(1, spots=(5, 13), num_scen=1), synth.make_tiny(2, spots=(4, 5), num_scen=3)]
+    zs = []
+    for call in (False, True):
+        with A.Solver(Ps, xupdate=xupdate, deterministic=1, **(dict(pass_threads=256, pass_unroll=1, format="csr")
+                                                               if xupdate == "cg" else {})) as S:
+            S.iterate(3)
+            if call:
+                for p, P in enumerate(Ps):
+                    ref = features.spot_features(wls.from_problem(P), P.struct_id)
+                    _close(S.spot_features(P.struct_id, p), ref, 1e-4, 1e-6)
+            S.iterate(3)
+            zs.append([S.z(p) for p in range(2)])
+    assert all(np.array_equal(a, b) for a, b in zip(*zs))
+
+
+@pytest.mark.parametrize("xupdate", ["cg", "dense"])
 def test_dual_consistent_warm_start_at_optimum(xupdate):
     """Restarting at x* with y_s = -grad f_s(x*) leaves every x-update at x*
     and the consensus step at x*: the stop rule holds within a few iterations."""
