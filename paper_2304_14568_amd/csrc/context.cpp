@@ -760,6 +760,21 @@ struct admm_ctx {
     pass_unroll = pcfg[0].unroll;
   }
 
+  // Workgroup size of the gradient pass where the tuner does not run.  A CU takes
+  // four workgroups of 512 threads, or eight of 256 up to 20 KiB of LDS each
+  // (1 706 spots): more than 1 024 tiles then run in one round instead of two.  A
+  // gradient of 13 scenarios of 707 spots takes 43.9 instead of 48.7 us, of 1 000
+  // spots 51.6 instead of 57.1 and of 1 493 spots 69.7 instead of 72.9; of 2 003
+  // spots, where the LDS leaves six of them, 112.5 instead of 109.9, and of five
+  // scenarios of 300 spots, whose few tiles run in one round of either size, 26.5
+  // instead of 25.2.
+  void dense_pass_threads() {
+    for (int p = 0; p < P; ++p) {
+      const Pat& pt = H.pat[p];
+      if (8 * pass_smem_bytes(pt.n, acc) <= 163840 && pt.tile_end - pt.tile_begin > 1024) pcfg[p].threads = 256;
+    }
+  }
+
   // Per patient, the workgroup size and row pipelining of the products other
   // than the CG operator: the fastest forward product (objective pass at z,
   // fp32 values) of 512 or 1024 threads, with or without pipelining, in the
@@ -1402,7 +1417,10 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
     if (o.pass_unroll) c->pass_unroll = o.pass_unroll;
     c->set_all_cfg();
     clk.mark("cached inverses");
-    if (!c->dense) c->autotune();  // the dense x-update does not run the CG pass per iteration
+    if (!c->dense)
+      c->autotune();
+    else if (!o.pass_threads)
+      c->dense_pass_threads();  // the dense x-update does not run the CG pass per iteration
     check(hipEventCreate(&c->ev_a), "hipEventCreate");
     check(hipEventCreate(&c->ev_b), "hipEventCreate");
     check(hipStreamSynchronize(c->stream), "setup sync");

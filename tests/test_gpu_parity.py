@@ -287,3 +287,31 @@ def test_gradient_and_objective_at_column_group_edges(spots):
             assert abs(f - fr) <= 1e-7 * fr
             assert np.all(np.abs(g - gr) <= 1e-6 * np.abs(gr).max())
             assert abs(S.objective(x) - fr) <= 1e-7 * fr
+
+
+@pytest.mark.parametrize("n,num_scen,threads", [(200, 3, 256), (1706, 3, 256), (1707, 3, 512), (200, 2, 512)])
+def test_gradient_workgroup_size_of_a_dense_context(n, num_scen, threads):
+    """Without the tuner, 256 threads where eight workgroups share a CU's LDS (up
+    to 1 706 spots) and there are more than 1 024 tiles (of 8 192 elements here).
+    The column sums are exact, so the gradient has the bits of either size."""
+    rng = np.random.default_rng(n)
+    m, per = 31000, 96
+    As = [synth.Csr(row_ptr=np.arange(0, per * m + 1, per, dtype=np.int64),
+                    col=(rng.integers(0, n // per, (m, per)) + n // per * np.arange(per)).astype(np.int32).ravel(),
+                    val=rng.uniform(0.2, 1.0, per * m).astype(np.float32)) for _ in range(num_scen)]
+    P = synth.Problem(m=m, n=n, A=As, prob=np.full(num_scen, 1 / num_scen), struct_id=(np.arange(m) % 2).astype(np.uint8),
+                      struct_weight=np.array([0.5, 1.0]), presc=rng.uniform(0.5, 1.5, m), lb=np.zeros(n),
+                      ub=np.full(n, 10.0))
+    W = wls.from_problem(P)
+    x = rng.uniform(0.0, 1.0, n).astype(np.float32).astype(np.float64)
+    out = []
+    for t in (0, 256, 512):
+        with _solver(P, xupdate="dense", pass_threads=t) as S:
+            if t == 0:
+                assert S.tuning(0)["threads"] == threads
+            out.append(S.gradient(x))
+    fr, gr = wls.objective(W, x), wls.gradient(W, x)
+    assert np.all(np.abs(out[0][0] - gr) <= 1e-6 * np.abs(gr).max()) and abs(out[0][1] - fr) <= 1e-7 * fr
+    for g, f in out[1:]:
+        assert np.array_equal(g, out[0][0])
+        assert abs(f - out[0][1]) <= m * num_scen * 2.0 ** -52 * f  # fp64 sums of m N terms in another order
