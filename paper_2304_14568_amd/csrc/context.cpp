@@ -458,8 +458,7 @@ struct admm_ctx {
         if (cs == pt.num_scen) gram_of = p;
       }
       launch_gram_finish(f, p, g0, cs, npad, pt.n, rho[p], accumulate_gsum ? 1 : 0, stream);
-      launch_sweep(f, cs, npad, stream);
-      launch_sweep_store(f, p, g0, cs, npad, stream);
+      launch_sweep(f, p, g0, cs, npad, stream);
     }
     check(hipGetLastError(), "factor launch");
     factored_rho[p] = rho[p];

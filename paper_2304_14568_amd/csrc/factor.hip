@@ -18,7 +18,8 @@
 //        A_ij -= U_i R_j off the block row and column,
 //        A_:K = U, A_K: = U^T, A_KK = -P;
 //     after the last block A = -B_s^-1.  The sweep matrix stays symmetric, so
-//     only its upper 64 x 64 tiles are updated (half the work).  k_sweep_store writes M_s = B_s^-1 in fp32.
+//     only its upper 64 x 64 tiles are updated (half the work).  The last
+//     step stores M_s = B_s^-1 in fp32.
 //  4. k_gq_pack: sum_s G_s rounded to 48 bits for the objective tiles.
 //  5. every iteration, three launches: k_dense_x (x_s = M_s c_s tile by tile,
 //     the previous iteration's stopping test in one workgroup per patient), k_xzres (the
@@ -908,6 +909,20 @@ __device__ __forceinline__ void sweep_next_pivot(const FactorArgs& f, int npad, 
   sweep_pivot_block<KBN>(pt, lds, f.P + static_cast<int64_t>(g) * kKb * kKb);
 }
 
+// A 64 x 64 tile of M_s in LDS (rows kLdM apart) to its stored order.  Thread t of
+// the x-update holds the 4 x 4 block of rows 4 (t / 16) .. + 3 and columns
+// 4 (t % 16) .. + 3 as four float4 (row k = 0..3 of the block); float4 k of
+// thread t is stored at k * 256 + t, so that every wave load instruction of
+// the x-update reads 1 KiB contiguous.
+constexpr int kLdM = kFb + 4;
+__device__ __forceinline__ void store_xtile(float* __restrict__ dst, const float* tile) {
+  const int t = threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    *reinterpret_cast<float4*>(dst + 4 * (k * 256 + t)) =
+        *reinterpret_cast<const float4*>(tile + (4 * (t >> 4) + k) * kLdM + 4 * (t & 15));
+}
+
 // Rank-KB update A_ij -= U_i R_j of one upper 64 x 64 tile off the pivot row and
 // column, whose tiles are replaced by the panels.  Waves 2 x 2, 32 rows and
 // columns each, on the fp64 MFMA: the accumulators start from -A_ij, the panels
@@ -921,8 +936,13 @@ __device__ __forceinline__ void sweep_next_pivot(const FactorArgs& f, int npad, 
 // (KBN columns; 0: none) in registers, in the same order of products, and invert
 // it beside the other tiles' work: two inversions of 13 scenarios of 2 003 spots
 // and a warm start's other work 9.57 -> 8.74 ms.
-template <int KB, int KBN>
-__global__ __launch_bounds__(256, 4) void k_sweep_update(FactorArgs f, int npad, int k0, int nscen) {
+//
+// LAST: the last step's tiles are the inverse's, rounded to fp32 and stored in the
+// x-update's order instead of going back to A (a kernel that did so afterwards
+// took 109 us at 13 scenarios of 2 003 spots; the step itself 149 -> 140).
+template <int KB, int KBN, bool LAST>
+__global__ __launch_bounds__(256, 4) void k_sweep_update(FactorArgs f, int npad, int k0, int nscen, int patient,
+                                                         int scen_begin) {
   constexpr int MT = kFb, kLd = MT + 16, kSlab = 16;
   constexpr int W = MT / 32;                 // 16-wide groups of a wave
   constexpr int kQ = kSlab * MT / 2 / 256;   // double2 per thread, slab and panel
@@ -953,6 +973,22 @@ __global__ __launch_bounds__(256, 4) void k_sweep_update(FactorArgs f, int npad,
   const double* Ut = f.U + static_cast<int64_t>(g) * f.npmax * kKb;
   const double* R = f.R + static_cast<int64_t>(g) * f.npmax * kKb;
   const bool rowK = i0 / kKb == k0 / kKb, colK = j0 / kKb == k0 / kKb;
+  float* Mt = nullptr;  // the stored tile, formed in LDS first
+  float* mt = reinterpret_cast<float*>(lds);
+  if constexpr (LAST) {
+    Mt = f.Mp + f.scen[scen_begin + g].mpack_off + tile_index(bi, bj, f.pat[patient].nbk) * kFb * kFb;
+    if (colK) {  // M = -A: P, or -U
+      const double* Pg = f.P + static_cast<int64_t>(g) * kKb * kKb;
+      for (int q = 0; q < kFb / 4; ++q) {
+        const int r = tid & 63, c = (tid >> 6) + 4 * q;
+        mt[r * kLdM + c] = static_cast<float>(rowK ? Pg[(j0 - k0 + c) * kKb + i0 - k0 + r]
+                                                   : -Ut[static_cast<int64_t>(j0 - k0 + c) * npad + i0 + r]);
+      }
+      __syncthreads();
+      store_xtile(Mt, mt);
+      return;
+    }
+  }
   if (rowK && colK) return;  // already -P
   if (KBN != 0 && i0 / kKb == k1 / kKb && j0 / kKb == k1 / kKb) return;
   if (rowK || colK) {
@@ -1049,6 +1085,18 @@ __global__ __launch_bounds__(256, 4) void k_sweep_update(FactorArgs f, int npad,
     stage((s + 1) & 1);
     __syncthreads();
   }
+  if constexpr (LAST) {
+#pragma unroll
+    for (int a = 0; a < W; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int b = 0; b < W; ++b)
+          mt[(wi + 16 * a + kk + 4 * r) * kLdM + wj + 16 * b + m] = static_cast<float>(acc[a][b][r]);
+    __syncthreads();
+    store_xtile(Mt, mt);
+    return;
+  }
 #pragma unroll
   for (int a = 0; a < W; ++a)
 #pragma unroll
@@ -1057,31 +1105,6 @@ __global__ __launch_bounds__(256, 4) void k_sweep_update(FactorArgs f, int npad,
 #pragma unroll
       for (int b = 0; b < W; ++b) *at_bytes(row + 16 * b, oa) = -acc[a][b][r];
     }
-}
-
-// Position of entry (r, c) inside a stored 64 x 64 tile of M_s.  Thread t of
-// the x-update holds the 4 x 4 block of rows 4 (t / 16) .. + 3 and columns
-// 4 (t % 16) .. + 3 as four float4 (row k = 0..3 of the block); float4 k of
-// thread t is stored at k * 256 + t, so that every wave load instruction of
-// the x-update reads 1 KiB contiguous.
-__host__ __device__ __forceinline__ int xtile_pos(int r, int c) {
-  return 4 * ((r & 3) * 256 + (r >> 2) * 16 + (c >> 2)) + (c & 3);
-}
-
-// packed M = -A (upper tiles) in fp32, for the chunk of scenarios starting at scen_begin
-__global__ __launch_bounds__(256) void k_sweep_store(FactorArgs f, int patient, int scen_begin, int npad) {
-  const Pat pt = f.pat[patient];
-  const Scen sc = f.scen[scen_begin + static_cast<int>(blockIdx.y)];
-  const int64_t nn = static_cast<int64_t>(npad) * npad;
-  const double* A = f.A + static_cast<int64_t>(blockIdx.y) * nn;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; idx < nn; idx += stride) {
-    const int i = static_cast<int>(idx / npad), j = static_cast<int>(idx % npad);
-    const int I = i / kFb, J = j / kFb;
-    if (I <= J)
-      f.Mp[sc.mpack_off + tile_index(I, J, pt.nbk) * kFb * kFb + xtile_pos(i % kFb, j % kFb)] =
-          static_cast<float>(-A[idx]);
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1097,7 +1120,7 @@ constexpr int kDppRor8 = 0x128;
 // the diagonal, b = T^T c_I (the tile's contribution to the rows of block J).
 // Thread t holds the 4 x 4 block at rows 4 rb, columns 4 cb (rb = t / 16,
 // cb = t % 16; four float4 loads, each a 1 KiB contiguous read per wave in
-// the stored order of xtile_pos), so both products use the registers as
+// the stored order of store_xtile), so both products use the registers as
 // loaded: the row sums are reduced over the 16 lanes of a DPP row, the column
 // sums over the wave's four rows by shuffles and over the four waves in
 // shared memory.  The tile table entry carries every address, so the tile
@@ -1624,7 +1647,7 @@ void launch_gram_finish(FactorArgs f, int patient, int scen_begin, int nscen, in
                      nscen, npad, n, rho, accumulate_gsum);
 }
 
-void launch_sweep(FactorArgs f, int nscen, int npad, hipStream_t st) {
+void launch_sweep(FactorArgs f, int patient, int scen_begin, int nscen, int npad, hipStream_t st) {
   const int n64 = npad / 64, nt = n64 * (n64 + 1) / 2;
   // The next pivot block goes beside the update where the update takes longer
   // than the pivot's chain within it (85 to 105 us, against 32 in a launch of its
@@ -1632,12 +1655,12 @@ void launch_sweep(FactorArgs f, int nscen, int npad, hipStream_t st) {
   // the scenarios, 104 + 31 against 127 us with 4 914, 147 + 32 against 157 us
   // with 6 864.
   const bool beside = static_cast<int64_t>(nt) * nscen >= 4096;
-  auto step = [&](auto kbc, auto kbn, int k0) {
+  auto step = [&](auto kbc, auto kbn, auto last, int k0) {
     constexpr int KB = decltype(kbc)::value, KBN = decltype(kbn)::value;
     if (k0 == 0 || !beside) hipLaunchKernelGGL(k_sweep_pivot<KB>, dim3(nscen), dim3(512), 0, st, f, npad, k0);
     hipLaunchKernelGGL(k_sweep_panel<KB>, dim3(n64, nscen), dim3(256), 0, st, f, npad, k0);
-    hipLaunchKernelGGL((k_sweep_update<KB, KBN>), dim3((nt + (KBN != 0 ? 1 : 0)) * nscen), dim3(256), 0, st, f, npad, k0,
-                       nscen);
+    hipLaunchKernelGGL((k_sweep_update<KB, KBN, decltype(last)::value>), dim3((nt + (KBN != 0 ? 1 : 0)) * nscen), dim3(256),
+                       0, st, f, npad, k0, nscen, patient, scen_begin);
   };
   constexpr std::integral_constant<int, kKb> full{};
   constexpr std::integral_constant<int, 64> half{};
@@ -1645,13 +1668,15 @@ void launch_sweep(FactorArgs f, int nscen, int npad, hipStream_t st) {
   for (int k0 = 0; k0 < npad; k0 += kKb) {
     const int left = npad - k0;
     if (left >= 2 * kKb && beside)
-      step(full, full, k0);
+      step(full, full, std::false_type{}, k0);
     else if (left > kKb && beside)
-      step(full, half, k0);
-    else if (left >= kKb)
-      step(full, none, k0);
+      step(full, half, std::false_type{}, k0);
+    else if (left > kKb)
+      step(full, none, std::false_type{}, k0);
+    else if (left == kKb)
+      step(full, none, std::true_type{}, k0);
     else
-      step(half, none, k0);
+      step(half, none, std::true_type{}, k0);
   }
 }
 
@@ -1660,13 +1685,6 @@ void launch_gq_pack(const double* Gp, uint32_t* Gq, int64_t ntiles, hipStream_t 
   const int64_t n = ntiles * 4096;
   const unsigned grid = static_cast<unsigned>(std::min<int64_t>((n + 255) / 256, 65536));
   hipLaunchKernelGGL(k_gq_pack, dim3(grid), dim3(256), 0, st, Gp, Gq, n);
-}
-
-void launch_sweep_store(FactorArgs f, int patient, int scen_begin, int nscen, int npad, hipStream_t st) {
-  int64_t nb = (static_cast<int64_t>(npad) * npad + 255) / 256;
-  if (nb > 4096) nb = 4096;
-  hipLaunchKernelGGL(k_sweep_store, dim3(static_cast<unsigned>(nb), nscen), dim3(256), 0, st, f, patient,
-                     scen_begin, npad);
 }
 
 void launch_xsym(const FactorArgs& f, const double* c, int njobs, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {

@@ -311,8 +311,7 @@ void launch_gram_tiles(const MatDev& m, const double* rw64, const Scen* scen, in
                        int ld, hipStream_t st);
 void launch_gram_finish(FactorArgs f, int patient, int scen_begin, int nscen, int npad, int n, double rho,
                         int accumulate_gsum, hipStream_t st);
-void launch_sweep(FactorArgs f, int nscen, int npad, hipStream_t st);
-void launch_sweep_store(FactorArgs f, int patient, int scen_begin, int nscen, int npad, hipStream_t st);
+void launch_sweep(FactorArgs f, int patient, int scen_begin, int nscen, int npad, hipStream_t st);
 void launch_gq_pack(const double* Gp, uint32_t* Gq, int64_t ntiles, hipStream_t st);
 void launch_xsym(const FactorArgs& f, const double* c, int njobs, hipStream_t st, hipEvent_t e0 = nullptr,
                  hipEvent_t e1 = nullptr);
