@@ -218,8 +218,8 @@ def main():
     ap.add_argument("--calib-copy-mib", type=int, default=0,
                     help="first copy this many MiB device-to-device (a reference kernel for HBM byte counters)")
     ap.add_argument("--graph", action="store_true",
-                    help="replay each iteration from a captured HIP graph in the throughput region "
-                         "(the instrumented region always launches directly)")
+                    help="with --xupdate cg, replay each iteration from a captured HIP graph in the throughput "
+                         "region (the instrumented region and the dense iterations always launch directly)")
     ap.add_argument("--cpu-scaling", default="",
                     help="only time the FP64 oracle (set-up and iterations to the 1e-5 gap) on the first N "
                          "scenarios of the workload for each N of this comma-separated list, and on the "
@@ -294,7 +294,7 @@ def main():
         # x-update roofline: every launch reads each scenario's packed fp32
         # inverse once (upper 64 x 64 tiles of M_s, 16 KiB each) and its fp64
         # right-hand side; in the three-launch order the same launch (k_dense_x)
-        # runs the previous iteration's stopping test in its workgroup 0
+        # runs the previous iteration's stopping test in its first workgroup
         nb = (P.n + 63) // 64
         tiles = nb * (nb + 1) // 2
         bytes_per_launch = float(P.num_scen * (tiles * 64 * 64 * 4 + 8 * P.n))

@@ -1,5 +1,5 @@
 // Host runtime: device state of a context, the launch sequence of one ADMM-BB
-// iteration (captured once into a HIP graph and replayed), the PGD loop and the
+// iteration (the CG path's captured once into a HIP graph and replayed), the PGD loop and the
 // extern "C" entry points of include/admmbb.h.
 #include <hip/hip_runtime.h>
 
@@ -442,7 +442,7 @@ struct admm_ctx {
   // chunks also add up the packed sum_s G_s of the objective.  The Gram matrices
   // do not depend on the penalty, so where the last patient built here fits one
   // chunk, d_G still holds them and a new penalty only repeats the sweep (13
-  // scenarios of 2 003 spots: 3.7 instead of 7.6 ms).
+  // scenarios of 2 003 spots: 3.1 instead of 7.0 ms).
   void factorize(int p, bool accumulate_gsum) {
     const Pat& pt = H.pat[p];
     const int npad = pt.npad;

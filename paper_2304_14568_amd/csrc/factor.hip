@@ -5,7 +5,7 @@
 //
 //  1. G_s = A_s^T diag(c_s w) A_s, upper 64 x 64 tiles: lists of the rows
 //     that reach each tile (k_gram_rows, k_gram_scan), then one workgroup per
-//     tile adds its rows' products in LDS (k_gram_tiles).  k_gram (one fp64
+//     tile multiplies its rows on the fp64 MFMA (k_gram_tiles).  k_gram (one fp64
 //     atomic per product, one wave per stored row) is the fallback when the
 //     lists do not fit in device memory.
 //  2. k_gram_finish: the upper tiles of the sweep work matrix
