@@ -133,6 +133,7 @@ struct admm_ctx {
   int64_t pass_count = 0;
   // dense x-update (cached inverses)
   bool dense = false;
+  double* d_gbig = nullptr;  // per scenario: a power of two no entry of its Gram matrix reaches
   double *d_G = nullptr, *d_Aw = nullptr, *d_Gp = nullptr, *d_g0 = nullptr;
   double *d_Pb = nullptr, *d_U = nullptr, *d_R = nullptr, *d_fpart = nullptr;
   float* d_Mp = nullptr;
@@ -373,11 +374,20 @@ struct admm_ctx {
     return f;
   }
 
+  // The smallest power of two above max_j (G_s)_jj, a bound of every entry of G_s
+  // and of its partial sums; 0 where twice that is beyond fp64.
+  double gram_bound(int g) const {
+    int e = 0;
+    (void)std::frexp(H.gdiag_max[static_cast<size_t>(g)], &e);  // gdiag_max = f 2^e, f < 1
+    return std::isfinite(H.gdiag_max[static_cast<size_t>(g)]) && e < 1023 ? std::ldexp(1.0, e) : 0.0;
+  }
+
   // Gram matrices G_s of the scenarios [g0, g0 + cs) of patient pt into the
   // chunk buffer (the upper tiles are what the next steps read): per-tile row
   // lists and one fp64 MFMA accumulation per tile; where the lists do not fit
-  // in device memory, one fp64 atomic per product (also taken when the
-  // environment sets ADMMBB_GRAM_ATOMIC, which tests use to compare the two).
+  // in device memory, or a diagonal entry leaves no room in fp64 for the sums'
+  // bound, one fp64 atomic per product (also taken when the environment sets
+  // ADMMBB_GRAM_ATOMIC, which tests use to compare the two).
   // The lists live in the sweep's work matrices, which are free until the Gram
   // matrices are done, or in a buffer of their own where those are too small
   // (few spots: a list entry takes 16 bytes, a work matrix 8 npad^2).
@@ -392,14 +402,15 @@ struct admm_ctx {
     const int64_t ntl = static_cast<int64_t>(nb) * (nb + 1) / 2, nt = ntl * cs;
     auto up = [](int64_t b) { return (b + 255) & ~int64_t{255}; };
     // waves that list a scenario's rows: 8 192 over the chunk's scenarios, at
-    // most one per 64 voxels, and few enough that their counts take at most an
-    // eighth of the work matrices
+    // most one per 64 voxels, and at most 2 048 (their counts then take (1 + 1 / nb)
+    // / 8 of the work matrices)
     const int nchunk = static_cast<int>(
         std::max<int64_t>(1, std::min<int64_t>({8192 / cs > 256 ? 8192 / cs : 256, 2048, (pt.m + 63) / 64})));
     const int64_t b_row = up(4 * static_cast<int64_t>(pt.m) * cs);
     const int64_t b_cnt = up(4 * nt * nchunk), b_tot = up(4 * nt), b_off = up(8 * (nt + 1));
     const int64_t room = 8 * nn * cs;
     bool lists = std::getenv("ADMMBB_GRAM_ATOMIC") == nullptr;
+    for (int s = 0; s < cs; ++s) lists = lists && gram_bound(g0 + s) > 0.0;
     char* base = reinterpret_cast<char*>(d_Aw);
     int64_t used = b_row + b_cnt + b_tot + b_off;
     if (lists && used > room) {
@@ -425,7 +436,8 @@ struct admm_ctx {
         list = static_cast<GramEntry*>(bl.p);
       lists = list != nullptr;
       if (lists)
-        launch_gram_tiles(csr32, d_rw64, d_scen, g0, cs, nb, pt.m, row_of, nchunk, cnt, off, list, d_G, pt.npad, stream);
+        launch_gram_tiles(csr32, d_rw64, d_scen, g0, cs, nb, pt.m, row_of, nchunk, cnt, off, list, d_gbig + g0,
+                          d_G, pt.npad, stream);
     }
     if (!lists) {
       (void)hipGetLastError();  // the failed allocation
@@ -1265,6 +1277,9 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
         std::copy(H.g0[p].begin(), H.g0[p].end(), g0all.begin() + H.pat[p].zvec_base);
       c->d_g0 = c->upload(g0all);
       c->d_rw64 = c->upload(H.rw64);
+      std::vector<double> gbig(H.scen.size());
+      for (size_t g = 0; g < gbig.size(); ++g) gbig[g] = c->gram_bound(static_cast<int>(g));
+      c->d_gbig = c->upload(gbig);
       c->factored_rho.assign(num_patients, 0.0);
     }
     clk.mark("dense buffers and tables");

@@ -5,7 +5,8 @@
 //
 //  1. G_s = A_s^T diag(c_s w) A_s, upper 64 x 64 tiles: lists of the rows
 //     that reach each tile (k_gram_rows, k_gram_scan), then one workgroup per
-//     tile multiplies its rows on the fp64 MFMA (k_gram_tiles).  k_gram (one fp64
+//     tile multiplies its rows on the fp64 MFMA and adds them up without loss
+//     (k_gram_tiles).  k_gram (one fp64
 //     atomic per product, one wave per stored row) is the fallback when the
 //     lists do not fit in device memory.
 //  2. k_gram_finish: the upper tiles of the sweep work matrix
@@ -262,21 +263,32 @@ __global__ __launch_bounds__(1024) void k_gram_scan(const int32_t* __restrict__ 
 // block's times its weight in fp64; then each wave adds all 32 rows to its 32 x
 // 32 quarter of the tile, leaving out the 16-column groups that no row of a
 // step uses (listed in voxel order, four rows need a third of the products; in
-// the order of the stored rows, four fifths).  The next rows are requested
-// before the products of the current ones, and four workgroups per CU hide the
-// rest of the loads' latency, which bounds the kernel: 5.3 ms for 13 scenarios
-// of 2 981 spots (1.2 ms of MFMA issue), 10.3 ms with a whole tile per wave and
-// two waves per SIMD, 6.5 ms without the skipped groups.  One product at a time
-// through LDS atomics, with one row at a time per wave, took 17.7 ms.  Padding
+// the order of the stored rows, four fifths).
+//
+// The products of four rows start from zero, and their sums are added without
+// loss: `hi` starts from gbig[s], a power of two above every entry of G_s, so
+// t = hi + d rounds once and d - (t - hi) is exactly what it dropped, which `lo`
+// collects (hi - big is exact at the end).  An entry is then one rounding from
+// its four-row sums, however many rows it has: the diagonal of a patient's matrix
+// (1 500 to 2 300 rows) is 4.8e-17 off (relative, root mean square), where 64-bit
+// fixed-point sums of one product at a time through LDS atomics (17.7 ms at 13
+// scenarios of 2 981 spots) leave 6e-17 to 9e-17 and a running fp64 sum over the
+// list 1.2e-15 to 1.5e-15.  The residuals and their
+// registers (three workgroups per CU instead of four) cost 8.8 instead of 5.3
+// ms there, 3.7 instead of 2.3 ms at 1 700 spots; four workgroups
+// with spills (12 ms) or eight waves with an eighth of the tile each (9 to 12 ms)
+// are no faster.
+// The next rows are requested before the products of the current ones.  Padding
 // (value 0, the last column repeated) is left out.
 constexpr int kGramWaves = 4;
 constexpr int kGramRows = 8;       // listed rows a wave expands at a time
 constexpr int kGramLd = kFb + 16;  // row stride: four rows that one load reads start 32 (16) banks apart
 
-__global__ __launch_bounds__(64 * kGramWaves, 4) void k_gram_tiles(MatDev mat, const double* __restrict__ rw64,
+__global__ __launch_bounds__(64 * kGramWaves, 3) void k_gram_tiles(MatDev mat, const double* __restrict__ rw64,
                                                                 const Scen* __restrict__ scen, int g0, int nb,
                                                                 const int64_t* __restrict__ off,
                                                                 const GramEntry* __restrict__ list,
+                                                                const double* __restrict__ gbig,
                                                                 double* __restrict__ G, int ld) {
   constexpr int kStep = kGramWaves * kGramRows;
   __shared__ __align__(16) double bufI[kStep * kGramLd];
@@ -300,11 +312,15 @@ __global__ __launch_bounds__(64 * kGramWaves, 4) void k_gram_tiles(MatDev mat, c
   const int wu = __builtin_amdgcn_readfirstlane(w);
   const int qi = 32 * (wu >> 1), qj = 32 * (wu & 1);  // the wave's quarter
   const int64_t l0 = off[s * ntiles + t], le = off[s * ntiles + t + 1];
-  v4d acc[2][2];
+  const double big = gbig[s];
+  v4d hi[2][2], lo[2][2];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int b = 0; b < 2; ++b) {
+      hi[a][b] = v4d{big, big, big, big};
+      lo[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
+    }
   // one row's share of a lane: of either segment, the chunk (four elements,
   // aligned, so a neighbouring block's may be among them) at its place of the
   // eight, and the one eight further on
@@ -404,8 +420,12 @@ __global__ __launch_bounds__(64 * kGramWaves, 4) void k_gram_tiles(MatDev mat, c
       for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b)
-          if ((ui >> a & 1u) && (uj >> b & 1u))
-            acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+          if ((ui >> a & 1u) && (uj >> b & 1u)) {
+            const v4d d = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], v4d{0.0, 0.0, 0.0, 0.0}, 0, 0, 0);
+            const v4d t = hi[a][b] + d;
+            lo[a][b] += d - (t - hi[a][b]);  // exact: hi >= big >= d
+            hi[a][b] = t;
+          }
     }
     __syncthreads();  // the next rows overwrite the buffers
   }
@@ -418,7 +438,8 @@ __global__ __launch_bounds__(64 * kGramWaves, 4) void k_gram_tiles(MatDev mat, c
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = qi + 16 * a + kk + 4 * r, col = qj + 16 * b + m;
-        if (I != J || row <= col) Gs[static_cast<int64_t>(I * kFb + row) * ld + J * kFb + col] = acc[a][b][r];
+        if (I != J || row <= col)
+          Gs[static_cast<int64_t>(I * kFb + row) * ld + J * kFb + col] = (hi[a][b][r] - big) + lo[a][b][r];
       }
 }
 
@@ -1630,13 +1651,13 @@ void launch_gram_lists(const MatDev& m, const Scen* scen, int g0, int nscen, int
 }
 
 void launch_gram_tiles(const MatDev& m, const double* rw64, const Scen* scen, int g0, int nscen, int nb, int ms,
-                       const int32_t* row_of, int nchunk, uint32_t* cnt, const int64_t* off, GramEntry* list, double* G,
-                       int ld, hipStream_t st) {
+                       const int32_t* row_of, int nchunk, uint32_t* cnt, const int64_t* off, GramEntry* list,
+                       const double* gbig, double* G, int ld, hipStream_t st) {
   const int nt = nb * (nb + 1) / 2;
   hipLaunchKernelGGL(k_gram_rows<true>, dim3(nchunk, nscen), dim3(64), 4 * nt, st, m, scen, g0, nb, row_of, ms, nchunk,
                      cnt, off, list);
-  hipLaunchKernelGGL(k_gram_tiles, dim3(nt, nscen), dim3(64 * kGramWaves), 0, st, m, rw64, scen, g0, nb, off, list, G,
-                     ld);
+  hipLaunchKernelGGL(k_gram_tiles, dim3(nt, nscen), dim3(64 * kGramWaves), 0, st, m, rw64, scen, g0, nb, off, list,
+                     gbig, G, ld);
 }
 
 void launch_gram_finish(FactorArgs f, int patient, int scen_begin, int nscen, int npad, int n, double rho,

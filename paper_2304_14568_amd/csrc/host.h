@@ -91,6 +91,7 @@ struct Packed {
   std::vector<double> b64;        // the same in fp64 (dense x-update right-hand sides)
   std::vector<float> dinv;        // Jacobi inverse diagonal (stacked), filled when requested
   std::vector<float> gdiag;       // (A_s^T c_s W A_s)_jj per scenario (stacked)
+  std::vector<double> gdiag_max;  // per scenario: max_j (A_s^T c_s W A_s)_jj in fp64
   std::vector<double> gdiag_mean; // per patient: mean over scenarios and spots of (A_s^T c_s W A_s)_jj
   std::vector<std::vector<double>> g0;  // per patient: 2 sum_s b_s
   std::vector<float> lb, ub;      // per patient stacked

@@ -298,7 +298,7 @@ void launch_gram(const MatDev& m, const double* rw64, const Scen& sc, double* G,
 // nchunk waves per scenario (launch_gram_lists counts: row_of[nscen * ms], ms the
 // number of voxels, cnt[nscen * nchunk * nt] and tot[nscen * nt], off[nscen * nt
 // + 1] the lists' offsets), then filled and added up, one workgroup per tile and
-// scenario (launch_gram_tiles)
+// scenario (launch_gram_tiles; gbig[nscen]: a power of two above every entry)
 struct GramEntry {  // one stored row in a tile's list
   int32_t row;
   uint32_t c0;          // its first 4-element chunk
@@ -307,8 +307,8 @@ struct GramEntry {  // one stored row in a tile's list
 void launch_gram_lists(const MatDev& m, const Scen* scen, int g0, int nscen, int nb, int ms, int32_t* row_of,
                        int nchunk, uint32_t* cnt, int32_t* tot, int64_t* off, hipStream_t st);
 void launch_gram_tiles(const MatDev& m, const double* rw64, const Scen* scen, int g0, int nscen, int nb, int ms,
-                       const int32_t* row_of, int nchunk, uint32_t* cnt, const int64_t* off, GramEntry* list, double* G,
-                       int ld, hipStream_t st);
+                       const int32_t* row_of, int nchunk, uint32_t* cnt, const int64_t* off, GramEntry* list,
+                       const double* gbig, double* G, int ld, hipStream_t st);
 void launch_gram_finish(FactorArgs f, int patient, int scen_begin, int nscen, int npad, int n, double rho,
                         int accumulate_gsum, hipStream_t st);
 void launch_sweep(FactorArgs f, int patient, int scen_begin, int nscen, int npad, hipStream_t st);

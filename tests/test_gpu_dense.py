@@ -405,9 +405,42 @@ def test_sweep_with_the_next_pivot_beside_the_update(n, num_scen, monkeypatch):
         assert np.all(np.abs(xs[0][s] - ref) <= 2.0 ** -23 * M + 2.0 ** -23 * np.abs(ref).max())
 
 
+@pytest.mark.parametrize("m,per", [(20000, 64), (400, 40), (130, 13)])
+def test_gram_sums_are_those_of_more_than_64_bits(m, per):
+    """The diagonal of the cached Gram matrix, read through the dense form of
+    the projected gradient (f of a unit vector with zero prescriptions is G_jj,
+    every other product zero), against sums in extended precision: some 9 800,
+    120 and 13 rows of weights and squares over five decades.  G_jj itself is one
+    rounding to fp64, at most 2^-53 relative; a row's own roundings add less than
+    that over 13 rows and average out over more, where a running fp64 sum of
+    9 800 rows is off by 28 times as much."""
+    import paper_2304_14568_amd as A
+    n = 130
+    rng = np.random.default_rng(m)
+    col = np.sort(np.argsort(rng.random((m, n)), axis=1)[:, :per], axis=1).astype(np.int32)
+    val = np.exp(rng.uniform(-6, 0, (m, per))).astype(np.float32)
+    w, c = np.array([0.3, 1.0]), 0.7
+    P = synth.Problem(m=m, n=n, A=[synth.Csr(row_ptr=np.arange(0, m * per + 1, per, dtype=np.int64), col=col.ravel(),
+                                             val=val.ravel())],
+                      prob=np.array([c]), struct_id=(np.arange(m) % 2).astype(np.uint8), struct_weight=w,
+                      presc=np.zeros(m), lb=np.zeros(n), ub=np.full(n, np.inf))
+    rw = (np.float64(c) * w)[P.struct_id].astype(np.longdouble)
+    err = []
+    with A.Solver(P, xupdate="dense") as S:
+        for j in range(n):
+            r, k = np.nonzero(col == j)
+            v = val[r, k].astype(np.longdouble)
+            want = np.sum(np.sort(rw[r] * v * v))
+            x0 = np.zeros(n)
+            x0[j] = 1.0
+            got = np.longdouble(S.pgd(0, x0, alpha=1.0, max_iter=0)[1]["obj"])
+            err.append(float((got - want) / want))
+    assert np.sqrt(np.mean(np.square(err))) <= 2.0 ** -53
+
+
 def test_dense_set_up_and_iterations_are_bitwise_reproducible(monkeypatch):
-    """The Gram tiles are summed in 64-bit fixed point (exact, independent of
-    the order of the atomics) and everything after them in fixed order, so two
+    """The Gram tiles are summed in the order of their row lists, and everything
+    after them in fixed order too, so two
     contexts of the same problem produce identical iterates."""
     import paper_2304_14568_amd as A
     monkeypatch.delenv("ADMMBB_GRAM_ATOMIC", raising=False)

@@ -149,8 +149,8 @@ def test_full_size_cg_forms_match_the_oracle_minimum(full, precision):
 
 def test_full_size_dense_pgd_matches_the_oracle_minimum(full):
     """PGD with the paper's relative-change stop (Sec. 2.1, here at 1e-11)
-    against the oracle's f*.  The Gram sums behind the dense PGD are exact
-    (fixed point), so the set-up and every PGD iterate are the same in every
+    against the oracle's f*.  The Gram sums behind the dense PGD are formed
+    in a fixed order, so the set-up and every PGD iterate are the same in every
     run: two runs stop at the same iteration with the same point."""
     import paper_2304_14568_amd as A
     P, W, fs, xs, cond = full
