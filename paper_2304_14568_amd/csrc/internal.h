@@ -68,6 +68,7 @@ struct Tile {
   float wmax;         // max over the tile's rows of c_s w_i sum_j |a_ij|
   float pmax;         // max over the tile's rows of c_s w_i p_i
   float cmax;         // max over columns of sum over the tile's rows of |a_ij|
+  float amax;         // max over the tile's rows of |a_ij|
   int32_t slice_begin; // sliced layout: index of the tile's first slice in MatDev::soff
 };
 

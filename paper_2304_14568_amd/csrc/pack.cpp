@@ -385,7 +385,7 @@ admm_status pack_problems(const admm_problem* probs, int num_patients, const adm
       auto round_up = [](double x) { return static_cast<float>(x * (1.0 + 1e-6)); };
       int64_t t_begin = 0, t_chunks = 0;
       int t_lanes = -1;
-      double wm = 0.0, pm = 0.0;
+      double wm = 0.0, pm = 0.0, am = 0.0;
       auto close_tile = [&](int64_t t_end) {
         double cm = 0.0;
         for (int32_t j : touched) {
@@ -401,6 +401,7 @@ admm_status pack_problems(const admm_problem* probs, int num_patients, const adm
         t.wmax = round_up(wm);
         t.pmax = round_up(pm);
         t.cmax = round_up(cm);
+        t.amax = round_up(am);
         r.tiles.push_back(t);
       };
       // rows are visited in the sorted order, so their source entries are
@@ -425,7 +426,7 @@ admm_status pack_problems(const admm_problem* probs, int num_patients, const adm
           close_tile(q);
           t_begin = q;
           t_chunks = 0;
-          wm = pm = 0.0;
+          wm = pm = am = 0.0;
         }
         t_lanes = lanes;
         const double wi = pr.struct_weight[pr.struct_id[i]];
@@ -438,6 +439,7 @@ admm_status pack_problems(const admm_problem* probs, int num_patients, const adm
         }
         wm = std::max(wm, cwi * rsum);
         pm = std::max(pm, cwi * pr.presc[i]);
+        am = std::max(am, static_cast<double>(rmax));
         const int64_t dst = r.nnz_base + 4 * static_cast<int64_t>(off);
         const float scl = rmax > 0.0f ? rmax : 1.0f;
         const int32_t* colp = A.col + b;

@@ -475,9 +475,11 @@ __global__ __launch_bounds__(NT) void k_pass(PassArgs a, int tile_begin) {
         vmax = fmaxf(vmax, fabsf(a.tin[a.mat.rorig[rb0 + r]]));
     }
   }
-  // fixed-point scale: every partial column sum of this tile, and every single
-  // contribution, is below cmax * (wmax * max|v| + pmax) < 2^50 / 2^F (for the
-  // transpose product: cmax * max|t_i|)
+  // fixed-point scale 2^F: every single contribution is below amax * (wmax *
+  // max|v| + pmax) < 2^50 / 2^F, which to_fixed takes, and every partial column sum
+  // of this tile below cmax * (...) < 2^62 / 2^F, which the accumulator takes (for
+  // the transpose product: times max|t_i|).  A scale from cmax and 2^50 alone
+  // loses a bit of every contribution whenever a tile's rows double.
   double fscale = 1.0, funscale = 1.0;
   if constexpr (kScatter && ACC == ACC_FIX64) {
 #pragma unroll
@@ -490,9 +492,9 @@ __global__ __launch_bounds__(NT) void k_pass(PassArgs a, int tile_begin) {
     const double tb = MODE == PASS_RMATVEC
                           ? static_cast<double>(vm)
                           : static_cast<double>(t.wmax) * vm + (MODE == PASS_GRAD ? static_cast<double>(t.pmax) : 0.0);
-    const double bound = 1.0625 * tb * static_cast<double>(t.cmax);
-    if (bound > 0.0 && isfinite(bound)) {
-      const int F = 49 - ilogb(bound);
+    const double each = 1.0625 * tb * static_cast<double>(t.amax), bound = 1.0625 * tb * static_cast<double>(t.cmax);
+    if (each > 0.0 && isfinite(bound)) {
+      const int F = min(49 - ilogb(each), 61 - ilogb(bound));
       fscale = ldexp(1.0, F);
       funscale = ldexp(1.0, -F);
     }

@@ -233,6 +233,31 @@ def test_pgd_gpu(tiny):
 
 
 @pytest.mark.parametrize("fmt", ["csr", "sell"])
+def test_fixed_point_keeps_a_faint_column(fmt):
+    """Column sums in fixed point, 1 024 rows a tile, one spot 2^-27 of the
+    others: its sums too are fp32 partials (2^-24) of contributions that lose
+    nothing to speak of, added and rounded once more (2^-24).  With the scale
+    from the largest column sum alone they were 2e-6 off."""
+    n, m = 8, 4096
+    rng = np.random.default_rng(0)
+    a = rng.uniform(0.5, 1.0, (m, n)).astype(np.float32)
+    a[:, 7] *= np.float32(2.0 ** -27)
+    P = synth.Problem(m=m, n=n, A=[synth.Csr(row_ptr=np.arange(0, m * n + 1, n, dtype=np.int64),
+                                             col=np.tile(np.arange(n, dtype=np.int32), m), val=a.ravel())],
+                      prob=np.ones(1), struct_id=np.zeros(m, np.uint8), struct_weight=np.ones(1), presc=np.zeros(m),
+                      lb=np.zeros(n), ub=np.full(n, 10.0))
+    t = rng.uniform(0.5, 1.0, m).astype(np.float32)
+    a64 = a.astype(np.float64)
+    with _solver(P, xupdate="cg", lds_acc=2, format=fmt) as S:
+        ref = a64.T @ t.astype(np.float64)
+        assert np.all(np.abs(S.rmatvec(t, 0) - ref) <= 2.0 ** -23 * ref)
+        # the gradient's t_i are rounded to fp32 first: 2^-24 more
+        g, _ = S.gradient(np.ones(n))
+        ref = 2.0 * a64.T @ (a64 @ np.ones(n))
+        assert np.all(np.abs(g - ref) <= 2.0 ** -22 * ref)
+
+
+@pytest.mark.parametrize("fmt", ["csr", "sell"])
 def test_fixed_point_pass_is_deterministic(small, fmt):
     """With 64-bit fixed-point column accumulators every sum in an iteration is
     order-independent or in a fixed order, so two runs agree bit for bit."""
