@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "host.h"
+#include "progress.h"
 
 using namespace admmbb;
 
@@ -99,7 +100,7 @@ struct admm_ctx {
   PatState* h_ps = nullptr;  // pinned
   uint32_t* d_heads = nullptr;            // per patient: heads run so far
   volatile uint32_t* h_progress = nullptr;  // pinned, written by every head: heads << 1 | stopped
-  uint32_t heads_queued = 0;              // heads queued so far
+  HeadCount heads;                          // those of the run under way
   double* h_scr = nullptr;   // pinned: 64 doubles of scratch, then
   double* h_in = nullptr;    // a plan (nmax doubles) on its way to the device
   float* h_out = nullptr;    // a gradient (nmax floats) written by the device
@@ -578,20 +579,19 @@ struct admm_ctx {
       if (!dense) launch_head(stop_enabled, 1);
       launch_body(stop_enabled, timing);
     }
-    ++heads_queued;  // one per iteration in every order
   }
 
-  // Waits until every patient has had its first `heads` heads (of those queued
-  // since the context's set-up) and returns whether all have stopped.  The heads
-  // report to pinned memory while the device goes on with what is queued behind
-  // them; where the stream has run dry without them (it failed), the state is
-  // read instead, which reports the failure.
-  bool all_stopped_by(uint32_t heads) {
+  // Waits until every patient has had the first `count` heads of the run and
+  // returns whether all have stopped.  The heads report to pinned memory while
+  // the device goes on with what is queued behind them; where the stream has run
+  // dry without them (it failed), the state is read instead, which reports the
+  // failure.
+  bool all_stopped_by(uint32_t count) {
     uint32_t spins = 0;
     bool all = true;
     for (int p = 0; p < P; ++p) {
       uint32_t w = h_progress[p];
-      while ((((w >> 1) - heads) & 0x7fffffffu) >= 0x40000000u) {
+      while (!heads.reached(w, p, count)) {
         if ((++spins & 0xfffu) == 0 && hipStreamQuery(stream) != hipErrorNotReady) {
           read_state();
           bool st = true;
@@ -633,16 +633,17 @@ struct admm_ctx {
   // the three-launch order the stopping test of each iteration runs in the
   // next one's first launch, and a final one follows the loop.  The host sees a
   // stop some iterations late; those queued behind it are skipped on the device.
+  // The caller has just read the state, so the stream is idle.
   void run(int k, int stop_enabled) {
     if (timing) {
       check(hipEventRecord(ev_a, stream), "hipEventRecord");
       pass_ms_sum = 0.0;
       pass_count = 0;
     }
-    if (dense) {
-      launch_head(stop_enabled, 0);
-      ++heads_queued;
-    }
+    heads.begin(h_progress, P);
+    // one head per iteration in every order, and the dense form's before the first
+    const uint32_t first = dense ? 1 : 0;
+    if (dense) launch_head(stop_enabled, 0);
     const int every = std::max(1, opts.check_every);
     // iterations queued beyond the one whose head the host waits for: enough to
     // keep the device busy while the report of a stop travels and the host
@@ -650,7 +651,6 @@ struct admm_ctx {
     // (a large patient's still load its tiles: 45 us of 2 981 spots x 13).
     // Waiting for each iteration cost 10 to 15 us of idle device each
     const int ahead = dense && n_xjobs <= 4096 ? 4 : 2;
-    const uint32_t base = heads_queued;
     for (int it = 0; it < k; ++it) {
       one_iteration(stop_enabled);
       // without the stopping test the device skips stopped patients by itself:
@@ -662,12 +662,11 @@ struct admm_ctx {
         for (int p = 0; p < P; ++p) all = all && (h_ps[p].stopped != 0);
         if (all) break;
       } else if (stop_enabled && it >= ahead && (it + 1) % every == 0) {
-        if (all_stopped_by(base + static_cast<uint32_t>(it - ahead) + 1)) break;
+        if (all_stopped_by(first + static_cast<uint32_t>(it - ahead) + 1)) break;
       }
     }
     if (!dense) launch_head(stop_enabled, 0);
     if (dense && opts.dense_launches == 3) launch_dense_head(vec_args(stop_enabled), 0, stream);
-    if (!dense || opts.dense_launches == 3) ++heads_queued;
     if (timing) {
       check(hipEventRecord(ev_b, stream), "hipEventRecord");
       check(hipEventSynchronize(ev_b), "hipEventSynchronize");

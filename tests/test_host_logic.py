@@ -5,6 +5,7 @@ from __future__ import annotations
 
 import importlib.util
 import os
+import subprocess
 
 import numpy as np
 import pytest
@@ -45,6 +46,44 @@ def test_bench_kernel_source_key():
     key = bench.kernel_source_hash(src, "__global__ __launch_bounds__(256) void k_xsym(")
     assert len(key) == 16
     assert bench.kernel_source_hash(src, "no such kernel(") == ""
+
+
+def _run_cpp(tmp_path, body):
+    """Compile and run a program over the library's host-only headers."""
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text('#include <cassert>\n#include <cstdio>\n#include "progress.h"\nusing namespace admmbb;\n' + body)
+    csrc = os.path.join(ROOT, "paper_2304_14568_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-pthread", "-I", csrc, str(src), "-o", str(exe)],
+                   check=True)
+    return subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout
+
+
+def test_head_count_starts_from_the_reported_words(tmp_path):
+    """A run that fails after one of its heads was queued: the device has had one
+    more than the host finished counting.  The next run counts from the words
+    it finds, so a word that the failed run left, stop bit included, never passes
+    for a head of the next one; nor does the wrap of the 31-bit count."""
+    _run_cpp(tmp_path, """
+int main() {
+  for (uint32_t had : {0u, 7u, 0x7ffffffdu, 0x7fffffffu}) {
+    uint32_t words[2] = {had << 1, (had + 3) << 1};
+    HeadCount h;
+    h.begin(words, 2);
+    assert(!h.reached(words[0], 0, 1) && !h.reached(words[1], 1, 1));
+    // the first iteration's head runs and stops patient 0; its launch then throws
+    words[0] = (had + 1) << 1 | 1;
+    words[1] = (had + 4) << 1;
+    assert(h.reached(words[0], 0, 1) && h.reached(words[1], 1, 1) && !h.reached(words[0], 0, 2));
+    HeadCount next;
+    next.begin(words, 2);
+    assert(!next.reached(words[0], 0, 1) && !next.reached(words[1], 1, 1));
+    for (uint32_t k = 1; k <= 5; ++k) {
+      const uint32_t w = (had + 1 + k) << 1;
+      assert(next.reached(w, 0, k) && next.reached(w, 0, 1) && !next.reached(w, 0, k + 1));
+    }
+  }
+}
+""")
 
 
 @pytest.mark.slow
