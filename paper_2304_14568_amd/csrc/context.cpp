@@ -37,6 +37,17 @@ inline void check(hipError_t e, const char* what) {
   if (e != hipSuccess) throw HipError{e, what};
 }
 
+// How this process waits for the current device (hipSetDeviceFlags).
+HostWait host_wait() {
+  unsigned flags = 0;
+  if (hipGetDeviceFlags(&flags) != hipSuccess) (void)hipGetLastError();
+  switch (flags & hipDeviceScheduleMask) {
+    case hipDeviceScheduleBlockingSync: return HostWait::sleep;
+    case hipDeviceScheduleYield: return HostWait::yield;
+    default: return HostWait::spin;
+  }
+}
+
 // Waits for a stream when it goes out of scope: declared after the host
 // buffers that queued copies read or write, it keeps them alive until the
 // copies are done, also when a failed call leaves the scope by an exception.
@@ -586,19 +597,16 @@ struct admm_ctx {
   // the device goes on with what is queued behind them; where the stream has run
   // dry without them (it failed), the state is read instead, which reports the
   // failure.
-  bool all_stopped_by(uint32_t count) {
-    uint32_t spins = 0;
+  bool all_stopped_by(uint32_t count, HostWait how) {
     bool all = true;
     for (int p = 0; p < P; ++p) {
-      uint32_t w = h_progress[p];
-      while (!heads.reached(w, p, count)) {
-        if ((++spins & 0xfffu) == 0 && hipStreamQuery(stream) != hipErrorNotReady) {
-          read_state();
-          bool st = true;
-          for (int q = 0; q < P; ++q) st = st && (h_ps[q].stopped != 0);
-          return st;
-        }
-        w = h_progress[p];
+      uint32_t w = 0;
+      auto reached = [&] { return heads.reached(w = h_progress[p], p, count); };
+      if (!wait_report(how, reached, [&] { return hipStreamQuery(stream) != hipErrorNotReady; })) {
+        read_state();
+        bool st = true;
+        for (int q = 0; q < P; ++q) st = st && (h_ps[q].stopped != 0);
+        return st;
       }
       all = all && (w & 1u);
     }
@@ -641,6 +649,7 @@ struct admm_ctx {
       pass_count = 0;
     }
     heads.begin(h_progress, P);
+    const HostWait how = host_wait();
     // one head per iteration in every order, and the dense form's before the first
     const uint32_t first = dense ? 1 : 0;
     if (dense) launch_head(stop_enabled, 0);
@@ -662,7 +671,7 @@ struct admm_ctx {
         for (int p = 0; p < P; ++p) all = all && (h_ps[p].stopped != 0);
         if (all) break;
       } else if (stop_enabled && it >= ahead && (it + 1) % every == 0) {
-        if (all_stopped_by(first + static_cast<uint32_t>(it - ahead) + 1)) break;
+        if (all_stopped_by(first + static_cast<uint32_t>(it - ahead) + 1, how)) break;
       }
     }
     if (!dense) launch_head(stop_enabled, 0);
@@ -2021,19 +2030,17 @@ admm_status pgd_dense(admm_ctx* ctx, const pgd_options& o, int32_t patient, cons
   const int64_t max_rounds =
       1 + static_cast<int64_t>(o.max_iter) * ((o.max_trials + kPgdK - 1) / kPgdK);
   constexpr uint32_t kAhead = 6;
+  const HostWait how = host_wait();
   bool done = false;
   for (int64_t r = 1; r <= max_rounds && !done; ++r) {
     launch_pgd_round(a, 0, par, ++seq, s);
     par ^= 1;
-    uint32_t w = *progress, spins = 0;
-    while ((((w >> 1) - (seq - kAhead)) & 0x7fffffffu) >= 0x40000000u) {
-      if ((++spins & 0xfffu) == 0 && hipStreamQuery(s) != hipErrorNotReady) {
-        check(hipGetLastError(), "PGD launch");
-        check(hipStreamSynchronize(s), "sync");  // reports a failure; else the word is there now
-        if ((((*progress >> 1) - (seq - kAhead)) & 0x7fffffffu) >= 0x40000000u)
-          throw HipError{hipErrorUnknown, "PGD rounds did not report"};
-      }
-      w = *progress;
+    uint32_t w = 0;
+    auto reached = [&] { return ((((w = *progress) >> 1) - (seq - kAhead)) & 0x7fffffffu) < 0x40000000u; };
+    if (!wait_report(how, reached, [&] { return hipStreamQuery(s) != hipErrorNotReady; })) {
+      check(hipGetLastError(), "PGD launch");
+      check(hipStreamSynchronize(s), "sync");  // reports a failure; else the word is there now
+      if (!reached()) throw HipError{hipErrorUnknown, "PGD rounds did not report"};
     }
     done = (w & 1u) != 0;
   }

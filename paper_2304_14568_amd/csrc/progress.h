@@ -2,7 +2,9 @@
 // of pinned memory per patient, the number of heads the patient has had << 1,
 // the lowest bit set once it has stopped.  Host code only, without the runtime.
 #pragma once
+#include <chrono>
 #include <cstdint>
+#include <thread>
 #include <vector>
 
 namespace admmbb {
@@ -22,5 +24,31 @@ struct HeadCount {
     return (((word >> 1) - base[static_cast<size_t>(p)] - heads) & 0x7fffffffu) < 0x40000000u;
   }
 };
+
+// How the host waits for a report, as the process asked the runtime to wait for
+// the device: by spinning (the runtime's default does the same), giving its turn
+// to other threads in between, or asleep.  The last spins for as long as the
+// runtime does before it blocks, then looks every 50 us: a few dense iterations
+// are queued ahead of the one waited for, and a CG iteration takes longer.
+enum class HostWait { spin, yield, sleep };
+
+// Until reached(), or until dry() says that nothing is queued any more that could
+// report; returns whether the report is there.
+template <class Reached, class Dry>
+bool wait_report(HostWait how, Reached reached, Dry dry) {
+  using clock = std::chrono::steady_clock;
+  constexpr std::chrono::microseconds kNap{50};
+  const clock::time_point t0 = clock::now();
+  for (uint32_t spins = 1; !reached(); ++spins) {
+    if ((spins & 63u) == 0 && how == HostWait::yield) std::this_thread::yield();
+    const bool nap = how == HostWait::sleep && (spins & 63u) == 0 && clock::now() - t0 > kNap;
+    if (nap) {
+      std::this_thread::sleep_for(kNap);
+      spins |= 63u;  // once asleep, a look per nap
+    }
+    if ((nap || (spins & 0xfffu) == 0) && dry()) return reached();
+  }
+  return true;
+}
 
 }  // namespace admmbb

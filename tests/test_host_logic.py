@@ -86,6 +86,39 @@ int main() {
 """)
 
 
+def test_host_waits_as_the_process_asked(tmp_path):
+    """A report that comes after 200 ms: asleep the wait takes a few per cent of a
+    core, by spinning all of it; and a stream that runs dry without the report
+    ends the wait in every form."""
+    out = _run_cpp(tmp_path, """
+#include <atomic>
+#include <ctime>
+static double cpu() {
+  timespec t;
+  clock_gettime(CLOCK_THREAD_CPUTIME_ID, &t);
+  return t.tv_sec + 1e-9 * t.tv_nsec;
+}
+int main() {
+  for (HostWait how : {HostWait::sleep, HostWait::yield, HostWait::spin}) {
+    std::atomic<int> word{0};
+    std::thread dev([&] {
+      std::this_thread::sleep_for(std::chrono::milliseconds(200));
+      word = 1;
+    });
+    const double c0 = cpu();
+    assert(wait_report(how, [&] { return word.load() != 0; }, [] { return false; }));
+    printf("%.4f\\n", cpu() - c0);
+    dev.join();
+    int looks = 0;
+    assert(!wait_report(how, [] { return false; }, [&] { return ++looks == 3; }));
+    assert(wait_report(how, [&] { return looks > 3; }, [&] { return ++looks > 3; }));  // there when the stream is dry
+  }
+}
+""")
+    asleep, _, spinning = [float(v) for v in out.split()]
+    assert asleep < 0.04 and spinning > 2 * asleep
+
+
 @pytest.mark.slow
 def test_stored_references_match_the_generator():
     """Every stored oracle minimum of the scenario-count study still describes
