@@ -110,7 +110,7 @@ struct admm_ctx {
   int trace_cap = 0;
   PatState* h_ps = nullptr;  // pinned
   uint32_t* d_heads = nullptr;            // per patient: heads run so far
-  volatile uint32_t* h_progress = nullptr;  // pinned, written by every head: heads << 1 | stopped
+  volatile uint32_t* h_progress = nullptr;  // pinned, written by every head: heads << 1 | stopped; then the dense PGD's
   HeadCount heads;                          // those of the run under way
   double* h_scr = nullptr;   // pinned: 64 doubles of scratch, then
   double* h_in = nullptr;    // a plan (nmax doubles) on its way to the device
@@ -1399,9 +1399,10 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
           "hipHostMalloc");
     {
       void* hp = nullptr;
-      check(hipHostMalloc(&hp, sizeof(uint32_t) * c->P, hipHostMallocCoherent), "hipHostMalloc");
+      // coherent: read by the host while kernels that write it are running
+      check(hipHostMalloc(&hp, sizeof(uint32_t) * (c->P + 1), hipHostMallocCoherent), "hipHostMalloc");
       c->h_progress = static_cast<uint32_t*>(hp);
-      for (int p = 0; p < c->P; ++p) c->h_progress[p] = 0;
+      for (int p = 0; p <= c->P; ++p) c->h_progress[p] = 0;
     }
     launch_fill_f32(reinterpret_cast<float*>(c->d_heads), 0.0f, c->P, c->stream);
     check(hipHostMalloc(reinterpret_cast<void**>(&c->h_scr), sizeof(double) * (64 + 2 * static_cast<size_t>(H.nmax)),
@@ -2001,7 +2002,7 @@ admm_status pgd_dense(admm_ctx* ctx, const pgd_options& o, int32_t patient, cons
     e.alpha = o.alpha > 0 ? o.alpha : 1.0;
     e.pick = -1;
   }
-  volatile uint32_t* progress = reinterpret_cast<volatile uint32_t*>(ctx->h_scr + 32);
+  volatile uint32_t* progress = ctx->h_progress + ctx->P;
   *progress = 0;
   a.progress = const_cast<uint32_t*>(progress);
   check(hipMemcpyAsync(a.st, h0, sizeof(h0), hipMemcpyHostToDevice, s), "H2D");
