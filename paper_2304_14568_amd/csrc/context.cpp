@@ -1546,6 +1546,7 @@ admm_status admm_spot_features(admm_ctx* ctx, int32_t patient, const uint8_t* vo
   const Scen& s0 = ctx->H.scen[pt.scen_begin];
   const Scen& s1 = ctx->H.scen[pt.scen_begin + N - 1];
   std::vector<float> col(static_cast<size_t>(3) * N * n);
+  StreamDrain drain{ctx->stream};
   uint8_t* cls = static_cast<uint8_t*>(ctx->staging(static_cast<size_t>(m)));
   check(hipMemcpyAsync(cls, voxel_class, static_cast<size_t>(m), hipMemcpyHostToDevice, ctx->stream), "H2D");
   for (int c = 0; c < 3; ++c) {
