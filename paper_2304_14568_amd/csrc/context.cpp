@@ -650,6 +650,14 @@ struct admm_ctx {
     }
     heads.begin(h_progress, P);
     const HostWait how = host_wait();
+    // where every patient has stopped before, one iteration (which changes nothing
+    // but completes what a checkpoint left pending): queued ahead, they take 70 us
+    // more at 2 981 spots x 13 scenarios, 300 us at 5 762
+    if (stop_enabled) {
+      bool all = true;
+      for (int p = 0; p < P; ++p) all = all && (h_ps[p].stopped != 0);
+      if (all) k = std::min(k, 1);
+    }
     // one head per iteration in every order, and the dense form's before the first
     const uint32_t first = dense ? 1 : 0;
     if (dense) launch_head(stop_enabled, 0);

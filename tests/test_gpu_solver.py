@@ -195,6 +195,30 @@ def test_solve_that_runs_ahead_of_the_stop_flags(xupdate, launches):
             assert all(np.array_equal(zs[p], S.z(p)) for p in range(2))
 
 
+@pytest.mark.parametrize("xupdate", ["dense", "cg"])
+def test_solve_of_a_stopped_context_is_one_iteration(patients, xupdate):
+    """Solving again where every patient has stopped changes nothing, and queues
+    one iteration, not the run-ahead of a solve under way: a solve of at most one
+    iteration (the limit reached before) takes as long."""
+    import time
+    import paper_2304_14568_amd as A
+    P = patients[0][0]
+    best = {}
+    for limit in (3000, None):
+        with A.Solver(P, xupdate=xupdate, deterministic=1, max_iter=limit or best["iter"] + 1) as S:
+            z, info, st = S.solve()
+            assert st == A.OK
+            best["iter"] = info[0]["iter"]
+            best[limit] = 1e9
+            for _ in range(20):
+                t = time.perf_counter()
+                A.lib.admm_solve(S.ctx, None, None)
+                best[limit] = min(best[limit], time.perf_counter() - t)
+            z2, info2, st2 = S.solve()
+            assert st2 == st and info2 == info and np.array_equal(z[0], z2[0])
+    assert best[3000] < 1.25 * best[None]
+
+
 @pytest.mark.parametrize("precond", [0, 1])
 @pytest.mark.parametrize("n", [65, 1025, 2048, 2049, 4097, 8193])
 def test_cg_step_at_spots_per_thread_edges(n, precond):
