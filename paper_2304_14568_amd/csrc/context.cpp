@@ -154,7 +154,7 @@ struct admm_ctx {
   XJob* d_fjobs = nullptr;
   uint32_t* d_Gq = nullptr;
   XTile* d_xtiles = nullptr;
-  int n_xjobs = 0, n_fjobs = 0, ld_max = 0;
+  int n_xjobs = 0, n_fjobs = 0;
   int64_t gp_elems = 0;
   std::vector<double> factored_rho;  // per patient: penalty of the cached inverse
   int gram_of = -1;                  // patient all of whose Gram matrices d_G holds (-1: none)
@@ -381,7 +381,6 @@ struct admm_ctx {
     f.fjobs = d_fjobs;
     f.Gq = d_Gq;
     f.fpart = d_fpart;
-    f.npmax = ld_max;
     f.npat = P;
     return f;
   }
@@ -1066,6 +1065,25 @@ static int64_t dense_chunk_bytes() {
   return b;
 }
 
+// Work buffers of the dense set-up, in doubles, shared by all patients: each
+// patient's scenarios pass through in chunks, and each buffer is the largest
+// that any one patient asks for.
+struct SweepRoom {
+  int64_t limit = dense_chunk_bytes();
+  int64_t matrix = 0;  // Gram matrices of a chunk, and as much for its sweep matrices
+  int64_t panel = 0;   // 128 x npad per scenario of a chunk, two of them
+  int64_t pivots = 0;  // 128 x 128 pivot inverse per scenario of a chunk
+  // scenarios per chunk of a patient
+  int64_t take(int64_t npad, int64_t scenarios) {
+    const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(scenarios, limit / (16 * npad * npad)));
+    matrix = std::max(matrix, chunk * npad * npad);
+    panel = std::max(panel, chunk * 128 * npad);
+    pivots = std::max(pivots, chunk * 128 * 128);
+    return chunk;
+  }
+  int64_t bytes() const { return 8 * (2 * matrix + 2 * panel + pivots); }
+};
+
 admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, const admm_options* opts,
                              admm_ctx** out) {
   SetupClock clk;
@@ -1155,21 +1173,18 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
     (void)hipGetLastError();  // report only this call's errors
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0)
       return set_err(nullptr, ADMM_E_HIP, "no HIP device available");
-    const int64_t kChunkBytes = dense_chunk_bytes();
-    int64_t need = 0, chunk_need = 0;
+    int64_t need = 0;
+    SweepRoom room;
     bool fits_n = true;
     for (int p = 0; p < num_patients; ++p) {
       const int64_t n = probs[p].n, N = probs[p].num_scen;
       const int64_t npad = (n + 63) / 64 * 64, nb = npad / 64, tiles = nb * (nb + 1) / 2;
       fits_n = fits_n && n <= 8128;
-      const int64_t per_scen = 16 * npad * npad;
-      const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(N, kChunkBytes / per_scen));
-      // the chunk's Gram and sweep matrices with the sweep's U, R panels
-      chunk_need = std::max(chunk_need, chunk * (per_scen + 2 * 8 * 128 * npad));
+      (void)room.take(npad, N);
       // every iteration: packed fp32 inverses, packed fp64 sum of G, tile partials
       need += tiles * 4096 * (4 * N + 8) + tiles * 1024 * N;
     }
-    need += chunk_need;
+    need += room.bytes();
     size_t free_b = 0, total_b = 0;
     const hipError_t e = hipMemGetInfo(&free_b, &total_b);
     if (e != hipSuccess) return set_err(nullptr, ADMM_E_HIP, std::string("hipMemGetInfo: ") + hipGetErrorString(e));
@@ -1220,22 +1235,16 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
     // dense x-update: sizes, offsets and work lists (before the tables go to the device)
     std::vector<XJob> fjobs;
     std::vector<XTile> xtiles;
-    // dense set-up works on chunks of scenarios: G and the sweep matrix (fp64,
-    // npad^2 each) for at most kChunkBytes at a time
-    const int64_t kChunkBytes = dense_chunk_bytes();
     if (c->dense) {
-      int64_t chunk_elems = 0, moff = 0, goff = 0;
+      int64_t moff = 0, goff = 0;
+      SweepRoom room;
       c->chunk_scen.assign(num_patients, 1);
       for (int p = 0; p < num_patients; ++p) {
         Pat& pt = H.pat[p];
         pt.npad = (pt.n + 63) / 64 * 64;
         pt.nbk = pt.npad / 64;
-        c->ld_max = std::max(c->ld_max, pt.npad);
-        const int64_t nn = static_cast<int64_t>(pt.npad) * pt.npad;
         const int64_t tiles = static_cast<int64_t>(pt.nbk) * (pt.nbk + 1) / 2;
-        const int chunk = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(pt.num_scen, kChunkBytes / (16 * nn))));
-        c->chunk_scen[p] = chunk;
-        chunk_elems = std::max(chunk_elems, chunk * nn);
+        c->chunk_scen[p] = static_cast<int>(room.take(pt.npad, pt.num_scen));
         pt.gpack_off = goff;
         goff += tiles * 4096;
         pt.fobj_begin = static_cast<int32_t>(fjobs.size());
@@ -1271,19 +1280,17 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
       }
       c->n_xjobs = static_cast<int>(xtiles.size());
       c->n_fjobs = static_cast<int>(fjobs.size());
-      c->d_G = c->alloc<double>(static_cast<size_t>(chunk_elems));
-      c->d_Aw = c->alloc<double>(static_cast<size_t>(chunk_elems));
+      c->d_G = c->alloc<double>(static_cast<size_t>(room.matrix));
+      c->d_Aw = c->alloc<double>(static_cast<size_t>(room.matrix));
       c->d_Mp = c->alloc<float>(static_cast<size_t>(moff));
       c->d_xpart = c->alloc<double>(static_cast<size_t>(moff / 4096) * 128);
       c->d_c64 = c->alloc<double>(static_cast<size_t>(H.vec_total));
       c->d_b64 = c->upload(H.b64);
       c->d_Gp = c->alloc<double>(static_cast<size_t>(goff));
       c->gp_elems = goff;
-      // the sweep's pivot inverses and panels of the largest chunk
-      const size_t cmax = static_cast<size_t>(*std::max_element(c->chunk_scen.begin(), c->chunk_scen.end()));
-      c->d_Pb = c->alloc<double>(cmax * 128 * 128);
-      c->d_U = c->alloc<double>(cmax * 128 * c->ld_max);
-      c->d_R = c->alloc<double>(cmax * 128 * c->ld_max);
+      c->d_Pb = c->alloc<double>(static_cast<size_t>(room.pivots));
+      c->d_U = c->alloc<double>(static_cast<size_t>(room.panel));
+      c->d_R = c->alloc<double>(static_cast<size_t>(room.panel));
       c->d_fpart = c->alloc<double>(fjobs.size());
       c->d_xtiles = c->upload(xtiles);
       c->d_fjobs = c->upload(fjobs);

@@ -799,8 +799,8 @@ __global__ __launch_bounds__(256) void k_sweep_panel(FactorArgs f, int npad, int
     }
     return;
   }
-  double* Ut = f.U + static_cast<int64_t>(g) * f.npmax * kKb;
-  double* R = f.R + static_cast<int64_t>(g) * f.npmax * kKb;
+  double* Ut = f.U + static_cast<int64_t>(g) * npad * kKb;
+  double* R = f.R + static_cast<int64_t>(g) * npad * kKb;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, m = lane & 15, kk = lane >> 4;
   constexpr int NC = KB / 64;  // 16-row groups of Ut per wave
   v4d acc[NC][4];
@@ -866,8 +866,8 @@ __device__ __forceinline__ void sweep_next_pivot(const FactorArgs& f, int npad, 
   constexpr int kPer = PivotTiles<KBN>::kPer;
   static_assert(4 * kSlab * kLd <= 4 * 16 * 80 && kPivotLds <= 4 * 16 * 80 && kSlab * KBN / 2 % 256 == 0);
   const double* A = f.A + static_cast<int64_t>(g) * npad * npad + static_cast<int64_t>(k1) * npad + k1;
-  const double* Ut = f.U + static_cast<int64_t>(g) * f.npmax * kKb + k1;
-  const double* R = f.R + static_cast<int64_t>(g) * f.npmax * kKb + k1;
+  const double* Ut = f.U + static_cast<int64_t>(g) * npad * kKb + k1;
+  const double* R = f.R + static_cast<int64_t>(g) * npad * kKb + k1;
   const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, kk = lane >> 4;
   PivotTiles<KBN> pt(__builtin_amdgcn_readfirstlane(tid >> 6));
   uint32_t o[kQ];
@@ -991,8 +991,8 @@ __global__ __launch_bounds__(256, 4) void k_sweep_update(FactorArgs f, int npad,
   const int bj = bi + t0;
   double* A = f.A + static_cast<int64_t>(g) * npad * npad;  // chunk buffer
   const int i0 = bi * MT, j0 = bj * MT;
-  const double* Ut = f.U + static_cast<int64_t>(g) * f.npmax * kKb;
-  const double* R = f.R + static_cast<int64_t>(g) * f.npmax * kKb;
+  const double* Ut = f.U + static_cast<int64_t>(g) * npad * kKb;
+  const double* R = f.R + static_cast<int64_t>(g) * npad * kKb;
   const bool rowK = i0 / kKb == k0 / kKb, colK = j0 / kKb == k0 / kKb;
   float* Mt = nullptr;  // the stored tile, formed in LDS first
   float* mt = reinterpret_cast<float*>(lds);

@@ -257,15 +257,14 @@ struct FactorArgs {
   double* Gp;         // per patient: packed sum_s G_s, fp64
   const double* g0;   // per patient: 2 sum_s A_s^T c_s W p, fp64 (zvec layout)
   double* P;          // set-up chunk, per scenario: 128 x 128 pivot-block inverse
-  double* U;          // set-up chunk, per scenario: 128 x npmax column panel, transposed
-  double* R;          // set-up chunk, per scenario: 128 x npmax row panel
+  double* U;          // set-up chunk, per scenario: 128 x npad column panel, transposed
+  double* R;          // set-up chunk, per scenario: 128 x npad row panel
   double* xpart;      // per packed tile of every scenario: T c_J (64) and T^T c_I (64), fp64
   const XTile* xtiles; // x-update: one per packed tile of every scenario
   int32_t nxtiles;
   const XJob* fjobs;  // objective: one per packed tile of every patient
   uint32_t* Gq;       // objective: Gp rounded to 48 bits, tile k of fjobs at 6144 k (layout in fobj_tile)
   double* fpart;      // objective partial per objective job
-  int32_t npmax;      // largest npad
   int32_t npat;       // patients of the context
 };
 

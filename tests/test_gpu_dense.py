@@ -405,6 +405,36 @@ def test_sweep_with_the_next_pivot_beside_the_update(n, num_scen, monkeypatch):
         assert np.all(np.abs(xs[0][s] - ref) <= 2.0 ** -23 * M + 2.0 ** -23 * np.abs(ref).max())
 
 
+def _random_patient(n, num_scen, m, per, seed):
+    rng = np.random.default_rng(seed)
+    As = [synth.Csr(row_ptr=np.arange(0, per * m + 1, per, dtype=np.int64),
+                    col=np.sort(rng.integers(0, n // per, (m, per)) + n // per * np.arange(per), axis=1).astype(np.int32).ravel(),
+                    val=rng.uniform(0.2, 1.0, per * m).astype(np.float32)) for _ in range(num_scen)]
+    return synth.Problem(m=m, n=n, A=As, prob=np.full(num_scen, 1 / num_scen), struct_id=np.zeros(m, np.uint8),
+                         struct_weight=np.ones(1), presc=rng.uniform(0.5, 1.5, m), lb=np.zeros(n), ub=np.full(n, 10.0))
+
+
+def test_set_up_room_of_a_mixed_batch():
+    """A patient of 64 spots and 1 000 scenarios beside one of 2 048 spots and
+    one scenario: the sweep's panels are sized for either patient (131 MB), not for
+    as many scenarios as the one and as many spots as the other (4.3 GB), and both
+    patients iterate as they do alone."""
+    import torch
+    import paper_2304_14568_amd as A
+    Ps = [_random_patient(64, 1000, 128, 4, 1), _random_patient(2048, 1, 4096, 4, 2)]
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    with A.Solver(Ps, xupdate="dense") as S:
+        used = free - torch.cuda.mem_get_info()[0]
+        S.iterate(3)
+        got = [S.z(0), S.z(1)]
+    assert used < 1 << 30
+    for P, z in zip(Ps, got):
+        with A.Solver(P, xupdate="dense") as S:
+            S.iterate(3)
+            assert np.array_equal(S.z(), z)
+
+
 @pytest.mark.parametrize("m,per", [(20000, 64), (400, 40), (130, 13)])
 def test_gram_sums_are_those_of_more_than_64_bits(m, per):
     """The diagonal of the cached Gram matrix, read through the dense form of
