@@ -537,6 +537,11 @@ struct admm_mlp {
     a.splits = (B + a.rows_per_split - 1) / a.rows_per_split;
     return a;
   }
+  // on the net's own stream, which the null stream does not wait for, nor it for that
+  void clear_moments() {
+    admmbb::launch_fill_f32(m, 0.0f, np, stream);
+    admmbb::launch_fill_f32(v, 0.0f, np, stream);
+  }
   // the layers and the scalars
   void forward(const MlpArgs& a, bool bf16) {
     const int smem = 4 * kRows * (lds_stride(H) + std::max(lds_stride(F), lds_stride(H)));
@@ -620,9 +625,10 @@ admm_status mlp_create(int32_t nin, int32_t hidden, uint64_t seed, void* stream,
     for (int j = 0; j < H; ++j) th[n->ow3 + j] = uni(std::sqrt(3.0 / H));
     for (int j = 0; j < H; ++j) th[n->owr + j] = uni(std::sqrt(3.0 / H)) * 0.1f;
     ck(hipMemcpy(n->th, th.data(), sizeof(float) * n->np, hipMemcpyHostToDevice));
-    ck(hipMemset(n->m, 0, sizeof(float) * n->np));
-    ck(hipMemset(n->v, 0, sizeof(float) * n->np));
-    ck(hipMemset(n->g, 0, sizeof(float) * n->np));
+    n->clear_moments();
+    admmbb::launch_fill_f32(n->g, 0.0f, n->np, n->stream);
+    ck(hipGetLastError());
+    ck(hipStreamSynchronize(n->stream));
   } catch (const HipErr& e) {
     delete n;
     return mlp_fail(nullptr, "mlp_create", e.e);
@@ -661,8 +667,9 @@ admm_status mlp_set_params(admm_mlp* n, const float* in) {
   try {
     ck(hipStreamSynchronize(n->stream));
     ck(hipMemcpy(n->th, in, sizeof(float) * n->np, hipMemcpyHostToDevice));
-    ck(hipMemset(n->m, 0, sizeof(float) * n->np));
-    ck(hipMemset(n->v, 0, sizeof(float) * n->np));
+    n->clear_moments();
+    ck(hipGetLastError());
+    ck(hipStreamSynchronize(n->stream));
     n->step = 0;
   } catch (const HipErr& e) {
     return mlp_fail(n, "mlp_set_params", e.e);

@@ -82,6 +82,29 @@ def test_mlp_adam_step_parity():
         _close(net.get_params(), th, 1e-5, 1e-6)
 
 
+def test_mlp_set_params_starts_adam_afresh():
+    """New parameters clear the moments before the next step reads them: a net
+    set back to its first weights repeats its first steps bit for bit, time after
+    time, with no other wait between the clear and the step."""
+    import paper_2304_14568_amd as A
+    rng = np.random.default_rng(5)
+    X = rng.normal(size=(300, 15)).astype(np.float32)
+    t = np.abs(rng.normal(size=300)).astype(np.float32)
+    net = A.Mlp(15, 160, seed=3)
+    theta = net.get_params()
+    want = None
+    for _ in range(20):
+        net.set_params(theta)
+        for _ in range(3):
+            net.loss_grad(X, t, 0.1, 0.2, want_grad=False)
+            net.adam_step(lr=1e-2)
+        got = net.get_params()
+        assert not np.array_equal(got, theta)
+        want = got if want is None else want
+        assert np.array_equal(got, want)
+    net.close()
+
+
 def test_mlp_bf16_inference_close_to_fp32():
     import paper_2304_14568_amd as A
     rng = np.random.default_rng(6)
