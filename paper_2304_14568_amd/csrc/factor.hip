@@ -1674,7 +1674,10 @@ void launch_sweep(FactorArgs f, int patient, int scen_begin, int nscen, int npad
   // than the pivot's chain within it (85 to 105 us, against 32 in a launch of its
   // own): per step, update and pivot 64 + 31 against 103 us with 2 730 tiles over
   // the scenarios, 104 + 31 against 127 us with 4 914, 147 + 32 against 157 us
-  // with 6 864.
+  // with 6 864.  A whole new penalty from 4 096 tiles on, apart against beside, over
+  // other numbers of scenarios: 715 against 700 us at 192 spots x 700, 1 175 against
+  // 1 095 at 707 x 63, 1 390 against 1 290 at 1 000 x 31, 3 410 against 3 000 at
+  // 2 003 x 13, 3 340 against 3 230 at 2 981 x 4, 6 180 against 6 060 at 5 762 x 1.
   const bool beside = static_cast<int64_t>(nt) * nscen >= 4096;
   auto step = [&](auto kbc, auto kbn, auto last, int k0) {
     constexpr int KB = decltype(kbc)::value, KBN = decltype(kbn)::value;
