@@ -90,7 +90,7 @@ struct admm_ctx {
     matlp = fmt == FMT_SELL ? selllp : csrlp;
   }
   // device vectors
-  float *d_x = nullptr, *d_r = nullptr, *d_v = nullptr, *d_q = nullptr, *d_zp = nullptr, *d_y = nullptr;
+  float *d_x = nullptr, *d_r = nullptr, *d_v = nullptr, *d_q = nullptr, *d_y = nullptr;
   float *d_b = nullptr, *d_dinv = nullptr, *d_z = nullptr, *d_lb = nullptr, *d_ub = nullptr;
   float *d_pvec = nullptr, *d_pvec2 = nullptr, *d_pvec3 = nullptr, *d_mvec = nullptr;
   int mvec_scen = 1;        // m-vectors of the largest patient that d_mvec holds
@@ -331,7 +331,6 @@ struct admm_ctx {
     a.r = d_r;
     a.v = d_v;
     a.q = d_q;
-    a.zp = d_zp;
     a.y = d_y;
     a.b = d_b;
     a.dinv = d_dinv;
@@ -1383,7 +1382,6 @@ admm_status admm_setup_batch(const admm_problem* probs, int32_t num_patients, co
     c->d_v = c->alloc<float>(V);
     c->d_q = c->alloc<float>(V);
     c->d_y = c->alloc<float>(V);
-    c->d_zp = o.precond ? c->alloc<float>(V) : c->d_r;
     c->d_dinv = o.precond ? c->upload(H.dinv) : nullptr;
     c->d_b = c->upload(H.b);
     c->d_dprev = c->alloc<double>(V);
@@ -1989,7 +1987,6 @@ admm_status pgd_dense(admm_ctx* ctx, const pgd_options& o, int32_t patient, cons
   a.g0 = ctx->d_g0 + pt.zvec_base;
   a.lb = ctx->d_lb + pt.zvec_base;
   a.ub = ctx->d_ub + pt.zvec_base;
-  a.jobs = ctx->d_fjobs + pt.fobj_begin;
   a.njobs = pt.fobj_end - pt.fobj_begin;
   a.nb = pt.nbk;
   a.n = n;

@@ -203,7 +203,6 @@ struct VecArgs {
   float* r;
   float* v;
   float* q;
-  float* zp;               // preconditioned residual (== r when no preconditioner)
   float* y;
   const float* b;          // A_s^T c_s W p
   const float* dinv;       // Jacobi inverse diagonal (per scenario), may be null
@@ -236,13 +235,11 @@ struct XTile {
   int32_t I, J;    // block row and block column
 };
 
+// One packed tile of sum_s G_s for the objective.
 struct XJob {
-  int32_t g;    // scenario (x-update) or patient (objective)
+  int32_t g;    // patient
   int32_t ij;   // tile (I, J) as I * 65536 + J
 };
-
-// x-update reduction: block row I of one scenario's x_s, with every address
-// it needs, so that its loads depend on this entry only
 
 // Symmetric matrices of the dense x-update are stored as their upper 64 x 64
 // tiles (I <= J) in the order t(I, J) = I nb - I (I - 1) / 2 + (J - I), each
@@ -356,7 +353,6 @@ struct PgdArgs {
   const double* g0;  // 2 sum_s A_s^T c_s W p of the patient, fp64
   const float* lb;
   const float* ub;
-  const XJob* jobs;  // the patient's packed tiles in packed order
   int32_t njobs, nb, n;  // tiles, block rows, spots
   int32_t np;        // n rounded up to whole 64-blocks: length of every vector below
   double* x;         // [2] x np by round parity, zero beyond n

@@ -97,10 +97,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduce(VecArgs a, int blk_be
       a.r[vi] = rf;
       a.x[vi] = zj;
       float zpv = rf;
-      if (a.dinv != nullptr) {
-        zpv = rf * a.dinv[vi];
-        a.zp[vi] = zpv;
-      }
+      if (a.dinv != nullptr) zpv = rf * a.dinv[vi];
       a.v[vi] = zpv;
       const double c = static_cast<double>(a.b[vi]) + 0.5 * rho * zj - 0.5 * static_cast<double>(yv);
       loc[0] = static_cast<double>(rf) * zpv;
@@ -196,7 +193,6 @@ __global__ __launch_bounds__(1024) void k_cg_step(VecArgs a) {
     if (j < sc.n) {
       a.x[sc.vec_base + j] = fmaf(alpha, v[e], x[e]);
       a.r[sc.vec_base + j] = r[e];
-      if (a.dinv != nullptr) a.zp[sc.vec_base + j] = d[e];
       loc += static_cast<double>(r[e]) * d[e];
     }
   }

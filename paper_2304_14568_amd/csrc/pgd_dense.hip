@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256, 5) void k_pgd_tiles(PgdArgs a, int mode, int p
   __shared__ TileLds<kPgdK> s;
   __shared__ double fk[kPgdK], gd[kPgdK];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  const int64_t tile = blockIdx.x;  // jobs are the tiles in packed order
+  const int64_t tile = blockIdx.x;  // in packed order
   int I, J;
   tile_place(static_cast<int>(tile), a.nb, I, J);
   const PgdDevState cur = a.st[par];
