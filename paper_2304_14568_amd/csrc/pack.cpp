@@ -248,8 +248,10 @@ admm_status pack_problems(const admm_problem* probs, int num_patients, const adm
   // against 6 per nonzero), so a tile takes at least 10 n nonzeros, as long as
   // that leaves every workgroup slot (12 n bytes of LDS each, four of 512 threads
   // per CU at most) its share and 256 more.  A CG iteration of one scenario of
-  // 8 501 spots 772 -> 503 us (2 048 -> 512 tiles), three of 5 500 spots 770 ->
-  // 600 us, three of 2 981 spots 439 -> 389 us; 13 of 2 981 spots keep 2 048.
+  // 8 501 spots 783 -> 516 us (2 048 -> 512 tiles), three of 5 500 spots 739 ->
+  // 574 us, three of 2 981 spots 444 -> 388 us; with bf16 values, whose CG passes
+  // read 4 bytes per nonzero, 799 -> 506, 723 -> 562 and 436 -> 382 us; 13 of 2 981
+  // spots keep 2 048.
   (void)nnz_all;
   std::vector<int64_t> tile_chunks_of(num_patients);
   for (int p = 0; p < num_patients; ++p) {

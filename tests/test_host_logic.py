@@ -136,15 +136,16 @@ def test_stored_references_match_the_generator():
     assert all(a < b for a, b in zip(fs, fs[1:]))
 
 
-def test_gram_pair_index_multiply_shift_is_exact():
-    """The tile Gram kernel splits a pair index p of an nI x nJ block of
-    products as a = p / nJ, computed as (p * (2^19 // nJ + 1)) >> 19 in 32-bit
-    arithmetic.  A row's segment in one 64-column block holds at most 64
-    nonzeros plus 3 entries of padding, so nJ <= 67 and p < 67 * 67; the
-    formula must be exact on that whole range and must not overflow."""
-    for nJ in range(1, 68):
-        m = (1 << 19) // nJ + 1
-        p = np.arange(67 * 67, dtype=np.uint64)
-        assert int(p.max()) * m < 2 ** 32
-        a = ((p * np.uint64(m)) & np.uint64(0xFFFFFFFF)) >> np.uint64(19)
-        assert np.array_equal(a, p // np.uint64(nJ))
+def test_packed_tile_number_to_its_blocks():
+    """The dense PGD finds the blocks (I, J), I <= J, of packed tile number t from a
+    float32 square root and a correction by whole rows (t(I, I) = I nb - I (I - 1)
+    / 2, J = I + t - t(I, I)): the root is within one of the row for every tile of
+    up to 128 blocks, so the correction takes at most one step."""
+    f = np.float32
+    for nb in range(1, 129):
+        first = np.array([i * nb - i * (i - 1) // 2 for i in range(nb)])
+        t = np.arange(nb * (nb + 1) // 2)
+        b = f(2 * nb + 1)
+        root = (f(0.5) * (b - np.sqrt(np.maximum(b * b - f(8) * t.astype(f), f(0))))).astype(np.int32)
+        row = np.searchsorted(first, t, side="right") - 1
+        assert np.all(np.abs(np.clip(root, 0, nb - 1) - row) <= 1)
