@@ -208,7 +208,8 @@ def test_dense_setup_in_scenario_chunks_matches_one_chunk(probs, monkeypatch):
     with A.Solver(P, xupdate="dense", use_graph=0) as S:
         S.iterate(15)
         z_chunked = S.z()
-    # the Gram matrices sum with fp64 atomics (order-dependent in the last bits)
+    # (every sum is in an order that the chunks do not change; the bits are
+    # compared in test_new_penalty_equals_a_fresh_set_up)
     assert np.linalg.norm(z_chunked - z_one) <= 1e-6 * np.linalg.norm(z_one)
 
 

@@ -116,6 +116,8 @@ def test_checkpoint_resume_is_exact(patients):
 
 @pytest.mark.parametrize("xupdate", ["cg", "dense"])
 def test_graph_replay_matches_direct_launches(patients, xupdate):
+    """A CG iteration replayed from a captured graph against its direct launches,
+    bit for bit; the dense iteration launches directly whatever the option says."""
     import paper_2304_14568_amd as A
     P = patients[0][0]
     out = []
