@@ -273,11 +273,11 @@ __global__ __launch_bounds__(1024) void k_gram_scan(const int32_t* __restrict__ 
 // (1 500 to 2 300 rows) is 4.8e-17 off (relative, root mean square), where 64-bit
 // fixed-point sums of one product at a time through LDS atomics (17.7 ms at 13
 // scenarios of 2 981 spots) leave 6e-17 to 9e-17 and a running fp64 sum over the
-// list 1.2e-15 to 1.5e-15.  The residuals and their
-// registers (three workgroups per CU instead of four) cost 8.8 instead of 5.3
-// ms there, 3.7 instead of 2.3 ms at 1 700 spots; four workgroups
-// with spills (12 ms) or eight waves with an eighth of the tile each (9 to 12 ms)
-// are no faster.
+// list 1.2e-15 to 1.5e-15.  The residuals and their registers (three workgroups
+// per CU instead of four) cost 8.8 instead of 5.3 ms there, 3.7 instead of 2.3 ms
+// at 1 700 spots; four workgroups with spills (12 ms) or eight waves with an
+// eighth of the tile each (9 to 12 ms) are no faster.
+//
 // The next rows are requested before the products of the current ones.  Padding
 // (value 0, the last column repeated) is left out.
 constexpr int kGramWaves = 4;
